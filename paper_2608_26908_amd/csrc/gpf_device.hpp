@@ -303,6 +303,15 @@ __device__ __forceinline__ void project_masked(unsigned mask, const R (&v)[N], R
     out[i] = (((mask >> i) & 1u) && v[i] - theta > R(0)) ? v[i] - theta : R(0);
 }
 
+// Barrier of a block whose threads exchange data through LDS only: unlike
+// __syncthreads() it does not order (and so does not wait for) the global
+// loads in flight.
+__device__ __forceinline__ void block_sync_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Neighbour coordinate along one axis for field values: periodic axes wrap,
 // walls mirror the adjacent cell (zero normal derivative).
 __device__ __forceinline__ int nb_field(int x, int s, int n, int per) {

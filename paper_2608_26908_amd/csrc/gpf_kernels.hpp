@@ -1,8 +1,8 @@
 // gpf_kernels.hpp -- HIP kernels of the coupled GP phase-field / LBM step.
 //
-// One step = two z-marching launches over TX x TY tiles of (x, y):
+// One step = two launches over tiles of cells:
 //   k_phi_z    phi^n, mu^n            -> phi^{n+1}          (Eq. PhfGrand, Sec. 2.1)
-//   k_mulbm_z  phi^n, phi^{n+1}, mu^n, U^{n-1}, f*^{n-1}
+//   k_mulbm    phi^n, phi^{n+1}, mu^n, U^{n-1}, f*^{n-1}
 //                                     -> mu^{n+1}, U^n, f*^n (Eq. conc; Eqs. LBMEq_1,
 //                                        f^eq, discreteForce, buoyancy, rhovel)
 // f buffers hold post-collision, pre-streaming populations as deviations
@@ -55,80 +55,100 @@ __device__ __forceinline__ T* lane_at(T* base, int64_t u, int l) {
   return reinterpret_cast<T*>(reinterpret_cast<C*>(base + u) + (uint32_t)l * (uint32_t)sizeof(T));
 }
 
-// Source columns of the pulls of one lane along x, fixed for a z-marching
-// thread: xs[1 - c_x] is the column of the cell P - c_k (wrapped on a
-// periodic axis, clamped at a wall) and xw[1 - c_x] says it lies behind a wall.
-struct PullX {
+// A scalar pointer that the compiler may not re-derive: stepping it from one
+// component to the next costs two scalar additions, where forming every
+// component's address anew costs a 64-bit multiplication each.
+template <class T> __device__ __forceinline__ void opaque_ptr(T*& q) { asm volatile("" : "+s"(q)); }
+
+// Streaming stores of the C components v of one cell: element u + l of each.
+template <int C, class R>
+__device__ __forceinline__ void store_comps(const KP<R>& p, R* __restrict__ out, int64_t u, int l, const R (&v)[C]) {
+  R* q = out + u;
+  opaque_ptr(q);
+#pragma unroll
+  for (int k = 0; k < C; ++k) {
+    __builtin_nontemporal_store(v[k], lane_at(q, 0, l));
+    if (k + 1 < C) {
+      q += p.cells;
+      opaque_ptr(q);
+    }
+  }
+}
+
+// Source cells of the pulls of one lane, as element offsets: xs, ys, zs at
+// index 1 - c is the cell P - c_k's part along that axis (wrapped on a
+// periodic axis, clamped at a wall); w*: the source with c = +1 (index 0) or
+// c = -1 (index 2) lies behind a wall.  With ROW a wave's lanes share their
+// row, so ys joins zs in the scalar part of the address.
+template <bool ROW> struct PullAt {
+  using YS = typename std::conditional<ROW, int64_t, int>::type;
   int xs[3];
-  bool xw[3];
+  YS ys[3];
+  int64_t zs[3];
+  bool wx[3], wy[3], wz[3];
 };
-__device__ __forceinline__ PullX pull_x(int x, int n0, int per0) {
-  PullX q;
-  q.xs[1] = x;
-  q.xw[1] = false;
-  q.xw[0] = !per0 && x - 1 < 0;
-  q.xw[2] = !per0 && x + 1 >= n0;
-  q.xs[0] = (x - 1 < 0) ? (per0 ? x - 1 + n0 : 0) : x - 1;
-  q.xs[2] = (x + 1 >= n0) ? (per0 ? x + 1 - n0 : n0 - 1) : x + 1;
+template <int D, bool ROW, class R>
+__device__ __forceinline__ PullAt<ROW> pull_at(const KP<R>& p, int x, int y, int z) {
+  PullAt<ROW> q;
+  auto axis = [](int v, int n, int per, int (&s)[3], bool (&w)[3]) {
+    s[1] = v;
+    w[1] = false;
+    w[0] = !per && v - 1 < 0;
+    w[2] = !per && v + 1 >= n;
+    s[0] = (v - 1 < 0) ? (per ? v - 1 + n : 0) : v - 1;
+    s[2] = (v + 1 >= n) ? (per ? v + 1 - n : n - 1) : v + 1;
+  };
+  int ys[3], zs[3] = {0, 0, 0};
+  q.wz[0] = q.wz[1] = q.wz[2] = false;
+  axis(x, p.n[0], p.per[0], q.xs, q.wx);
+  axis(y, p.n[1], p.per[1], ys, q.wy);
+  if constexpr (D == 3) axis(z, p.n[2], p.per[2], zs, q.wz);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    q.ys[i] = (typename PullAt<ROW>::YS)ys[i] * (typename PullAt<ROW>::YS)p.sy;
+    q.zs[i] = (int64_t)zs[i] * p.sz;
+  }
   return q;
 }
 
-// The populations f^n of the cell (x, y, z) for a wave whose lanes share the
-// row y and plane z (what pull_f does cell by cell): the source row and plane
-// of population k, and with them a wall between source and cell along y or z,
-// are the same on every lane, so they are decided with scalar arithmetic and
-// only the x walls of the grid's first and last column differ between lanes.
-template <int D, int Q, class R>
-__device__ __forceinline__ void pull_row(const KP<R>& p, const R* __restrict__ fin, int x, int y, int z,
-                                         const PullX& px, R (&f)[Q]) {
+// The populations f^n of the cell (x, y, z) (what pull_f does cell by cell)
+// for a wave whose lanes share the plane z and, with ROW, the row y: each
+// access is a scalar base plus the lane's 32-bit offset.  Every source is
+// loaded first (clamped at walls); then the cells at a wall, in tiles at the
+// grid's faces only, take the reflected population f*_{opp k}(P) instead
+// (half-way bounce-back).
+template <int D, int Q, bool ROW, class R>
+__device__ __forceinline__ void pull_cell(const KP<R>& p, const R* __restrict__ fin, const PullAt<ROW>& px,
+                                          R (&f)[Q]) {
   using L = Lat<Q>;
-  const int64_t own = (int64_t)z * p.sz + (int64_t)y * p.sy;
-  // source row and plane of population k; false when behind a y or z wall
-  auto src = [&](int k, int64_t& row) -> bool {
-    int ys = y - L::c(k, 1), zs = (D == 3) ? z - L::c(k, 2) : z;
-    bool in = true;
-    if (ys < 0 || ys >= p.n[1]) {
-      if (p.per[1])
-        ys += (ys < 0) ? p.n[1] : -p.n[1];
-      else
-        in = false;
+  const R* q = fin;
+  opaque_ptr(q);
+#pragma unroll
+  for (int k = 0; k < Q; ++k) {
+    const int ix = 1 - L::c(k, 0), iy = 1 - L::c(k, 1), iz = 1 - L::c(k, 2);
+    f[k] = __builtin_nontemporal_load(
+        lane_at(q, px.zs[iz] + (ROW ? (int64_t)px.ys[iy] : 0), px.xs[ix] + (ROW ? 0 : (int)px.ys[iy])));
+    if (k + 1 < Q) {
+      q += p.cells;
+      opaque_ptr(q);
     }
-    if (D == 3 && (zs < 0 || zs >= p.n[2])) {
-      if (p.per[2])
-        zs += (zs < 0) ? p.n[2] : -p.n[2];
-      else
-        in = false;
-    }
-    row = (int64_t)zs * p.sz + (int64_t)ys * p.sy;
-    return in;
-  };
-  // reflected population at the cell itself (half-way bounce-back), plus the
-  // moving-lid term where the source lies above the upper y wall
+  }
   auto bounce = [&](int k) -> R {
-    R val = *lane_at(fin, (int64_t)L::opp(k) * p.cells + own, x);
-    if (L::c(k, 1) < 0 && !p.per[1] && y - L::c(k, 1) >= p.n[1])
-      val += R(6 * L::w(k)) * p.rho0 * R(L::c(k, 0)) * p.lid_u;
+    R val = *lane_at(fin, (int64_t)L::opp(k) * p.cells + px.zs[1] + (ROW ? (int64_t)px.ys[1] : 0),
+                     px.xs[1] + (ROW ? 0 : (int)px.ys[1]));
+    // the moving lid: sources above the upper y wall
+    if (L::c(k, 1) < 0 && px.wy[2]) val += R(6 * L::w(k)) * p.rho0 * R(L::c(k, 0)) * p.lid_u;
     return val;
   };
 #pragma unroll
-  for (int k = 0; k < Q; ++k) {
-    int64_t row;
-    if (src(k, row))
-      f[k] = __builtin_nontemporal_load(lane_at(fin, (int64_t)k * p.cells + row, px.xs[1 - L::c(k, 0)]));
-    else
-      f[k] = bounce(k);
-  }
-  // lanes whose x source lies behind a wall (the tiles at x = 0 and n0 - 1)
+  for (int a = 0; a < D; ++a)
 #pragma unroll
-  for (int side = 0; side < 3; side += 2) {
-    if (px.xw[side]) {
+    for (int side = 0; side < 3; side += 2)
+      if (a == 0 ? px.wx[side] : (a == 1 ? px.wy[side] : px.wz[side])) {
 #pragma unroll
-      for (int k = 0; k < Q; ++k) {
-        int64_t row;
-        if (1 - L::c(k, 0) == side && src(k, row)) f[k] = bounce(k);
+        for (int k = 0; k < Q; ++k)
+          if (1 - L::c(k, a) == side) f[k] = bounce(k);
       }
-    }
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -315,155 +335,58 @@ __device__ __forceinline__ bool phi_from_stencil(const KP<R>& p, const R (&v)[N]
   return false;
 }
 
-// ---------------------------------------------------------------------------
-// mu^{n+1}, U^n and the post-collision populations of cell (x, y, z), given
-// the values it reads around itself:
-//   ph1n[0] / mun[0]: phi^{n+1} / mu^n at the cell, ph1n[1 + 2a + s] / mun[..]
-//   at its -e_a (s = 0) and +e_a (s = 1) neighbours (wrapped on periodic
-//   axes; never used across walls); uc: U^{n-1} at the cell; un[a][s]: the
-//   a-component of U^{n-1} at those neighbours; ph0: phi^n at the cell.
-// The populations are pulled from fin (the previous post-collision f*).
-// ---------------------------------------------------------------------------
-// SH: the shrinkage force is on (a separate instance keeps the registers of
-// the common case unchanged)
 // T - T_E of a cell at pull-axis coordinate c, step shift ts
 template <class R>
 __device__ __forceinline__ R tdev_at(const KP<R>& p, int c, R ts) {
   return (p.G != R(0)) ? p.G * (R(c) - ts) : p.tdev_iso;
 }
 
-// MT: the equilibrium compositions depend on T (some mT != 0); a separate
-// instance keeps the registers of the common case
-template <int D, int Q, int N, int NC, class R, bool SH, bool MT>
-__device__ __forceinline__ void mulbm_core(const KP<R>& p, int x, int y, int z, const PullX& px, R ts0,
-                                           const R (&ph1n)[2 * D + 1][N],
-                                           const R (&mun)[2 * D + 1][NC], const R (&uc)[D],
-                                           const R (&un)[D][2], const R (&ph0)[N],
-                                           const R* __restrict__ fin, R* __restrict__ mu_out,
-                                           R* __restrict__ u_out, R* __restrict__ fout,
-                                           R* __restrict__ dr_out) {
-  using L = Lat<Q>;
-  const int64_t own = (int64_t)z * p.sz + (int64_t)y * p.sy;  // the cell is own + x
-  const int pos[3] = {x, y, z};
-  // T^n - T_E at the cell and at its neighbours (slots of ph1n); only the
-  // neighbours along the pull axis differ from the cell
-  const int pa = p.pull_axis;
-  const R tdc = MT ? tdev_at(p, pos[pa], ts0) : R(0);
-  auto tdev_slot = [&](int slot) -> R {
-    if constexpr (!MT) return R(0);
-    if (slot == 0) return tdc;
-    const int a = (slot - 1) / 2;
-    if (a != pa) return tdc;
-    return tdev_at(p, nb_field(pos[a], ((slot - 1) & 1) ? 1 : -1, p.n[a], p.per[a]), ts0);
-  };
+// C^b_i(mu, T) of one cell, mu as stored; MT: the equilibrium compositions
+// depend on T (some mT != 0; an instance of its own keeps the registers of
+// the common case)
+template <int N, int NC, class R, bool MT>
+__device__ __forceinline__ R comp_of(const KP<R>& p, int b, int i, const R (&m)[NC], R td) {
+  R C = p.c0s[b][i];
+  if constexpr (MT) C += p.mT[b][i] * td;
+#pragma unroll
+  for (int k = 0; k < NC; ++k) C += p.chi[i][k] * m[k];
+  return C;
+}
 
-  // pull streaming of the previous post-collision populations: issued first,
-  // so the loads are in flight during the chemical-potential update, where
-  // that costs no occupancy (FP32, two phases, one solute; elsewhere the
-  // populations held through the update take the kernel past a register
-  // threshold)
-  constexpr bool EARLY = !SH && !MT && N == 2 && NC == 1 && sizeof(R) == 4;
-  R f[L::Q];
-  if constexpr (EARLY) pull_row<D, Q, R>(p, fin, x, y, z, px, f);
-
-  // per-cell quantities at phi^{n+1}: c* = sum h C(mu^n, T^n), M = sum phi D chi
-  auto quant = [&](int slot, R (&M)[NC][NC], R (&cs)[NC]) {
-    const R td = tdev_slot(slot);
-    R ph[N], h[N];
+// What a face of the chemical-potential update takes from one of its two
+// cells besides mu: the mixture composition c*_i = sum_b h_b(phi^{n+1})
+// C^b_i(mu^n, T^n) and the diffusivity d_i = sum_b phi_b D^b_i (the mobility
+// is M_ik = d_i chi_ik).
+template <int N, int NC, class R, bool MT>
+__device__ __forceinline__ void face_quant(const KP<R>& p, const R (&ph)[N], const R (&m)[NC], R td, R (&cs)[NC],
+                                           R (&d)[NC]) {
+  R h[N];
+  interp_h<N, R>(ph, h);
 #pragma unroll
-    for (int b = 0; b < N; ++b) ph[b] = ph1n[slot][b];
-    interp_h<N, R>(ph, h);
-#pragma unroll
-    for (int i = 0; i < NC; ++i) {
-      cs[i] = R(0);
-#pragma unroll
-      for (int k = 0; k < NC; ++k) M[i][k] = R(0);
-    }
+  for (int i = 0; i < NC; ++i) {
+    cs[i] = R(0);
+    d[i] = R(0);
 #pragma unroll
     for (int b = 0; b < N; ++b) {
-#pragma unroll
-      for (int i = 0; i < NC; ++i) {
-        R C = p.c0s[b][i];
-        if constexpr (MT) C += p.mT[b][i] * td;
-#pragma unroll
-        for (int k = 0; k < NC; ++k) C += p.chi[i][k] * mun[slot][k];
-        cs[i] += h[b] * C;
-#pragma unroll
-        for (int k = 0; k < NC; ++k) M[i][k] += ph[b] * p.D[b][i] * p.chi[i][k];
-      }
+      cs[i] += h[b] * comp_of<N, NC, R, MT>(p, b, i, m, td);
+      d[i] += ph[b] * p.D[b][i];
     }
-  };
+  }
+}
 
-  R MP[NC][NC], cP[NC];
-  quant(0, MP, cP);
-  R divJ[NC];
-#pragma unroll
-  for (int i = 0; i < NC; ++i) divJ[i] = R(0);
-  const R conv = p.conv;  // lattice velocity -> phase-field units
-  const R idx = p.idx;
-#pragma unroll
-  for (int a = 0; a < D; ++a) {
-#pragma unroll
-    for (int si = 0; si < 2; ++si) {
-      const int s = si ? 1 : -1;
-      const bool wall = !p.per[a] && ((s < 0 && pos[a] == 0) || (s > 0 && pos[a] == p.n[a] - 1));
-      if (wall) continue;
-      const int slot = 1 + 2 * a + si;
-      R MQ[NC][NC], cQ[NC];
-      quant(slot, MQ, cQ);
-      const R uf = R(0.5) * (uc[a] + un[a][si]) * conv;
-#pragma unroll
-      for (int i = 0; i < NC; ++i) {
-        R JD = R(0);
-#pragma unroll
-        for (int k = 0; k < NC; ++k)
-          JD += -R(0.5) * (MP[i][k] + MQ[i][k]) * (R(s) * (mun[slot][k] - mun[0][k]) * idx);
-        const R JA = uf * R(0.5) * (cP[i] + cQ[i]);
-        divJ[i] += R(s) * (JD + JA) * idx;
-      }
-    }
-  }
-  R ph1[N], h0[N], h1[N];
-#pragma unroll
-  for (int b = 0; b < N; ++b) ph1[b] = ph1n[0][b];
-  interp_h<N, R>(ph0, h0);
-  interp_h<N, R>(ph1, h1);
-  R Dl[NC];
-#pragma unroll
-  for (int i = 0; i < NC; ++i) Dl[i] = -p.dt * divJ[i];
-  // dh/dt source with C at T^n, and the dT/dt term of Eq. (conc) over the
-  // step, -sum_b h_b^{n+1} (C^b(mu^n, T^{n+1}) - C^b(mu^n, T^n)) = -sum_b
-  // h_b^{n+1} mT[b] (T^{n+1} - T^n)
-  const R td0 = tdev_slot(0);
-  R sh = R(0);
-#pragma unroll
-  for (int b = 0; b < N; ++b) {
-    sh += h1[b];
-#pragma unroll
-    for (int i = 0; i < NC; ++i) {
-      R C = p.c0s[b][i];
-      if constexpr (MT) C += p.mT[b][i] * td0;
-#pragma unroll
-      for (int k = 0; k < NC; ++k) C += p.chi[i][k] * mun[0][k];
-      Dl[i] -= C * (h1[b] - h0[b]);
-      if constexpr (MT) Dl[i] -= h1[b] * (p.mT[b][i] * p.dtdev);
-    }
-  }
-  R mn[NC];
-  if (NC == 1) {
-    mn[0] = mun[0][0] + Dl[0] / (sh * p.chi[0][0]);
-  } else {
-    const R a11 = sh * p.chi[0][0], a12 = sh * p.chi[0][1];
-    const R a21 = sh * p.chi[1][0], a22 = sh * p.chi[1][NC - 1];
-    const R det = a11 * a22 - a12 * a21;
-    mn[0] = mun[0][0] + (a22 * Dl[0] - a12 * Dl[NC - 1]) / det;
-    mn[NC - 1] = mun[0][NC - 1] + (-a21 * Dl[0] + a11 * Dl[NC - 1]) / det;
-  }
-#pragma unroll
-  for (int i = 0; i < NC; ++i) __builtin_nontemporal_store(mn[i], lane_at(mu_out, i * p.cells + own, x));
-
-  // ---- LBM: pull streaming of the previous post-collision populations ----
-  if constexpr (!EARLY) pull_row<D, Q, R>(p, fin, x, y, z, px, f);
+// ---------------------------------------------------------------------------
+// Forces, moments and collision of one cell from its streamed populations f
+// (deviations): U^n and the post-collision populations, stored at element
+// u + l of each component.  phi^n, phi^{n+1}, mu^{n+1} at the cell; g1: the
+// differences phi^{n+1}_b(P + e_a) - phi^{n+1}_b(P - e_a) that the shrinkage
+// force (SH) takes its normals from; td0: T^n - T_E.
+// ---------------------------------------------------------------------------
+template <int D, int Q, int N, int NC, class R, bool SH, bool MT>
+__device__ __forceinline__ void collide_cell(const KP<R>& p, int64_t u0, int l0, const R (&f)[Q], const R (&ph0)[N],
+                                             const R (&ph1)[N], const R (&mn)[NC], const R (&g1)[SH ? N : 1][D],
+                                             R td0, R* __restrict__ u_out, R* __restrict__ fout,
+                                             R* __restrict__ dr_out) {
+  using L = Lat<Q>;
   // moments (deviation storage: rho = rho0 + sum f~, momentum = sum f~ c)
   R dr = R(0), mom[D];
 #pragma unroll
@@ -476,15 +399,13 @@ __device__ __forceinline__ void mulbm_core(const KP<R>& p, int x, int y, int z, 
       if (L::c(k, a) != 0) mom[a] += R(L::c(k, a)) * f[k];
   }
   const R rho = p.rho0 + dr;
-  if (dr_out) *lane_at(dr_out, own, x) = dr;  // kept for the adjoint sweep
+  if (dr_out) *lane_at(dr_out, u0, l0) = dr;  // kept for the adjoint sweep
   const R phil = ph1[N - 1];
   R bsum = R(0);
 #pragma unroll
   for (int i = 0; i < NC; ++i) {
-    R Cl = p.c0s[N - 1][i];
-    if constexpr (MT) Cl += p.mT[N - 1][i] * (td0 + p.dtdev);  // the liquid at T^{n+1}
-#pragma unroll
-    for (int k = 0; k < NC; ++k) Cl += p.chi[i][k] * mn[k];
+    // the liquid at T^{n+1}
+    const R Cl = comp_of<N, NC, R, MT>(p, N - 1, i, mn, td0 + p.dtdev);
     bsum += p.gbeta[i] * (Cl - p.c_ref[i]);
   }
   R FB[D];
@@ -493,19 +414,19 @@ __device__ __forceinline__ void mulbm_core(const KP<R>& p, int x, int y, int z, 
   FB[p.grav_axis] = -rho * phil * bsum * p.grav_sign;
   if constexpr (SH) {
     // shrinkage, Eq. (shrinkage): eta_b (phi^{n+1}_b - phi^n_b) along the unit
-    // normal of phi^{n+1}_b (central differences over the 7-point values held
-    // for the mu update; walls mirrored), per lattice step
+    // normal of phi^{n+1}_b (central differences, walls mirrored), per lattice
+    // step
 #pragma unroll
     for (int b = 0; b < N; ++b) {
       if (p.eta[b] == R(0)) continue;
       R g[D], gg = R(0);
 #pragma unroll
       for (int a = 0; a < D; ++a) {
-        g[a] = (ph1n[2 + 2 * a][b] - ph1n[1 + 2 * a][b]) / (R(2) * p.dx);
+        g[a] = g1[b][a] / (R(2) * p.dx);
         gg += g[a] * g[a];
       }
       if (gg > p.qmin2) {
-        const R s = p.eta[b] * (ph1n[0][b] - ph0[b]) / gsqrt(gg);
+        const R s = p.eta[b] * (ph1[b] - ph0[b]) / gsqrt(gg);
 #pragma unroll
         for (int a = 0; a < D; ++a) FB[a] += s * g[a];
       }
@@ -525,34 +446,54 @@ __device__ __forceinline__ void mulbm_core(const KP<R>& p, int x, int y, int z, 
     uu += u[a] * u[a];
     uF += u[a] * F[a];
   }
-  const R pref = p.guo;
+  // f*_k = f_k + omega (feq_k - f_k) + S_k, written per pair of opposite
+  // velocities as keep f_k + w_k (even +- odd):
+  //   even = omega dr - 3/2 omega rho u.u - 3 guo u.F + (c.u) (c.h),
+  //   odd = c.g,  g = 3 (omega rho u + guo F),  h = 9/2 omega rho u + 9 guo F
+  // (10 operations per pair instead of 30; 1 - omega is exact for tau <= 2)
+  const R orho = p.omega * rho;
+  const R keep = R(1) - p.omega;
+  const R e0 = p.omega * dr - R(1.5) * orho * uu - R(3) * p.guo * uF;
+  R g[D], h[D];
 #pragma unroll
-  for (int k = 0; k < L::Q; ++k) {
-    R cu = R(0), cF = R(0);
+  for (int a = 0; a < D; ++a) {
+    g[a] = R(3) * (orho * u[a] + p.guo * F[a]);
+    h[a] = R(4.5) * orho * u[a] + R(9) * p.guo * F[a];
+  }
+  R fp[L::Q];
+  fp[0] = keep * f[0] + R(L::w(0)) * e0;
+#pragma unroll
+  for (int k = 1; k < L::Q; ++k) {
+    constexpr auto opp = [](int q) { return L::opp(q); };
+    const int kb = opp(k);
+    if (kb < k) continue;
+    R cu = R(0), cg = R(0), ch = R(0);
 #pragma unroll
     for (int a = 0; a < D; ++a) {
       if (L::c(k, a) != 0) {
         cu += R(L::c(k, a)) * u[a];
-        cF += R(L::c(k, a)) * F[a];
+        cg += R(L::c(k, a)) * g[a];
+        ch += R(L::c(k, a)) * h[a];
       }
     }
-    const R wk = R(L::w(k));
-    const R feq = wk * (dr + rho * (R(3) * cu + R(4.5) * cu * cu - R(1.5) * uu));
-    const R S = pref * wk * (R(3) * (cF - uF) + R(9) * cu * cF);
-    __builtin_nontemporal_store(f[k] - (f[k] - feq) * p.omega + S, lane_at(fout, k * p.cells + own, x));
+    const R even = R(L::w(k)) * (e0 + cu * ch), odd = R(L::w(k)) * cg;
+    fp[k] = keep * f[k] + (even + odd);
+    fp[kb] = keep * f[kb] + (even - odd);
   }
-#pragma unroll
-  for (int a = 0; a < D; ++a) __builtin_nontemporal_store(u[a], lane_at(u_out, a * p.cells + own, x));
+  store_comps<L::Q, R>(p, fout, u0, l0, fp);
+  store_comps<D, R>(p, u_out, u0, l0, u);
 }
 
-// coordinate along one axis of a tile-halo cell: periodic axes wrap, walls
-// clamp (values across a wall are never used: wall faces carry no flux)
+// coordinate along one axis of a tile-halo cell, v >= -1: periodic axes wrap,
+// walls clamp (values across a wall are never used: wall faces carry no
+// flux).  Beyond n, the first cell past a periodic grid, nothing is used
+// either: those cells only have to lie inside.
 __device__ __forceinline__ int wrap_or_clamp(int v, int n, int per) {
-  if (per) return ((v % n) + n) % n;
-  return v < 0 ? 0 : (v >= n ? n - 1 : v);
+  if (v < 0) return per ? v + n : 0;
+  return v >= n ? (per ? min(v - n, n - 1) : n - 1) : v;
 }
 
-// Tile of a z-marching block.  Work-groups are dealt to the 8 XCDs
+// Tile of a phase-field block.  Work-groups are dealt to the 8 XCDs
 // round-robin; renumbering gives each XCD a contiguous range of tiles, so
 // tiles that are neighbours in y and z share its L2.
 struct Tile {
@@ -631,7 +572,7 @@ __device__ __forceinline__ void phi_walk(const KP<R>& p, const R* __restrict__ p
   };
   auto update = [&](int z, int sm, int s0, int sp) {
     if (!own) return;
-    int xq = x, yq = y;  // opaque per plane, as in k_mulbm_z
+    int xq = x, yq = y;  // opaque per plane: addresses are formed anew, not carried along z
     asm volatile("" : "+v"(xq), "+v"(yq));
     R v[N][3][3][3];
     const int sl[3] = {sm, s0, sp};
@@ -764,7 +705,7 @@ k_phi_z(KP<R> p, const R* __restrict__ phi, const R* __restrict__ mu, R* __restr
 // walks a contiguous part of the list (whose waves append in about the order
 // of the tiles), so tiles that are neighbours share its L2 as in k_phi_z.
 // count is the length of the list; it starts at zero, and the step's
-// k_mulbm_z, which runs after k_phi_zl, clears it for the next step.
+// k_mulbm, which runs after k_phi_zl, clears it for the next step.
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ void __launch_bounds__(256)
@@ -817,224 +758,254 @@ k_phi_zl(KP<R> p, const R* __restrict__ phi, const R* __restrict__ mu, R* __rest
 }
 
 // ---------------------------------------------------------------------------
-// Chemical potential + LBM, z-marching.  Each thread walks its (x, y) column
-// along z: phi^{n+1}, mu^n and U_z^{n-1} of the planes z-1, z, z+1 at its own
-// column stay in registers (one new plane is loaded per step), and the
-// in-plane neighbours (x +- 1, y +- 1) of phi^{n+1}, mu^n, U_x, U_y come from
-// a double-buffered LDS tile: each thread writes its own column's values from
-// registers, and the threads on the tile's edge also the halo cell beyond
-// them (corners are never read).  The next plane's values are fetched into
-// registers before a plane is computed, so their loads overlap it; one
-// barrier per plane.  Threads past the grid's edge hold the wrapped (periodic)
-// or clamped (wall) column, which only serves as a neighbour.
-// A tile row is one 64-lane wave, so a wave's row y and plane z are uniform:
-// every address is a scalar row offset plus the lane's column.
+// Chemical potential + LBM over TX x TY x TZ tiles, one cell per thread.
+// Each thread loads phi^{n+1}, mu^n and U of its own cell and of about one
+// cell of the tile's face halo, forms from them what the faces of the mu
+// update need (face_quant) once per cell, and shares it through LDS; the
+// populations are pulled meanwhile.  One barrier per block, no loop: a wave
+// has all of its loads in flight at once and many blocks per CU overlap
+// their loads with each other's arithmetic and stores.
+// Order of the tiles: strips of `strip` tile rows, walked layer by layer along
+// z, so that a layer's halo planes are read again while the strip's own are
+// still in L2; each XCD takes a contiguous part of that order.
+// Threads past the grid's edge hold the wrapped (periodic) or clamped (wall)
+// cell, which only serves as a neighbour.
 // ---------------------------------------------------------------------------
-template <int D, int Q, int N, int NC, class R, int TX, int TY, bool SH, bool MT>
-__global__ void __launch_bounds__(TX * TY)
-k_mulbm_z(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1,
-          const R* __restrict__ mu, const R* __restrict__ uold, const R* __restrict__ fin,
-          R* __restrict__ mu_out, R* __restrict__ u_out, R* __restrict__ fout, R* __restrict__ dr_out,
-          const uint8_t* __restrict__ phi_bulk, int zc_phi, R tshift, int tiles_x, int tiles_y, int zc,
-          unsigned* __restrict__ todo_count) {
-  static_assert(TX == 64, "one tile row per 64-lane wave");
-  static_assert(TY >= 2, "edge threads own one row and one column halo cell at most");
-  constexpr int HX = TX + 2, HY = TY + 2, HC = HX * HY;
-  constexpr int NV = N + NC + 2;  // phi^{n+1}, mu^n, U_x, U_y per tile cell
-  constexpr int NB = (D == 3) ? 2 : 1;
-  __shared__ R sh[NB][NV][HC];
-  const Tile T = tile_of(tiles_x, tiles_y, TX, TY, zc, p.n[2], D);
+// HBM bound in 3D (FP32, 256^3: 195 B/cell moved of the 168 that the state
+// needs), VALU issue beside it for three and four phases.  The form before
+// this one walked 64 x 4 columns plane by plane, held the next plane's values
+// in registers (127 to 186 of them, 2 to 4 waves per SIMD) and formed
+// face_quant at all seven cells: 50 to 81 registers now.  us per launch, then
+// and now: 675 -> 631 (256^3, two phases, FP32), 1407 -> 1236 (FP64), 357 ->
+// 293 (192^3, three phases, two solutes), 117 -> 67 (96 x 96 x 128, four
+// phases), 35 -> 19 (64^3); tiles of 32 x 4 x 2 and 32 x 4 x 4 cells took 646
+// and 673 on 256^3, 64 x 2 x 2 took 664 and 64 x 4 x 1 632.
+// LDS-shared slots of a tile: its T cells (slot = thread), then the halo of
+// each face: z-, z+ (TX x TY cells each), y-, y+ (TX x TZ), x-, x+ (TY x TZ).
+template <int D, int TX, int TY, int TZ> struct MuTile {
+  static constexpr int T = TX * TY * TZ;
+  static constexpr int HZ = (D == 3) ? TX * TY : 0, HY = TX * TZ, HX = TY * TZ;
+  static constexpr int H = 2 * (HZ + HY + HX);
+  // first halo slot of axis a, relative to T
+  static constexpr int base(int a) { return a == 2 ? 0 : (a == 1 ? 2 * HZ : 2 * (HZ + HY)); }
+  static constexpr int face(int a) { return a == 2 ? HZ : (a == 1 ? HY : HX); }
+};
+
+template <int D, int Q, int N, int NC, class R, int TX, int TY, int TZ, bool SH, bool MT>
+__global__ void __launch_bounds__(TX * TY * TZ)
+k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R* __restrict__ mu,
+        const R* __restrict__ uold, const R* __restrict__ fin, R* __restrict__ mu_out, R* __restrict__ u_out,
+        R* __restrict__ fout, R* __restrict__ dr_out, const uint8_t* __restrict__ phi_bulk, int phi_lx, int phi_ly,
+        int phi_lz, R tshift, int tiles_x, int tiles_y, int strip, unsigned* __restrict__ todo_count) {
+  using M = MuTile<D, TX, TY, TZ>;
+  constexpr bool ROW = TX == 64;
+  static_assert(TX * TY >= 64 && 64 % TX == 0, "a wave's lanes share a plane, and a row when TX is 64");
+  static_assert(D == 3 || TZ == 1, "one plane in 2D");
+  constexpr int T = M::T, H = M::H, HI = (H + T - 1) / T;
+  constexpr int NV = 3 * NC + (SH ? N : 0);  // mu, c*, d (and phi^{n+1}) per slot
+  __shared__ R sv[NV][T + H];
+  __shared__ R su[D * T + H];  // U_a of the cells, axis after axis, then of the halo of the faces along a
+  int x0, y0, z0;
+  {
+    // contiguous part of the tile order per XCD, then strips
+    const unsigned nb = gridDim.x, b = blockIdx.x, per8 = nb / 8u;
+    const unsigned lb = (b < per8 * 8u) ? (b % 8u) * per8 + b / 8u : b;
+    const unsigned tx = (unsigned)tiles_x, ty = (unsigned)tiles_y, layers = nb / (tx * ty);
+    const unsigned sfull = (unsigned)strip * tx * layers;  // tiles of a full strip
+    const unsigned s = lb / sfull, r = lb % sfull;
+    const unsigned hs = min((unsigned)strip, ty - s * (unsigned)strip);
+    const unsigned z = r / (hs * tx), q = r % (hs * tx);
+    x0 = (int)(q % tx) * TX;
+    y0 = (int)(s * (unsigned)strip + q / tx) * TY;
+    z0 = (int)z * TZ;
+  }
   const int tid = threadIdx.x;
   // the step's k_phi_zl, which read the list length, has finished: clear it
   // for the next step's k_phi_todo
   if (todo_count && blockIdx.x == 0 && tid == 0) atomicExch(todo_count, 0u);
-  const int lx = tid % TX, ly = __builtin_amdgcn_readfirstlane(tid / TX);
-  const int x = T.x0 + lx, y = T.y0 + ly;
-  const bool own = x < p.n[0] && y < p.n[1];
-  const int c0 = (ly + 1) * HX + (lx + 1);
+  const int lx = tid % TX;
+  const int ly = ROW ? __builtin_amdgcn_readfirstlane((tid / TX) % TY) : (tid / TX) % TY;
+  const int lz = (D == 3) ? __builtin_amdgcn_readfirstlane(tid / (TX * TY)) : 0;
+  const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
+  const bool own = x < p.n[0] && y < p.n[1] && (D == 2 || z < p.n[2]);
   const int xw = wrap_or_clamp(x, p.n[0], p.per[0]), yw = wrap_or_clamp(y, p.n[1], p.per[1]);
-  const int64_t rowc = (int64_t)yw * p.sy;  // + xw: the thread's column
-  // halo cells: 0 the row halo (y0 - 1 or y0 + TY), 1 the column halo (x0 - 1 or x0 + TX)
-  const bool hrow = ly == 0 || ly == TY - 1, hcol = lx == 0 || lx == TX - 1;
-  const int hy = (ly == 0) ? -1 : TY, hx = (lx == 0) ? -1 : TX;
-  const int hi0 = (hy + 1) * HX + (lx + 1), hi1 = (ly + 1) * HX + (hx + 1);
-  const int64_t hrow0 = (int64_t)wrap_or_clamp(T.y0 + hy, p.n[1], p.per[1]) * p.sy;  // + xw
-  const int hx1 = wrap_or_clamp(T.x0 + hx, p.n[0], p.per[0]);                        // + rowc
-  const PullX px = pull_x(x, p.n[0], p.per[0]);
-  // phi_bulk (k_phi_z's flags of this step, null when there are none): where
-  // the k_phi_z block holding this tile and these planes left every cell bulk,
-  // phi^n = phi^{n+1} there, so phi^n is not read (the two-phase, one-solute
-  // instances, where that saves a phase field per cell at no register cost)
-  constexpr bool SKIP0 = !SH && !MT && N == 2 && NC == 1;
+  const int zw = (D == 3) ? wrap_or_clamp(z, p.n[2], p.per[2]) : 0;
+  // the thread's cell: scalar part and lane part of its element offset
+  const int64_t cu = (int64_t)zw * p.sz + (ROW ? (int64_t)yw * p.sy : 0);
+  const int cl = xw + (ROW ? 0 : (int)((uint32_t)yw * (uint32_t)p.sy));
+  // phi_bulk (the phase field's flags of this step, null when there are none):
+  // where the phase-field tile (2^phi_lx x 2^phi_ly x 2^phi_lz cells) that
+  // holds this cell was left bulk, phi^n =
+  // phi^{n+1}, so phi^n is not read
   bool same0 = false;
-  if constexpr (SKIP0) {
-    if (phi_bulk) {
-      const unsigned tz = (D == 3) ? (unsigned)(T.z0 / zc_phi) : 0u;
-      const unsigned t0 = T.lb % (unsigned)(tiles_x * tiles_y);
-      same0 = phi_bulk[t0 + (unsigned)(tiles_x * tiles_y) * tz] != 0;
-    }
+  if (phi_bulk) {
+    const int ptx = ((p.n[0] - 1) >> phi_lx) + 1, pty = ((p.n[1] - 1) >> phi_ly) + 1;
+    same0 = phi_bulk[(xw >> phi_lx) + ptx * ((yw >> phi_ly) + pty * (D == 3 ? zw >> phi_lz : 0))] != 0;
   }
-  auto zoff = [&](int zz) -> int64_t {
-    return (D == 3) ? (int64_t)wrap_or_clamp(zz, p.n[2], p.per[2]) * p.sz : 0;
-  };
-
-  // own column, planes z-1 (index 0), z (1), z+1 (2)
-  R cph[3][N], cmu[3][NC], cuz[3];
-  auto fetch_col = [&](int zz, R (&ph)[N], R (&m)[NC], R& uz) {
-    const int64_t j = zoff(zz) + rowc;
+  R ph1[N], m0[NC], uc[D], ph0[N];
 #pragma unroll
-    for (int q = 0; q < N; ++q) ph[q] = *lane_at(phi1, q * p.cells + j, xw);
+  for (int q = 0; q < N; ++q) ph1[q] = *lane_at(phi1, q * p.cells + cu, cl);
 #pragma unroll
-    for (int q = 0; q < NC; ++q) m[q] = *lane_at(mu, q * p.cells + j, xw);
-    uz = (D == 3) ? *lane_at(uold, (D - 1) * p.cells + j, xw) : R(0);
-  };
-  // values of one plane that go to LDS besides the column's phi and mu: own
-  // U_x, U_y and the halo cells
-  R cuxy[2], hv[2][NV], ph0[N];
-  auto fetch_plane = [&](int zz) {
-    const int64_t zo = zoff(zz);
-    cuxy[0] = *lane_at(uold, zo + rowc, xw);
-    cuxy[1] = *lane_at(uold, p.cells + zo + rowc, xw);
+  for (int q = 0; q < NC; ++q) m0[q] = *lane_at(mu, q * p.cells + cu, cl);
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      if (h == 0 ? hrow : hcol) {
-        const int64_t j = zo + (h == 0 ? hrow0 : rowc);
-        const int l = (h == 0) ? xw : hx1;
+  for (int a = 0; a < D; ++a) uc[a] = *lane_at(uold, a * p.cells + cu, cl);
+  // halo cells of this thread: slots T + tid, T + tid + T, ...
+  R hph[HI][N], hm[HI][NC], hu[HI];
+  int hpa[HI];  // their pull-axis coordinate
 #pragma unroll
-        for (int q = 0; q < N; ++q) hv[h][q] = *lane_at(phi1, q * p.cells + j, l);
-#pragma unroll
-        for (int q = 0; q < NC; ++q) hv[h][N + q] = *lane_at(mu, q * p.cells + j, l);
-        hv[h][N + NC] = *lane_at(uold, j, l);
-        hv[h][N + NC + 1] = *lane_at(uold, p.cells + j, l);
+  for (int i = 0; i < HI; ++i) {
+    const int j = tid + i * T;
+    if (j < H) {
+      int hx, hy, hz, a;
+      if (j < 2 * M::HZ) {
+        const int r = j % (TX * TY);
+        a = 2;
+        hx = x0 + r % TX;
+        hy = y0 + r / TX;
+        hz = (j >= M::HZ) ? z0 + TZ : z0 - 1;
+      } else if (j < 2 * (M::HZ + M::HY)) {
+        const int q = j - 2 * M::HZ, r = q % M::HY;
+        a = 1;
+        hx = x0 + r % TX;
+        hz = z0 + r / TX;
+        hy = (q >= M::HY) ? y0 + TY : y0 - 1;
+      } else {
+        const int q = j - 2 * (M::HZ + M::HY), r = q % M::HX;
+        a = 0;
+        hy = y0 + r % TY;
+        hz = z0 + r / TY;
+        hx = (q >= M::HX) ? x0 + TX : x0 - 1;
       }
+      hx = wrap_or_clamp(hx, p.n[0], p.per[0]);
+      hy = wrap_or_clamp(hy, p.n[1], p.per[1]);
+      hz = (D == 3) ? wrap_or_clamp(hz, p.n[2], p.per[2]) : 0;
+      const int64_t o = (int64_t)hz * p.sz + (int64_t)hy * p.sy + hx;
+#pragma unroll
+      for (int q = 0; q < N; ++q) hph[i][q] = phi1[q * p.cells + o];
+#pragma unroll
+      for (int q = 0; q < NC; ++q) hm[i][q] = mu[q * p.cells + o];
+      hu[i] = uold[a * p.cells + o];
+      hpa[i] = (p.pull_axis == 0) ? hx : (p.pull_axis == 1 ? hy : hz);
     }
-  };
-  auto write_plane = [&](int bf) {
-#pragma unroll
-    for (int q = 0; q < N; ++q) sh[bf][q][c0] = cph[1][q];
-#pragma unroll
-    for (int q = 0; q < NC; ++q) sh[bf][N + q][c0] = cmu[1][q];
-    sh[bf][N + NC][c0] = cuxy[0];
-    sh[bf][N + NC + 1][c0] = cuxy[1];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      if (hrow) sh[bf][v][hi0] = hv[0][v];
-      if (hcol) sh[bf][v][hi1] = hv[1][v];
-    }
-  };
-  auto fetch_ph0 = [&](int zz, R (&o)[N]) {
-    if (same0) return;
-    const int64_t j = zoff(zz) + rowc;
-#pragma unroll
-    for (int q = 0; q < N; ++q) o[q] = *lane_at(phi0, q * p.cells + j, xw);
-  };
-
-  if (D == 3) {
-    fetch_col(T.z0 - 1, cph[0], cmu[0], cuz[0]);
-    fetch_col(T.z0 + 1, cph[2], cmu[2], cuz[2]);
   }
-  fetch_col(T.z0, cph[1], cmu[1], cuz[1]);
-  fetch_plane(T.z0);
-  fetch_ph0(T.z0, ph0);
-  {
-    // every value loaded before the loop is consumed here, so none is still
-    // in flight when the loop starts: the loop's own prefetch is then waited
-    // for where the next plane uses it, not (as the compiler's wait counting
-    // would otherwise place it, merging the loop's entry with its back edge)
-    // at the first use of a value carried into the loop, in mid-plane
-    auto settle = [](R& v) { asm volatile("" : "+v"(v)); };
+  R f[Q];
+  const PullAt<ROW> px = pull_at<D, ROW, R>(p, xw, yw, zw);
+  if (own) pull_cell<D, Q, ROW, R>(p, fin, px, f);
+  if (!same0) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-#pragma unroll
-      for (int q = 0; q < N; ++q) settle(cph[k][q]);
-#pragma unroll
-      for (int q = 0; q < NC; ++q) settle(cmu[k][q]);
-      settle(cuz[k]);
-    }
-#pragma unroll
-    for (int q = 0; q < N; ++q) settle(ph0[q]);
-    settle(cuxy[0]);
-    settle(cuxy[1]);
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int v = 0; v < NV; ++v) settle(hv[h][v]);
+    for (int q = 0; q < N; ++q) ph0[q] = *lane_at(phi0, q * p.cells + cu, cl);
   }
-  for (int z = T.z0; z < T.z1; ++z) {
-    const int bf = (z - T.z0) & (NB - 1);
-    write_plane(bf);
-    __syncthreads();
-    // next plane's loads, in flight while this plane is computed
-    R nph[N] = {}, nmu[NC] = {}, nuz = R(0), np0[N] = {};
-    if (z + 1 < T.z1) {
-      fetch_plane(z + 1);
-      fetch_ph0(z + 1, np0);
-      if (D == 3) fetch_col(z + 2, nph, nmu, nuz);
-    }
-    if (own) {
-      // strides and coordinates opaque per plane: addresses and the other
-      // quantities of the cell are formed anew on every plane instead of being
-      // carried along z (as pointers, one scalar register pair per buffer and
-      // population, or as per-lane values held in vector registers)
-      KP<R> q = p;
-      int xq = x, yq = y;
-      asm volatile("" : "+s"(q.cells), "+s"(q.sy), "+s"(q.sz), "+v"(xq), "+s"(yq));
-      R ph1n[2 * D + 1][N], mun[2 * D + 1][NC], uc[D], un[D][2];
-      const int off[4] = {-1, 1, -HX, HX};
+  const int pos[3] = {x, y, z};
+  const int pa = p.pull_axis;
+  const R td0 = MT ? tdev_at(p, pa == 0 ? xw : (pa == 1 ? yw : zw), tshift) : R(0);
+  R cs0[NC], d0[NC];
+  face_quant<N, NC, R, MT>(p, ph1, m0, td0, cs0, d0);
 #pragma unroll
-      for (int q = 0; q < N; ++q) {
-        ph1n[0][q] = cph[1][q];
+  for (int q = 0; q < NC; ++q) {
+    sv[q][tid] = m0[q];
+    sv[NC + q][tid] = cs0[q];
+    sv[2 * NC + q][tid] = d0[q];
+  }
+  if constexpr (SH)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) ph1n[1 + j][q] = sh[bf][q][c0 + off[j]];
-        if (D == 3) {
-          ph1n[2 * D - 1][q] = cph[0][q];
-          ph1n[2 * D][q] = cph[2][q];
-        }
-      }
+    for (int q = 0; q < N; ++q) sv[3 * NC + q][tid] = ph1[q];
+#pragma unroll
+  for (int a = 0; a < D; ++a) su[a * T + tid] = uc[a];
+#pragma unroll
+  for (int i = 0; i < HI; ++i) {
+    const int j = tid + i * T;
+    if (j < H) {
+      R cs[NC], d[NC];
+      face_quant<N, NC, R, MT>(p, hph[i], hm[i], MT ? tdev_at(p, hpa[i], tshift) : R(0), cs, d);
 #pragma unroll
       for (int q = 0; q < NC; ++q) {
-        mun[0][q] = cmu[1][q];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) mun[1 + j][q] = sh[bf][N + q][c0 + off[j]];
-        if (D == 3) {
-          mun[2 * D - 1][q] = cmu[0][q];
-          mun[2 * D][q] = cmu[2][q];
-        }
+        sv[q][T + j] = hm[i][q];
+        sv[NC + q][T + j] = cs[q];
+        sv[2 * NC + q][T + j] = d[q];
       }
-      uc[0] = sh[bf][N + NC][c0];
-      uc[1] = sh[bf][N + NC + 1][c0];
-      un[0][0] = sh[bf][N + NC][c0 - 1];
-      un[0][1] = sh[bf][N + NC][c0 + 1];
-      un[1][0] = sh[bf][N + NC + 1][c0 - HX];
-      un[1][1] = sh[bf][N + NC + 1][c0 + HX];
-      if (D == 3) {
-        uc[D - 1] = cuz[1];
-        un[D - 1][0] = cuz[0];
-        un[D - 1][1] = cuz[2];
-      }
-      R p0[N];
+      if constexpr (SH)
 #pragma unroll
-      for (int k = 0; k < N; ++k) p0[k] = same0 ? cph[1][k] : ph0[k];
-      mulbm_core<D, Q, N, NC, R, SH, MT>(q, xq, yq, z, px, tshift, ph1n, mun, uc, un, p0, fin, mu_out, u_out,
-                                         fout, dr_out);
+        for (int q = 0; q < N; ++q) sv[3 * NC + q][T + j] = hph[i][q];
+      su[D * T + j] = hu[i];
     }
-#pragma unroll
-    for (int q = 0; q < N; ++q) {
-      cph[0][q] = cph[1][q];
-      cph[1][q] = cph[2][q];
-      cph[2][q] = nph[q];
-      ph0[q] = np0[q];
-    }
-#pragma unroll
-    for (int q = 0; q < NC; ++q) {
-      cmu[0][q] = cmu[1][q];
-      cmu[1][q] = cmu[2][q];
-      cmu[2][q] = nmu[q];
-    }
-    cuz[0] = cuz[1];
-    cuz[1] = cuz[2];
-    cuz[2] = nuz;
   }
+  block_sync_lds();
+  if (!own) return;
+
+  // divergence of the face fluxes (diffusion and advection)
+  R divJ[NC];
+#pragma unroll
+  for (int i = 0; i < NC; ++i) divJ[i] = R(0);
+  R g1[SH ? N : 1][D];
+  const int lpos[3] = {lx, ly, lz}, text[3] = {TX, TY, TZ}, tstr[3] = {1, TX, TX * TY};
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    // index of the cell's column within a face of the tile across axis a
+    const int fi = a == 0 ? lz * TY + ly : (a == 1 ? lz * TX + lx : ly * TX + lx);
+#pragma unroll
+    for (int si = 0; si < 2; ++si) {
+      const int s = si ? 1 : -1;
+      const bool inner = si ? lpos[a] + 1 < text[a] : lpos[a] > 0;
+      const int h = M::base(a) + si * M::face(a) + fi;
+      const int slot = inner ? tid + s * tstr[a] : T + h;
+      if constexpr (SH) {
+        // (the slot beyond a wall holds the cell at the wall itself)
+#pragma unroll
+        for (int b = 0; b < N; ++b) g1[b][a] = si ? sv[3 * NC + b][slot] - g1[b][a] : sv[3 * NC + b][slot];
+      }
+      const bool wall = !p.per[a] && ((s < 0 && pos[a] == 0) || (s > 0 && pos[a] == p.n[a] - 1));
+      if (wall) continue;
+      const R uf = R(0.5) * (uc[a] + su[inner ? a * T + slot : D * T + h]) * p.conv;
+      R dm[NC];
+#pragma unroll
+      for (int k = 0; k < NC; ++k) dm[k] = R(s) * (sv[k][slot] - m0[k]) * p.idx;
+#pragma unroll
+      for (int i = 0; i < NC; ++i) {
+        const R df = -R(0.5) * (d0[i] + sv[2 * NC + i][slot]);
+        R JD = R(0);
+#pragma unroll
+        for (int k = 0; k < NC; ++k) JD += df * p.chi[i][k] * dm[k];
+        const R JA = uf * R(0.5) * (cs0[i] + sv[NC + i][slot]);
+        divJ[i] += R(s) * (JD + JA) * p.idx;
+      }
+    }
+  }
+  if (same0) {
+#pragma unroll
+    for (int q = 0; q < N; ++q) ph0[q] = ph1[q];
+  }
+  R h0[N], h1[N];
+  interp_h<N, R>(ph0, h0);
+  interp_h<N, R>(ph1, h1);
+  R Dl[NC];
+#pragma unroll
+  for (int i = 0; i < NC; ++i) Dl[i] = -p.dt * divJ[i];
+  // dh/dt source with C at T^n, and the dT/dt term of Eq. (conc) over the
+  // step, -sum_b h_b^{n+1} (C^b(mu^n, T^{n+1}) - C^b(mu^n, T^n)) = -sum_b
+  // h_b^{n+1} mT[b] (T^{n+1} - T^n)
+  R sh = R(0);
+#pragma unroll
+  for (int b = 0; b < N; ++b) {
+    sh += h1[b];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      Dl[i] -= comp_of<N, NC, R, MT>(p, b, i, m0, td0) * (h1[b] - h0[b]);
+      if constexpr (MT) Dl[i] -= h1[b] * (p.mT[b][i] * p.dtdev);
+    }
+  }
+  R mn[NC];
+  if (NC == 1) {
+    mn[0] = m0[0] + Dl[0] / (sh * p.chi[0][0]);
+  } else {
+    const R a11 = sh * p.chi[0][0], a12 = sh * p.chi[0][1];
+    const R a21 = sh * p.chi[1][0], a22 = sh * p.chi[1][NC - 1];
+    const R det = a11 * a22 - a12 * a21;
+    mn[0] = m0[0] + (a22 * Dl[0] - a12 * Dl[NC - 1]) / det;
+    mn[NC - 1] = m0[NC - 1] + (-a21 * Dl[0] + a11 * Dl[NC - 1]) / det;
+  }
+#pragma unroll
+  for (int i = 0; i < NC; ++i) __builtin_nontemporal_store(mn[i], lane_at(mu_out, i * p.cells + cu, cl));
+  collide_cell<D, Q, N, NC, R, SH, MT>(p, cu, cl, f, ph0, ph1, mn, g1, td0, u_out, fout, dr_out);
 }
 
 // ---------------------------------------------------------------------------
@@ -1300,9 +1271,8 @@ __global__ void k_loss_seed(const R* __restrict__ phi, const double* __restrict_
 // population update without its arithmetic, on 19 FP32 arrays of an
 // n0 x n1 x n2 grid (all axes periodic).  k_probe_copy19: out_k(P) = in_k(P);
 // k_probe_pull19: out_k(P) = in_k(P - c_k) with the D3Q19 velocities, one
-// thread per cell in 256-cell blocks; k_probe_pull19_z: the same pull in the
-// launch shape of k_mulbm_z (64 x TY tiles walking ZC planes, XCD-aware tile
-// order).  Streaming (nontemporal) loads and stores as in the step kernels.
+// thread per cell in 256-cell blocks; k_probe_pull19_z: the same pull by
+// 64 x TY tiles that walk ZC planes (XCD-aware tile order).  Streaming (nontemporal) loads and stores as in the step kernels.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_probe_copy19(const float* __restrict__ in, float* __restrict__ out,
                                                       int64_t cells) {

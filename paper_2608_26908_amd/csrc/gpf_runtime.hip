@@ -299,30 +299,28 @@ inline unsigned adj_blocks(const int64_t (&n)[3]) {
   return 8u * lin_blocks(n[0] * ((n[1] + 7) / 8) * n[2], gpf::ADJ_BLOCK);
 }
 
-// z-marching launch shape: 64 x GPF_TILE_Y tiles; each block of k_phi_z walks
-// GPF_ZCHUNK_PHI planes, each of k_mulbm_z GPF_ZCHUNK_MU (best measured of
-// 64 x {2, 4, 8} x {4, 8, 16, 32} on the 256^3 dendrite)
-#ifndef GPF_TILE_Y
+// launch shape of the phase field: 64 x GPF_TILE_Y tiles, each block walks
+// GPF_ZCHUNK_PHI planes (best measured of 64 x {2, 4, 8} x {4, 8, 16, 32})
 #define GPF_TILE_Y 4
-#endif
-#ifndef GPF_ZCHUNK_PHI2
 #define GPF_ZCHUNK_PHI2 4
-#endif
-#ifndef GPF_ZCHUNK_PHI
 #define GPF_ZCHUNK_PHI 16
+constexpr int kTileY = GPF_TILE_Y;
+constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
+// tiles of k_mulbm in 3D (64 x 4 cells in 2D), one cell per thread, and the
+// tile rows of a strip of its tile order (both measured, see the kernel)
+#ifndef GPF_MU_TX
+#define GPF_MU_TX 64
+#define GPF_MU_TY 4
+#define GPF_MU_TZ 2
 #endif
-#ifndef GPF_ZCHUNK_MU
-#define GPF_ZCHUNK_MU 4
-#endif
-constexpr int kTileY = GPF_TILE_Y, kZChunkMu = GPF_ZCHUNK_MU;
+#define GPF_MU_STRIP 8
+// planes that a block of the bandwidth probe's z-marched pull walks
+constexpr int kProbeZ = 4;
 // planes per phase-field block: a two-phase step spends its phase-field time
 // in the few tiles near the interface (3D: the tiles k_phi_zl walks), whose
 // plane walk a shorter chunk shortens; three and four phases have interface
 // throughout the solid, where a longer chunk re-reads fewer halo planes
 constexpr int zchunk_phi(int N) { return N == 2 ? GPF_ZCHUNK_PHI2 : GPF_ZCHUNK_PHI; }
-// a k_mulbm_z block's planes lie within one k_phi_z block's (its bulk flag applies)
-static_assert(zchunk_phi(2) % kZChunkMu == 0 && zchunk_phi(3) % kZChunkMu == 0,
-              "the phase-field plane chunk must be a multiple of the LBM's");
 // blocks of one k_phi_z launch (64 x kTileY tiles, zchunk_phi(N) planes each in 3D)
 inline int64_t phi_blocks(const gpf_ctx* c) {
   const int64_t tx = (c->n[0] + 63) / 64, ty = (c->n[1] + kTileY - 1) / kTileY;
@@ -391,10 +389,14 @@ struct Impl {
                            out.phi, bulk_in, bulk_out, act_out, ts, tiles_x, tiles_y, ZP);
     }
     if (ev) (void)hipEventRecord(ev[1], st);
-#define GPF_MULBM(SH, MT)                                                                                     \
-  hipLaunchKernelGGL((gpf::k_mulbm_z<D, Q, N, NC, R, TX, TY, SH, MT>), grid(kZChunkMu), block, 0, st, k, in.phi, \
-                     out.phi, in.mu, in.u, in.f, out.mu, out.u, out.f, out.dr, bulk_out, ZP, ts, tiles_x,            \
-                     tiles_y, kZChunkMu, counts)
+    constexpr int MX = D == 3 ? GPF_MU_TX : 64, MY = D == 3 ? GPF_MU_TY : 4, MZ = D == 3 ? GPF_MU_TZ : 1;
+    const int mtx = (int)((c->n[0] + MX - 1) / MX), mty = (int)((c->n[1] + MY - 1) / MY);
+    const int mtz = (int)((c->n[2] + MZ - 1) / MZ);
+    const dim3 mgrid((unsigned)mtx * (unsigned)mty * (unsigned)mtz);
+#define GPF_MULBM(SH, MT)                                                                                        \
+  hipLaunchKernelGGL((gpf::k_mulbm<D, Q, N, NC, R, MX, MY, MZ, SH, MT>), mgrid, dim3(MX * MY * MZ), 0, st, k, in.phi, \
+                     out.phi, in.mu, in.u, in.f, out.mu, out.u, out.f, out.dr, bulk_out, ilog2(TX), ilog2(TY), ilog2(ZP), ts, mtx, mty,    \
+                     GPF_MU_STRIP, counts)
     if (k.shrink) {
       if (k.tdep)
         GPF_MULBM(true, true);
@@ -1485,7 +1487,7 @@ int gpf_reduce_noalloc(gpf_ctx* c, int32_t which, double* dev_out) {
 int gpf_bandwidth_probe(int32_t pattern, const void* dev_in, void* dev_out, const int64_t* n, int32_t reps,
                         void* stream, double* gbps) {
   if (!dev_in || !dev_out || !n || !gbps || reps < 1 || pattern < 0 || pattern > 2) return GPF_ERR_ARG;
-  if (n[0] < 64 || n[0] % 64 || n[1] < kTileY || n[1] % kTileY || n[2] < kZChunkMu || n[2] % kZChunkMu ||
+  if (n[0] < 64 || n[0] % 64 || n[1] < kTileY || n[1] % kTileY || n[2] < kProbeZ || n[2] % kProbeZ ||
       n[0] > (1 << 20) || n[1] > (1 << 20) || n[2] > 65535)
     return GPF_ERR_ARG;
   const int64_t cells = n[0] * n[1] * n[2];
@@ -1494,7 +1496,7 @@ int gpf_bandwidth_probe(int32_t pattern, const void* dev_in, void* dev_out, cons
   float* out = static_cast<float*>(dev_out);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int n0 = (int)n[0], n1 = (int)n[1], n2 = (int)n[2];
-  const unsigned zblocks = (unsigned)((n0 / 64) * (n1 / kTileY) * (n2 / kZChunkMu));
+  const unsigned zblocks = (unsigned)((n0 / 64) * (n1 / kTileY) * (n2 / kProbeZ));
   auto launch = [&]() {
     if (pattern == 0)
       hipLaunchKernelGGL(gpf::k_probe_copy19, dim3(lin_blocks(cells, 256)), dim3(256), 0, st, in, out, cells);
@@ -1502,7 +1504,7 @@ int gpf_bandwidth_probe(int32_t pattern, const void* dev_in, void* dev_out, cons
       hipLaunchKernelGGL(gpf::k_probe_pull19, dim3(lin_blocks(cells, 256)), dim3(256), 0, st, in, out, n0, n1, n2);
     else
       hipLaunchKernelGGL((gpf::k_probe_pull19_z<kTileY>), dim3(zblocks), dim3(64 * kTileY), 0, st, in, out, n0, n1,
-                         n2, kZChunkMu);
+                         n2, kProbeZ);
   };
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return GPF_ERR_DEVICE;

@@ -1,0 +1,39 @@
+"""The step kernels at the edges of their tiles: grids one cell short of,
+equal to and one past a tile along each axis, past a strip of tile rows, and
+the smallest ones, from random states in which every cell is an interface or
+borders one, against the FP64 oracle (1e-12 of each field's largest value, the
+bar of every FP64 parity test)."""
+import numpy as np
+import pytest
+
+from gpu_helpers import STATE, field_floor, gpu_from, oracle_from, rel_err
+from inputs import busy_config, random_state
+
+pytestmark = pytest.mark.gpu
+
+GRIDS = [("binary3d", [63, 5, 3]), ("binary3d", [64, 4, 2]), ("binary3d", [65, 3, 1]), ("binary3d", [130, 33, 5]),
+         ("ternary3d_nc2", [66, 31, 4]), ("ternary3d_nc2", [1, 2, 9]), ("quaternary3d", [32, 65, 3]),
+         ("quaternary3d", [33, 4, 17]), ("binary2d", [63, 3]), ("binary2d", [65, 33]), ("ternary2d", [191, 5]),
+         ("ternary2d_nc2", [2, 67]), ("quaternary2d", [129, 34])]
+
+
+def _check(cfg, steps):
+    st = random_state(cfg, 11)
+    g, o = gpu_from(cfg, st, "fp64"), oracle_from(cfg, st)
+    g.step(steps)
+    o.step(steps)
+    ref = {k: o.get(k) for k in STATE}
+    for k in STATE:
+        assert rel_err(g.read(k), ref[k], field_floor(k, ref)) <= 1e-12, k
+
+
+@pytest.mark.parametrize("kind,n", GRIDS)
+def test_tile_edges(oracle, kind, n):
+    _check(busy_config(kind, n), 2)
+
+
+@pytest.mark.parametrize("n", [[65, 5, 3], [31, 34, 2]])
+def test_tile_edges_q27_shrinkage(oracle, n):
+    """the 27-velocity lattice with walls on every axis, and the shrinkage
+    force (its normals are read through the tile's halo)"""
+    _check(busy_config("binary3d", n, lattice="D3Q27", eta=[0.2, 0.0, 0.0], periodic=[0, 0, 0]), 2)
