@@ -82,7 +82,11 @@ template <> struct Lat<27> {
 template <class R> struct KP {
   int n[3];
   int per[3];
-  int64_t sy, sz, cells;  // strides of y and z, number of cells
+  // strides of y and z, stored elements per component: rows are padded to
+  // whole 128-byte lines (sy >= n[0]), so that a wave's accesses to its row
+  // start on a line
+  int64_t sy, sz, cells;
+  int64_t live;           // cells of the grid, n[0] n[1] n[2]
   int potential;          // 0 obstacle, 1 well
   int pull_axis, grav_axis;
   R dx, dt, eps, rate;    // rate = dt / (tau_pf eps)
@@ -301,6 +305,26 @@ __device__ __forceinline__ void project_masked(unsigned mask, const R (&v)[N], R
 #pragma unroll
   for (int i = 0; i < N; ++i)
     out[i] = (((mask >> i) & 1u) && v[i] - theta > R(0)) ? v[i] - theta : R(0);
+}
+
+// Cell i of the grid in dense order (x fastest, no padding): its coordinates
+// and its element P in a stored component; false past the last cell.
+template <class R>
+__device__ __forceinline__ bool dense_cell(const KP<R>& p, int64_t i, int& x, int& y, int& z, int64_t& P) {
+  if (i >= p.live) return false;
+  if (p.live <= (int64_t)0xffffffff) {  // 32-bit divisions are a quarter of the 64-bit ones
+    const unsigned r = (unsigned)i / (unsigned)p.n[0];
+    x = (int)((unsigned)i - r * (unsigned)p.n[0]);
+    z = (int)(r / (unsigned)p.n[1]);
+    y = (int)(r - (unsigned)z * (unsigned)p.n[1]);
+  } else {
+    const int64_t r = i / p.n[0];
+    x = (int)(i - r * p.n[0]);
+    z = (int)(r / p.n[1]);
+    y = (int)(r - (int64_t)z * p.n[1]);
+  }
+  P = (int64_t)z * p.sz + (int64_t)y * p.sy + x;
+  return true;
 }
 
 // Barrier of a block whose threads exchange data through LDS only: unlike

@@ -673,7 +673,7 @@ k_phi_z(KP<R> p, const R* __restrict__ phi, const R* __restrict__ mu, R* __restr
   // ACT (recomputation for the adjoint): act_out receives each cell's active
   // set of phases, which the reverse of the step reads instead of phi^n's
   // stencil (an instance of its own keeps the registers of the common case)
-  if (bulk_in && (D == 3 || p.cells > ((int64_t)1 << 18))) {
+  if (bulk_in && (D == 3 || p.live > ((int64_t)1 << 18))) {
     // If this block and every block its stencils reach (the 26 around it, none
     // beyond a wall) were bulk in that step, phi^n = phi^{n-1} on every stencil
     // the block evaluates, so each cell has its previous active set and is
@@ -767,7 +767,10 @@ k_phi_zl(KP<R> p, const R* __restrict__ phi, const R* __restrict__ mu, R* __rest
 // their loads with each other's arithmetic and stores.
 // Order of the tiles: strips of `strip` tile rows, walked layer by layer along
 // z, so that a layer's halo planes are read again while the strip's own are
-// still in L2; each XCD takes a contiguous part of that order.
+// still in L2; each XCD takes a contiguous part of that order.  With an eighth
+// of the rows per strip every XCD owns one strip and all eight walk the same
+// planes together (192^3 FP32: 259 us, strips of 8 tile rows 280; three phases
+// 273 and 294; 256^3: 630, and 640 to 708 with strips of a quarter or half).
 // Threads past the grid's edge hold the wrapped (periodic) or clamped (wall)
 // cell, which only serves as a neighbour.
 // ---------------------------------------------------------------------------
@@ -827,12 +830,15 @@ k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R
   const int ly = ROW ? __builtin_amdgcn_readfirstlane((tid / TX) % TY) : (tid / TX) % TY;
   const int lz = (D == 3) ? __builtin_amdgcn_readfirstlane(tid / (TX * TY)) : 0;
   const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
-  const bool own = x < p.n[0] && y < p.n[1] && (D == 2 || z < p.n[2]);
+  // the padding of a row is computed and stored too (from the wrapped or
+  // clamped cell): its last line leaves the chip whole
+  const bool own = x < (int)p.sy && y < p.n[1] && (D == 2 || z < p.n[2]);
   const int xw = wrap_or_clamp(x, p.n[0], p.per[0]), yw = wrap_or_clamp(y, p.n[1], p.per[1]);
   const int zw = (D == 3) ? wrap_or_clamp(z, p.n[2], p.per[2]) : 0;
   // the thread's cell: scalar part and lane part of its element offset
   const int64_t cu = (int64_t)zw * p.sz + (ROW ? (int64_t)yw * p.sy : 0);
   const int cl = xw + (ROW ? 0 : (int)((uint32_t)yw * (uint32_t)p.sy));
+  const int cs = cl + (x - xw);  // where the cell is stored
   // phi_bulk (the phase field's flags of this step, null when there are none):
   // where the phase-field tile (2^phi_lx x 2^phi_ly x 2^phi_lz cells) that
   // holds this cell was left bulk, phi^n =
@@ -915,12 +921,12 @@ k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R
   for (int i = 0; i < HI; ++i) {
     const int j = tid + i * T;
     if (j < H) {
-      R cs[NC], d[NC];
-      face_quant<N, NC, R, MT>(p, hph[i], hm[i], MT ? tdev_at(p, hpa[i], tshift) : R(0), cs, d);
+      R cq[NC], d[NC];
+      face_quant<N, NC, R, MT>(p, hph[i], hm[i], MT ? tdev_at(p, hpa[i], tshift) : R(0), cq, d);
 #pragma unroll
       for (int q = 0; q < NC; ++q) {
         sv[q][T + j] = hm[i][q];
-        sv[NC + q][T + j] = cs[q];
+        sv[NC + q][T + j] = cq[q];
         sv[2 * NC + q][T + j] = d[q];
       }
       if constexpr (SH)
@@ -1004,8 +1010,8 @@ k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R
     mn[NC - 1] = m0[NC - 1] + (-a21 * Dl[0] + a11 * Dl[NC - 1]) / det;
   }
 #pragma unroll
-  for (int i = 0; i < NC; ++i) __builtin_nontemporal_store(mn[i], lane_at(mu_out, i * p.cells + cu, cl));
-  collide_cell<D, Q, N, NC, R, SH, MT>(p, cu, cl, f, ph0, ph1, mn, g1, td0, u_out, fout, dr_out);
+  for (int i = 0; i < NC; ++i) __builtin_nontemporal_store(mn[i], lane_at(mu_out, i * p.cells + cu, cs));
+  collide_cell<D, Q, N, NC, R, SH, MT>(p, cu, cs, f, ph0, ph1, mn, g1, td0, u_out, fout, dr_out);
 }
 
 // ---------------------------------------------------------------------------
@@ -1019,42 +1025,39 @@ k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R
 // most 1/2 (-1 if none), max-reduced over each wave, then one atomic per wave.
 template <int N, class R>
 __global__ void __launch_bounds__(256) k_front(KP<R> p, const R* __restrict__ phi, int* __restrict__ front) {
-  const int64_t P = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int v = -1;
-  if (P < p.cells && phi[(N - 1) * p.cells + P] <= R(0.5)) {
-    const int64_t c = (p.pull_axis == 0) ? P % p.n[0]
-                      : (p.pull_axis == 1) ? (P / p.sy) % p.n[1] : P / p.sz;
-    v = (int)c;
-  }
+  int v = -1, x, y, z;
+  int64_t P;
+  if (dense_cell(p, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, x, y, z, P) &&
+      phi[(N - 1) * p.cells + P] <= R(0.5))
+    v = (p.pull_axis == 0) ? x : (p.pull_axis == 1) ? y : z;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
   if ((threadIdx.x & 63) == 0 && v >= 0) atomicMax(front, v);
 }
 
-// k_shift: out = in moved down an axis by d cells (index stride `stride`,
-// extent n_ax); the last d planes repeat the last plane of `in`.
+// k_shift: out = in moved down axis ax by d cells (all components); the last
+// d planes repeat the last plane of `in`.
 template <class R>
-__global__ void k_shift(const R* __restrict__ in, R* __restrict__ out, int64_t count, int64_t cells,
-                        int64_t stride, int64_t n_ax, int64_t d) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  const int64_t P = i % cells;
-  const int64_t c = (P / stride) % n_ax;
-  const int64_t src = min(c + d, n_ax - 1);
-  out[i] = in[i + (src - c) * stride];
+__global__ void k_shift(KP<R> p, const R* __restrict__ in, R* __restrict__ out, int ncomp, int ax, int64_t d) {
+  int x, y, z;
+  int64_t P;
+  if (!dense_cell(p, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, x, y, z, P)) return;
+  const int64_t c = ax == 0 ? x : (ax == 1 ? y : z), stride = ax == 0 ? 1 : (ax == 1 ? p.sy : p.sz);
+  const int64_t o = (min(c + d, (int64_t)p.n[ax] - 1) - c) * stride;
+  for (int k = 0; k < ncomp; ++k) out[k * p.cells + P] = in[k * p.cells + P + o];
 }
 
-// f^n_k(P) = stored f*_k(P - c_k) (+ bounce-back), plus w_k rho0: the full f.
+// f^n_k(P) = stored f*_k(P - c_k) (+ bounce-back), plus w_k rho0: the full f,
+// in dense order.
 template <int D, int Q, class R>
 __global__ void k_gather_f(KP<R> p, const R* __restrict__ fin, double* __restrict__ out) {
   using L = Lat<Q>;
-  const int64_t P = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (P >= p.cells) return;
-  const int x = (int)(P % p.n[0]);
-  const int y = (int)((P / p.sy) % p.n[1]);
-  const int z = (int)(P / p.sz);
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int64_t P;
+  int x, y, z;
+  if (!dense_cell(p, i, x, y, z, P)) return;
   for (int k = 0; k < L::Q; ++k)
-    out[k * p.cells + P] = (double)pull_f<D, Q, R>(p, fin, x, y, z, P, k) + L::w(k) * (double)p.rho0;
+    out[k * p.live + i] = (double)pull_f<D, Q, R>(p, fin, x, y, z, P, k) + L::w(k) * (double)p.rho0;
 }
 
 // inverse of k_gather_f: the stored pre-streaming f* that streams to f^n.
@@ -1064,15 +1067,13 @@ __global__ void k_gather_f(KP<R> p, const R* __restrict__ fin, double* __restric
 template <int D, int Q, class R>
 __global__ void k_scatter_f(KP<R> p, const double* __restrict__ fn, R* __restrict__ fst, int ax, int d) {
   using L = Lat<Q>;
-  const int64_t Qc = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (Qc >= p.cells) return;
-  const int x = (int)(Qc % p.n[0]);
-  const int y = (int)((Qc / p.sy) % p.n[1]);
-  const int z = (int)(Qc / p.sz);
-  auto at = [&](int c0, int c1, int c2) -> int64_t {
+  int64_t Qc;
+  int x, y, z;
+  if (!dense_cell(p, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, x, y, z, Qc)) return;
+  auto at = [&](int c0, int c1, int c2) -> int64_t {  // fn is in dense order
     int c[3] = {c0, c1, c2};
     c[ax] = min(c[ax] + d, p.n[ax] - 1);
-    return (int64_t)c[2] * p.sz + (int64_t)c[1] * p.sy + c[0];
+    return ((int64_t)c[2] * p.n[1] + c[1]) * p.n[0] + c[0];
   };
   for (int k = 0; k < L::Q; ++k) {
     int dst[3] = {x + L::c(k, 0), y + L::c(k, 1), z + L::c(k, 2)};
@@ -1086,10 +1087,10 @@ __global__ void k_scatter_f(KP<R> p, const double* __restrict__ fn, R* __restric
       }
     double val;
     if (in) {
-      val = fn[k * p.cells + at(dst[0], dst[1], dst[2])] - L::w(k) * (double)p.rho0;
+      val = fn[k * p.live + at(dst[0], dst[1], dst[2])] - L::w(k) * (double)p.rho0;
     } else {
       const int kb = L::opp(k);
-      val = fn[kb * p.cells + at(x, y, z)] - L::w(kb) * (double)p.rho0;
+      val = fn[kb * p.live + at(x, y, z)] - L::w(kb) * (double)p.rho0;
       if (L::c(kb, 1) < 0 && !p.per[1] && y - L::c(kb, 1) >= p.n[1])
         val -= 6.0 * L::w(kb) * (double)p.rho0 * L::c(kb, 0) * (double)p.lid_u;
     }
@@ -1097,36 +1098,37 @@ __global__ void k_scatter_f(KP<R> p, const double* __restrict__ fn, R* __restric
   }
 }
 
-template <class R>
-__global__ void k_to_double(const R* __restrict__ in, double* __restrict__ out, int64_t n) {
+// Components between the stored form (padded rows, precision R) and a dense
+// array of T.  MU: component i is stored less r0 (i = 0) or r1, the reference
+// chemical potentials.
+template <class R, class T, bool MU>
+__global__ void k_unpack(KP<R> p, const R* __restrict__ in, T* __restrict__ out, int ncomp, T r0, T r1) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = (double)in[i];
+  int64_t P;
+  int x, y, z;
+  if (!dense_cell(p, i, x, y, z, P)) return;
+  for (int k = 0; k < ncomp; ++k) {
+    T v = (T)in[k * p.cells + P];
+    if (MU) v += k == 0 ? r0 : r1;
+    out[k * p.live + i] = v;
+  }
 }
-
+template <class R, class T, bool MU>
+__global__ void k_pack(KP<R> p, const T* __restrict__ in, R* __restrict__ out, int ncomp, T r0, T r1) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int64_t P;
+  int x, y, z;
+  if (!dense_cell(p, i, x, y, z, P)) return;
+  for (int k = 0; k < ncomp; ++k) {
+    T v = in[k * p.live + i];
+    if (MU) v -= k == 0 ? r0 : r1;
+    out[k * p.cells + P] = (R)v;
+  }
+}
 template <class R>
 __global__ void k_from_double(const double* __restrict__ in, R* __restrict__ out, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) out[i] = (R)in[i];
-}
-
-// chemical potentials: FP64 mu <-> stored mu - mu_ref, component i = idx / cells
-template <class R>
-__global__ void k_mu_to_double(const R* __restrict__ in, double* __restrict__ out, int64_t cells,
-                               int nc, double r0, double r1) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nc * cells) out[i] = (double)in[i] + (i < cells ? r0 : r1);
-}
-template <class R>
-__global__ void k_mu_from_double(const double* __restrict__ in, R* __restrict__ out, int64_t cells,
-                                 int nc, double r0, double r1) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nc * cells) out[i] = (R)(in[i] - (i < cells ? r0 : r1));
-}
-template <class R>
-__global__ void k_mu_native(const R* __restrict__ in, R* __restrict__ out, int64_t cells, int nc,
-                            R r0, R r1) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nc * cells) out[i] = in[i] + (i < cells ? r0 : r1);
 }
 
 // derived per-cell fields in FP64: 0 rho, 1 mixture composition C (nc comps),
@@ -1136,34 +1138,33 @@ __global__ void k_derived(KP<R> p, int which, const R* __restrict__ phi, const R
                           const double* __restrict__ fgathered, double tshift_d,
                           double* __restrict__ out) {
   using L = Lat<Q>;
-  const int64_t P = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (P >= p.cells) return;
-  const int x = (int)(P % p.n[0]);
-  const int y = (int)((P / p.sy) % p.n[1]);
-  const int z = (int)(P / p.sz);
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int64_t P;
+  int x, y, z;
+  if (!dense_cell(p, i, x, y, z, P)) return;
   if (which == 0) {
     double r = 0.0;
-    for (int k = 0; k < L::Q; ++k) r += fgathered[k * p.cells + P];
-    out[P] = r;
+    for (int k = 0; k < L::Q; ++k) r += fgathered[k * p.live + i];
+    out[i] = r;
   } else if (which == 1) {
     double ph[N], h[N], m[NC];
     for (int b = 0; b < N; ++b) ph[b] = (double)phi[b * p.cells + P];
-    for (int i = 0; i < NC; ++i) m[i] = (double)mu[i * p.cells + P];
+    for (int q = 0; q < NC; ++q) m[q] = (double)mu[q * p.cells + P];
     interp_h<N, double>(ph, h);
     const int pos[3] = {x, y, z};
     const double td = (p.G != R(0)) ? (double)p.G * ((double)pos[p.pull_axis] - tshift_d) : (double)p.tdev_iso;
-    for (int i = 0; i < NC; ++i) {
+    for (int q = 0; q < NC; ++q) {
       double c = 0.0;
       for (int b = 0; b < N; ++b) {
-        double C = p.c0s_d[b][i] + (double)p.mT[b][i] * td;
-        for (int k = 0; k < NC; ++k) C += (double)p.chi[i][k] * m[k];
+        double C = p.c0s_d[b][q] + (double)p.mT[b][q] * td;
+        for (int k = 0; k < NC; ++k) C += (double)p.chi[q][k] * m[k];
         c += h[b] * C;
       }
-      out[i * p.cells + P] = c;
+      out[q * p.live + i] = c;
     }
   } else if (which == 2) {
     const int pos[3] = {x, y, z};
-    out[P] = (double)p.T_E + ((p.G != R(0)) ? (double)p.G * ((double)pos[p.pull_axis] - tshift_d)
+    out[i] = (double)p.T_E + ((p.G != R(0)) ? (double)p.G * ((double)pos[p.pull_axis] - tshift_d)
                                               : (double)p.tdev_iso);
   } else {
     unsigned mask = 0u;
@@ -1175,7 +1176,7 @@ __global__ void k_derived(KP<R> p, int which, const R* __restrict__ phi, const R
       for (int b = 0; b < N; ++b)
         if (phi[b * p.cells + j] > R(0)) mask |= 1u << b;
     }
-    out[P] = (double)mask;
+    out[i] = (double)mask;
   }
 }
 
@@ -1192,14 +1193,16 @@ k_partial(KP<R> p, int which, const R* __restrict__ phi, const R* __restrict__ m
   const int t = threadIdx.x;
   double acc[NC];
   for (int i = 0; i < NC; ++i) acc[i] = 0.0;
-  for (int64_t P = (int64_t)blockIdx.x * RED_BLOCK + t; P < p.cells;
-       P += (int64_t)gridDim.x * RED_BLOCK) {
+  for (int64_t j = (int64_t)blockIdx.x * RED_BLOCK + t; j < p.live; j += (int64_t)gridDim.x * RED_BLOCK) {
+    int64_t P;
+    int x, y, z;
+    dense_cell(p, j, x, y, z, P);
     if (which == 0) {
       double ph[N], h[N], m[NC];
       for (int b = 0; b < N; ++b) ph[b] = (double)phi[b * p.cells + P];
       for (int i = 0; i < NC; ++i) m[i] = (double)mu[i * p.cells + P];
       interp_h<N, double>(ph, h);
-      const int pos[3] = {(int)(P % p.n[0]), (int)((P / p.sy) % p.n[1]), (int)(P / p.sz)};
+      const int pos[3] = {x, y, z};
       const double td = (p.G != R(0)) ? (double)p.G * ((double)pos[p.pull_axis] - tshift_d) : (double)p.tdev_iso;
       for (int i = 0; i < NC; ++i) {
         double c = 0.0;
@@ -1211,9 +1214,6 @@ k_partial(KP<R> p, int which, const R* __restrict__ phi, const R* __restrict__ m
         acc[i] += c;
       }
     } else if (which == 1) {
-      const int x = (int)(P % p.n[0]);
-      const int y = (int)((P / p.sy) % p.n[1]);
-      const int z = (int)(P / p.sz);
       double r = 0.0;
       for (int k = 0; k < L::Q; ++k)
         r += (double)pull_f<D, Q, R>(p, f, x, y, z, P, k) + L::w(k) * (double)p.rho0;
@@ -1221,7 +1221,7 @@ k_partial(KP<R> p, int which, const R* __restrict__ phi, const R* __restrict__ m
     } else {
       double r = 0.0;
       for (int b = 0; b < N; ++b) {
-        const double d = (double)phi[b * p.cells + P] - target[b * p.cells + P];
+        const double d = (double)phi[b * p.cells + P] - target[b * p.live + j];
         r += d * d;
       }
       acc[0] += 0.5 * r;
@@ -1258,12 +1258,15 @@ __global__ void k_final_sum(const double* __restrict__ partial, int nblocks, int
   }
 }
 
-// dL/dphi of the loss 1/2 sum (phi - target)^2: phi - target in FP64
+// dL/dphi of the loss 1/2 sum (phi - target)^2: phi - target in FP64, dense
 template <class R>
-__global__ void k_loss_seed(const R* __restrict__ phi, const double* __restrict__ target,
-                            double* __restrict__ out, int64_t n) {
+__global__ void k_loss_seed(KP<R> p, const R* __restrict__ phi, const double* __restrict__ target,
+                            double* __restrict__ out, int ncomp) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = (double)phi[i] - target[i];
+  int64_t P;
+  int x, y, z;
+  if (!dense_cell(p, i, x, y, z, P)) return;
+  for (int k = 0; k < ncomp; ++k) out[k * p.live + i] = (double)phi[k * p.cells + P] - target[k * p.live + i];
 }
 
 // ---------------------------------------------------------------------------
@@ -1320,11 +1323,10 @@ __global__ void k_health(KP<R> p, const R* __restrict__ phi, const R* __restrict
                          const R* __restrict__ f, unsigned long long step,
                          unsigned long long* __restrict__ bad_step) {
   using L = Lat<Q>;
-  const int64_t P = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (P >= p.cells) return;
-  const int x = (int)(P % p.n[0]);
-  const int y = (int)((P / p.sy) % p.n[1]);
-  const int z = (int)(P / p.sz);
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int64_t P;
+  int x, y, z;
+  if (!dense_cell(p, i, x, y, z, P)) return;
   bool bad = false;
   for (int b = 0; b < N; ++b) bad |= !isfinite(phi[b * p.cells + P]);
   for (int i = 0; i < NC; ++i) bad |= !isfinite(mu[i * p.cells + P]);

@@ -49,6 +49,9 @@ struct gpf_ctx {
   int N = 0, nc = 0, Q = 0, dim = 0;
   int64_t n[3] = {1, 1, 1};
   int64_t cells = 0;
+  // stored rows (elements) and stored elements per component of the state:
+  // see row_pitch
+  int64_t pitch = 0, pcells = 0;
   size_t esize = 8;  // bytes per stored value
   hipStream_t stream = nullptr;
   DevBuf phi[2], mu[2], u[2], f[2];
@@ -149,6 +152,18 @@ void dev_release(gpf_ctx* c, DevBuf& b) {
 // ---------------------------------------------------------------------------
 // kernel parameter block
 // ---------------------------------------------------------------------------
+// Elements per stored row.  Rows start on 128-byte lines: a wave then stores
+// whole lines.  With rows of n[0] elements as they come, the streaming stores
+// of a width that is no multiple of a line leave the chip as partial lines
+// (255 x 256 x 128, FP32: k_mulbm took 560 us, 256 x 256 x 128 took 317; with
+// cached stores 427).  Rows shorter than half a line stay as they are, and so
+// do large grids whose memory would grow by more than an eighth.
+int64_t row_pitch(int64_t n0, int64_t cells, size_t esize) {
+  const int64_t line = 128 / (int64_t)esize, p = (n0 + line - 1) / line * line;
+  if (p > 2 * n0 || (cells > ((int64_t)1 << 24) && 8 * p > 9 * n0)) return n0;
+  return p;
+}
+
 // lattice weight w_k of D2Q9 (Q = 9), D3Q19 or D3Q27
 double lattice_w(int Q, int k) {
   return Q == 9 ? gpf::Lat<9>::w(k) : (Q == 19 ? gpf::Lat<19>::w(k) : gpf::Lat<27>::w(k));
@@ -163,9 +178,10 @@ gpf::KP<R> make_kp(const gpf_ctx* c) {
     k.n[a] = (int)c->n[a];
     k.per[a] = (a < c->dim) ? (int)((c->grid.periodic_mask >> a) & 1u) : 1;
   }
-  k.sy = c->n[0];
-  k.sz = c->n[0] * c->n[1];
-  k.cells = c->cells;
+  k.sy = c->pitch;
+  k.sz = c->pitch * c->n[1];
+  k.cells = c->pcells;
+  k.live = c->cells;
   k.potential = p.potential;
   k.pull_axis = p.pull_axis;
   k.grav_axis = p.grav_axis;
@@ -306,14 +322,13 @@ inline unsigned adj_blocks(const int64_t (&n)[3]) {
 #define GPF_ZCHUNK_PHI 16
 constexpr int kTileY = GPF_TILE_Y;
 constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
-// tiles of k_mulbm in 3D (64 x 4 cells in 2D), one cell per thread, and the
-// tile rows of a strip of its tile order (both measured, see the kernel)
+// tiles of k_mulbm in 3D (64 x 4 cells in 2D), one cell per thread (measured,
+// see the kernel)
 #ifndef GPF_MU_TX
 #define GPF_MU_TX 64
 #define GPF_MU_TY 4
 #define GPF_MU_TZ 2
 #endif
-#define GPF_MU_STRIP 8
 // planes that a block of the bandwidth probe's z-marched pull walks
 constexpr int kProbeZ = 4;
 // planes per phase-field block: a two-phase step spends its phase-field time
@@ -396,7 +411,7 @@ struct Impl {
 #define GPF_MULBM(SH, MT)                                                                                        \
   hipLaunchKernelGGL((gpf::k_mulbm<D, Q, N, NC, R, MX, MY, MZ, SH, MT>), mgrid, dim3(MX * MY * MZ), 0, st, k, in.phi, \
                      out.phi, in.mu, in.u, in.f, out.mu, out.u, out.f, out.dr, bulk_out, ilog2(TX), ilog2(TY), ilog2(ZP), ts, mtx, mty,    \
-                     GPF_MU_STRIP, counts)
+                     (mty + 7) / 8, counts)
     if (k.shrink) {
       if (k.tdep)
         GPF_MULBM(true, true);
@@ -430,12 +445,10 @@ struct Impl {
     const int64_t d = (int64_t)front - c->prm.frame_front;
     if (front < 0 || d <= 0) return GPF_OK;
     const int ax = c->prm.pull_axis;
-    const int64_t stride = ax == 0 ? 1 : (ax == 1 ? c->n[0] : c->n[0] * c->n[1]);
     const int s = c->cur, t = 1 - c->cur;
     auto mv = [&](DevBuf& in, DevBuf& out, int ncomp) {
-      const int64_t count = (int64_t)ncomp * c->cells;
-      hipLaunchKernelGGL((gpf::k_shift<R>), dim3(lin_blocks(count, 256)), dim3(256), 0, c->stream, P(in), P(out),
-                         count, c->cells, stride, c->n[ax], d);
+      hipLaunchKernelGGL((gpf::k_shift<R>), dim3(lin_blocks(c->cells, 256)), dim3(256), 0, c->stream, k, P(in), P(out),
+                         ncomp, ax, d);
     };
     mv(c->phi[s], c->phi[t], N);
     mv(c->mu[s], c->mu[t], NC);
@@ -581,20 +594,14 @@ struct Impl {
       case GPF_U: ncomp = D; break;
       default: break;
     }
+    if (field == GPF_FPOST) ncomp = Q;
     if (field == GPF_MU) {
-      const int64_t cnt = ncomp * c->cells;
-      hipLaunchKernelGGL((gpf::k_mu_to_double<R>), dim3(lin_blocks(cnt, 256)), dim3(256), 0, c->stream,
-                         P(c->mu[s]), out, c->cells, NC, k.mu_ref_d[0], k.mu_ref_d[1]);
+      hipLaunchKernelGGL((gpf::k_unpack<R, double, true>), dim3(nb), dim3(256), 0, c->stream, k, P(c->mu[s]), out, ncomp,
+                         k.mu_ref_d[0], k.mu_ref_d[1]);
     } else if (ncomp) {
-      const R* src = field == GPF_PHI ? P(c->phi[s]) : P(c->u[s]);
-      const int64_t cnt = ncomp * c->cells;
-      hipLaunchKernelGGL((gpf::k_to_double<R>), dim3(lin_blocks(cnt, 256)), dim3(256), 0, c->stream, src,
-                         out, cnt);
-    } else if (field == GPF_FPOST) {
-      ncomp = Q;
-      const int64_t cnt = ncomp * c->cells;
-      hipLaunchKernelGGL((gpf::k_to_double<R>), dim3(lin_blocks(cnt, 256)), dim3(256), 0, c->stream,
-                         P(c->f[s]), out, cnt);
+      const R* src = field == GPF_PHI ? P(c->phi[s]) : (field == GPF_U ? P(c->u[s]) : P(c->f[s]));
+      hipLaunchKernelGGL((gpf::k_unpack<R, double, false>), dim3(nb), dim3(256), 0, c->stream, k, src, out, ncomp, 0.0,
+                         0.0);
     } else if (field == GPF_F || field == GPF_RHO) {
       ncomp = (field == GPF_F) ? Q : 1;
       hipLaunchKernelGGL((gpf::k_gather_f<D, Q, R>), dim3(nb), dim3(256), 0, c->stream, k, P(c->f[s]),
@@ -621,33 +628,37 @@ struct Impl {
   }
 
   static int read_native(gpf_ctx* c, int field, void* dst) {
+    gpf::KP<R> k = make_kp<R>(c);
     const int s = c->cur;
-    size_t bytes = 0;
-    const void* src = nullptr;
+    R* out = static_cast<R*>(dst);
+    const dim3 g(lin_blocks(c->cells, 256)), b(256);
     switch (field) {
-      case GPF_PHI: src = c->phi[s].ptr; bytes = N * c->cells * sizeof(R); break;
-      case GPF_MU: {
-        gpf::KP<R> k = make_kp<R>(c);
-        const int64_t cnt = NC * c->cells;
-        hipLaunchKernelGGL((gpf::k_mu_native<R>), dim3(lin_blocks(cnt, 256)), dim3(256), 0, c->stream,
-                           P(c->mu[s]), static_cast<R*>(dst), c->cells, NC, k.mu_ref[0], k.mu_ref[1]);
-        HIP_OR_FAIL(c, hipGetLastError());
-        return GPF_OK;
+      case GPF_PHI:
+      case GPF_U: {
+        const R* src = field == GPF_PHI ? P(c->phi[s]) : P(c->u[s]);
+        const int ncomp = field == GPF_PHI ? N : D;
+        if (c->pcells == c->cells)
+          HIP_OR_FAIL(c, hipMemcpyAsync(dst, src, ncomp * c->cells * sizeof(R), hipMemcpyDeviceToDevice, c->stream));
+        else
+          hipLaunchKernelGGL((gpf::k_unpack<R, R, false>), g, b, 0, c->stream, k, src, out, ncomp, R(0), R(0));
+        break;
       }
-      case GPF_U: src = c->u[s].ptr; bytes = D * c->cells * sizeof(R); break;
+      case GPF_MU:
+        hipLaunchKernelGGL((gpf::k_unpack<R, R, true>), g, b, 0, c->stream, k, P(c->mu[s]), out, NC, k.mu_ref[0],
+                           k.mu_ref[1]);
+        break;
       case GPF_F: {
         double comps = 0;
         int rc = read(c, GPF_F, &comps);
         if (rc) return rc;
         const int64_t cnt = Q * c->cells;
         hipLaunchKernelGGL((gpf::k_from_double<R>), dim3(lin_blocks(cnt, 256)), dim3(256), 0,
-                           c->stream, static_cast<const double*>(c->scratch.ptr), static_cast<R*>(dst), cnt);
-        HIP_OR_FAIL(c, hipGetLastError());
-        return GPF_OK;
+                           c->stream, static_cast<const double*>(c->scratch.ptr), out, cnt);
+        break;
       }
       default: return fail(c, GPF_ERR_ARG, "field %d has no native device copy", field);
     }
-    HIP_OR_FAIL(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, c->stream));
+    HIP_OR_FAIL(c, hipGetLastError());
     return GPF_OK;
   }
 
@@ -656,23 +667,16 @@ struct Impl {
     gpf::KP<R> k = make_kp<R>(c);
     const int s = c->cur;
     const double* in = static_cast<const double*>(c->scratch.ptr);
-    if (field == GPF_FPOST) {
-      const int64_t cnt = Q * c->cells;
-      hipLaunchKernelGGL((gpf::k_from_double<R>), dim3(lin_blocks(cnt, 256)), dim3(256), 0, c->stream, in,
-                         P(c->f[s]), cnt);
-    } else if (field == GPF_F) {
-      hipLaunchKernelGGL((gpf::k_scatter_f<D, Q, R>), dim3(lin_blocks(c->cells, 256)), dim3(256), 0,
-                         c->stream, k, in, P(c->f[s]), 0, 0);
+    const dim3 g(lin_blocks(c->cells, 256)), b(256);
+    if (field == GPF_F) {
+      hipLaunchKernelGGL((gpf::k_scatter_f<D, Q, R>), g, b, 0, c->stream, k, in, P(c->f[s]), 0, 0);
     } else if (field == GPF_MU) {
-      const int64_t cnt = NC * c->cells;
-      hipLaunchKernelGGL((gpf::k_mu_from_double<R>), dim3(lin_blocks(cnt, 256)), dim3(256), 0, c->stream, in,
-                         P(c->mu[s]), c->cells, NC, k.mu_ref_d[0], k.mu_ref_d[1]);
+      hipLaunchKernelGGL((gpf::k_pack<R, double, true>), g, b, 0, c->stream, k, in, P(c->mu[s]), NC, k.mu_ref_d[0],
+                         k.mu_ref_d[1]);
     } else {
-      int ncomp = field == GPF_PHI ? N : D;
-      R* dst = field == GPF_PHI ? P(c->phi[s]) : P(c->u[s]);
-      const int64_t cnt = ncomp * c->cells;
-      hipLaunchKernelGGL((gpf::k_from_double<R>), dim3(lin_blocks(cnt, 256)), dim3(256), 0, c->stream, in,
-                         dst, cnt);
+      const int ncomp = field == GPF_PHI ? N : (field == GPF_U ? D : Q);
+      R* dst = field == GPF_PHI ? P(c->phi[s]) : (field == GPF_U ? P(c->u[s]) : P(c->f[s]));
+      hipLaunchKernelGGL((gpf::k_pack<R, double, false>), g, b, 0, c->stream, k, in, dst, ncomp, 0.0, 0.0);
     }
     HIP_OR_FAIL(c, hipGetLastError());
     return GPF_OK;
@@ -704,16 +708,16 @@ struct Impl {
   }
 
   static int loss_seed(gpf_ctx* c, double* dev_seed) {
-    const int64_t cnt = (int64_t)N * c->cells;
-    hipLaunchKernelGGL((gpf::k_loss_seed<R>), dim3(lin_blocks(cnt, 256)), dim3(256), 0, c->stream,
-                       P(c->phi[c->cur]), c->target, dev_seed, cnt);
+    gpf::KP<R> k = make_kp<R>(c);
+    hipLaunchKernelGGL((gpf::k_loss_seed<R>), dim3(lin_blocks(c->cells, 256)), dim3(256), 0, c->stream, k,
+                       P(c->phi[c->cur]), c->target, dev_seed, N);
     HIP_OR_FAIL(c, hipGetLastError());
     return GPF_OK;
   }
 
   // ---------------- adjoint ----------------
   static int alloc_state(gpf_ctx* c, StateBuf& s) {
-    const size_t cs = (size_t)c->cells * sizeof(R);
+    const size_t cs = (size_t)c->pcells * sizeof(R);
     int rc = dev_alloc(c, s.phi, N * cs);
     if (!rc) rc = dev_alloc(c, s.mu, NC * cs);
     if (!rc) rc = dev_alloc(c, s.u, D * cs);
@@ -842,7 +846,7 @@ struct Impl {
       return fail(c, GPF_ERR_STATE, "nothing recorded: call gpf_record before stepping");
     if (c->n[0] * ((c->n[1] + 7) / 8) * c->n[2] >= ((int64_t)1 << 31))
       return fail(c, GPF_ERR_UNSUPPORTED, "grid too large for the adjoint's 32-bit cell slots");
-    const size_t cs = (size_t)c->cells * sizeof(R);
+    const size_t cs = (size_t)c->pcells * sizeof(R);
     int rc = GPF_OK;
     if (!c->lam[0].phi.ptr) {
       for (int i = 0; i < 2 && !rc; ++i) rc = alloc_state(c, c->lam[i]);
@@ -854,9 +858,9 @@ struct Impl {
       if (!rc) rc = dev_alloc(c, c->t_part, (size_t)(D + 3) * nb * gpf::NG * sizeof(double));
       if (!rc) rc = dev_alloc(c, c->t_acc, gpf::NG * sizeof(double));
       if (!rc) rc = dev_alloc(c, c->t_slices, (size_t)gpf::GA * gpf::NG * sizeof(double));
-      if (!rc) rc = dev_alloc(c, c->t_rflag, (size_t)c->cells);
+      if (!rc) rc = dev_alloc(c, c->t_rflag, (size_t)c->pcells);
       if (!rc) rc = dev_alloc(c, c->t_rowflag, (size_t)2 * c->n[1] * c->n[2]);
-      if (!rc) rc = dev_alloc(c, c->t_fflag, (size_t)D * c->cells);
+      if (!rc) rc = dev_alloc(c, c->t_fflag, (size_t)D * c->pcells);
       // reverse of the face fluxes and cell terms: N (1 + D) values per face / cell
       if (!rc) rc = dev_alloc(c, c->t_fbuf, (size_t)D * N * (1 + D) * cs);
       if (!rc) rc = dev_alloc(c, c->t_cbuf, (size_t)N * (1 + D) * cs);
@@ -882,7 +886,7 @@ struct Impl {
         int r;
         if (!c->tape_f[b][i].ptr && (r = dev_alloc(c, c->tape_f[b][i], Q * cs))) return r;
       }
-      const size_t act_bytes = (size_t)(K - 1) * (size_t)c->cells;
+      const size_t act_bytes = (size_t)(K - 1) * (size_t)c->pcells;
       if (K > 1 && c->tape_act[b].bytes < act_bytes) {
         dev_release(c, c->tape_act[b]);
         if (int r = dev_alloc(c, c->tape_act[b], act_bytes)) return r;
@@ -926,12 +930,11 @@ struct Impl {
     if (!seed_on_device)
       HIP_OR_FAIL(c, hipMemcpyAsync(c->scratch.ptr, seed, (size_t)N * c->cells * sizeof(double),
                                     hipMemcpyHostToDevice, c->stream));
-    hipLaunchKernelGGL((gpf::k_from_double<R>), dim3(lin_blocks(N * c->cells, 256)), dim3(256), 0,
-                       c->stream, seed_on_device ? seed : static_cast<const double*>(c->scratch.ptr), P(li->phi),
-                       N * c->cells);
-    fill(c, li->mu, NC * c->cells);
-    fill(c, li->u, D * c->cells);
-    fill(c, li->f, Q * c->cells);
+    hipLaunchKernelGGL((gpf::k_pack<R, double, false>), dim3(lin_blocks(c->cells, 256)), dim3(256), 0, c->stream, k,
+                       seed_on_device ? seed : static_cast<const double*>(c->scratch.ptr), P(li->phi), N, 0.0, 0.0);
+    fill(c, li->mu, NC * c->pcells);
+    fill(c, li->u, D * c->pcells);
+    fill(c, li->f, Q * c->pcells);
     hipLaunchKernelGGL((gpf::k_fill<double>), dim3(1), dim3(gpf::NG), 0, c->stream,
                        static_cast<double*>(c->t_acc.ptr), (int64_t)gpf::NG, 0.0);
     // per-block running sums of the parameter derivatives over the sweep
@@ -952,7 +955,7 @@ struct Impl {
     auto seg_len = [&](int64_t sg) { return std::min<int64_t>(K, total - sg * K); };
     // step j of the recomputation of segment sg into tape b; it also records
     // the active sets of phi^{n0 + j} (j < K - 1)
-    auto act_of = [&](int b, int64_t j) { return static_cast<uint8_t*>(c->tape_act[b].ptr) + j * c->cells; };
+    auto act_of = [&](int b, int64_t j) { return static_cast<uint8_t*>(c->tape_act[b].ptr) + j * c->pcells; };
     auto recompute_step = [&](int b, int64_t sg, int64_t j, hipStream_t st) {
       launch_step(c, k, slot(b, sg, j), slot(b, sg, j + 1), (R)tshift(c, c->rec_start + sg * K + j), st, nullptr,
                   nullptr, nullptr, act_of(b, j));
@@ -1036,16 +1039,17 @@ struct Impl {
   static int lam_read(gpf_ctx* c, int field, double* host) {
     StateBuf& l = c->lam[c->lam_cur];
     const R* src = nullptr;
-    int64_t cnt = 0;
+    int ncomp = 0;
     switch (field) {
-      case GPF_PHI: src = P(l.phi); cnt = N * c->cells; break;
-      case GPF_MU: src = P(l.mu); cnt = NC * c->cells; break;
-      case GPF_U: src = P(l.u); cnt = D * c->cells; break;
-      case GPF_F: src = P(l.f); cnt = Q * c->cells; break;
+      case GPF_PHI: src = P(l.phi); ncomp = N; break;
+      case GPF_MU: src = P(l.mu); ncomp = NC; break;
+      case GPF_U: src = P(l.u); ncomp = D; break;
+      case GPF_F: src = P(l.f); ncomp = Q; break;
       default: return fail(c, GPF_ERR_ARG, "field %d has no adjoint", field);
     }
-    hipLaunchKernelGGL((gpf::k_to_double<R>), dim3(lin_blocks(cnt, 256)), dim3(256), 0, c->stream, src,
-                       static_cast<double*>(c->scratch.ptr), cnt);
+    const int64_t cnt = ncomp * c->cells;
+    hipLaunchKernelGGL((gpf::k_unpack<R, double, false>), dim3(lin_blocks(c->cells, 256)), dim3(256), 0, c->stream,
+                       make_kp<R>(c), src, static_cast<double*>(c->scratch.ptr), ncomp, 0.0, 0.0);
     HIP_OR_FAIL(c, hipMemcpyAsync(host, c->scratch.ptr, cnt * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));
     return GPF_OK;
@@ -1356,9 +1360,11 @@ int gpf_init(gpf_ctx** out, const gpf_grid* grid, int32_t n_phases, int32_t n_co
   for (int a = 0; a < 3; ++a) c->n[a] = (a < c->dim) ? grid->n[a] : 1;
   c->cells = c->n[0] * c->n[1] * c->n[2];
   c->esize = (params->precision == GPF_FP64) ? 8 : 4;
+  c->pitch = row_pitch(c->n[0], c->cells, c->esize);
+  c->pcells = c->pitch * c->n[1] * c->n[2];
   c->ops = pick(c->Q, c->N, c->nc, params->precision);
   rc = resolve_scratch(c);
-  const size_t cs = (size_t)c->cells * c->esize;
+  const size_t cs = (size_t)c->pcells * c->esize;
   for (int s = 0; s < 2 && !rc; ++s) {
     if (!rc) rc = dev_alloc(c, c->phi[s], c->N * cs);
     if (!rc) rc = dev_alloc(c, c->mu[s], c->nc * cs);
@@ -1578,7 +1584,7 @@ int gpf_record(gpf_ctx* c, int64_t checkpoint_every) {
   c->rec_start = c->step;
   c->have_adjoint = false;
   StateBuf s;
-  const size_t cs = (size_t)c->cells * c->esize;
+  const size_t cs = (size_t)c->pcells * c->esize;
   int rc = dev_alloc(c, s.phi, c->N * cs);
   if (!rc) rc = dev_alloc(c, s.mu, c->nc * cs);
   if (!rc) rc = dev_alloc(c, s.u, c->dim * cs);

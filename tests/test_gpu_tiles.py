@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
 GRIDS = [("binary3d", [63, 5, 3]), ("binary3d", [64, 4, 2]), ("binary3d", [65, 3, 1]), ("binary3d", [130, 33, 5]),
          ("ternary3d_nc2", [66, 31, 4]), ("ternary3d_nc2", [1, 2, 9]), ("quaternary3d", [32, 65, 3]),
          ("quaternary3d", [33, 4, 17]), ("binary2d", [63, 3]), ("binary2d", [65, 33]), ("ternary2d", [191, 5]),
-         ("ternary2d_nc2", [2, 67]), ("quaternary2d", [129, 34])]
+         ("ternary2d_nc2", [2, 67]), ("quaternary2d", [129, 34]),
+         # stored rows are padded to 16 values (FP64) from half a line on: the widths around that
+         ("binary3d", [7, 5, 3]), ("binary3d", [8, 5, 3]), ("ternary2d", [9, 6]), ("binary2d", [17, 9])]
 
 
 def _check(cfg, steps):
