@@ -582,8 +582,10 @@ k_adj_muphi(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1,
       for (int b = 0; b < N; ++b) p0b[b] += pb[b];
     } else {
       if constexpr (ACT) load_stencil<D, N, R>(p, phi0, x, y, z, v);
-      R Rv[N], vv[N], out[N], theta;
-      pf_rhs<D, N, NC, R>(p, v, mu0, x, y, z, tshift, Rv);
+      R Rv[N], vv[N], out[N], theta, ms[NC];
+#pragma unroll
+      for (int i = 0; i < NC; ++i) ms[i] = mu0[i * p.cells + P];
+      pf_rhs<D, N, NC, R, false>(p, v, ms, x, y, z, tshift, Rv);
 #pragma unroll
       for (int b = 0; b < N; ++b) vv[b] = v[b][1][1][1] + p.rate * Rv[b];
       project_masked<N, R>(active, vv, out, theta);

@@ -1,7 +1,7 @@
 // gpf_kernels.hpp -- HIP kernels of the coupled GP phase-field / LBM step.
 //
 // One step = two launches over tiles of cells:
-//   k_phi_z    phi^n, mu^n            -> phi^{n+1}          (Eq. PhfGrand, Sec. 2.1)
+//   k_phi    phi^n, mu^n            -> phi^{n+1}          (Eq. PhfGrand, Sec. 2.1)
 //   k_mulbm    phi^n, phi^{n+1}, mu^n, U^{n-1}, f*^{n-1}
 //                                     -> mu^{n+1}, U^n, f*^n (Eq. conc; Eqs. LBMEq_1,
 //                                        f^eq, discreteForce, buoyancy, rhovel)
@@ -186,11 +186,11 @@ __device__ __forceinline__ unsigned active_of(const R (&v)[N][3][3][3]) {
 //   R_a = eps [div J_a - sum_b dA_ab/dq(q_ab) . grad phi_b] - dW/dphi_a / eps
 //         - sum_b psi^b dh_b/dphi_a,
 // J_a = -sum_b phi_b,f dA_ab/dq(q_ab,f) on faces (none on wall faces).
-template <int D, int N, int NC, class R>
-__device__ __forceinline__ void pf_rhs(const KP<R>& p, const R (&v)[N][3][3][3],
-                                       const R* __restrict__ mu, int x, int y, int z, R tshift,
-                                       R (&Rv)[N]) {
-  const int64_t P = (int64_t)z * p.sz + (int64_t)y * p.sy + x;
+// mu: mu^n as stored.  ISO: no pair has an anisotropy, so a face flux needs
+// the normal derivative only (the general form's values, bit for bit).
+template <int D, int N, int NC, class R, bool ISO>
+__device__ __forceinline__ void pf_rhs(const KP<R>& p, const R (&v)[N][3][3][3], const R (&mu)[NC], int x, int y,
+                                       int z, R tshift, R (&Rv)[N]) {
   const int pos[3] = {x, y, z};
   const R idx = R(1) / p.dx;
   const R ih2 = R(0.5) / p.dx;
@@ -225,7 +225,7 @@ __device__ __forceinline__ void pf_rhs(const KP<R>& p, const R (&v)[N][3][3][3],
         for (int e = 0; e < D; ++e) {
           if (e == a)
             gf[b][e] = R(s) * (vQ - vP) * idx;
-          else
+          else if constexpr (!ISO)
             gf[b][e] = R(0.5) * (gc(b, 0, 0, 0, e) + gc(b, o[0], o[1], o[2], e));
         }
       }
@@ -237,9 +237,13 @@ __device__ __forceinline__ void pf_rhs(const KP<R>& p, const R (&v)[N][3][3][3],
 #pragma unroll
         for (int be = al + 1; be < N; ++be) {
           R q[D], g[D];
+          if constexpr (ISO) {
+            g[a] = R(2) * p.gamma[al][be] * (pf[al] * gf[be][a] - pf[be] * gf[al][a]);
+          } else {
 #pragma unroll
-          for (int e = 0; e < D; ++e) q[e] = pf[al] * gf[be][e] - pf[be] * gf[al][e];
-          dAdq<D, R, R>(q, p.gamma[al][be], p.delta[al][be], p.qmin2, g);
+            for (int e = 0; e < D; ++e) q[e] = pf[al] * gf[be][e] - pf[be] * gf[al][e];
+            dAdq<D, R, R>(q, p.gamma[al][be], p.delta[al][be], p.qmin2, g);
+          }
           J[al] -= pf[be] * g[a];
           J[be] += pf[al] * g[a];
         }
@@ -266,7 +270,12 @@ __device__ __forceinline__ void pf_rhs(const KP<R>& p, const R (&v)[N][3][3][3],
       R q[D], g[D];
 #pragma unroll
       for (int e = 0; e < D; ++e) q[e] = ph[al] * g0[be][e] - ph[be] * g0[al][e];
-      dAdq<D, R, R>(q, p.gamma[al][be], p.delta[al][be], p.qmin2, g);
+      if constexpr (ISO) {
+#pragma unroll
+        for (int e = 0; e < D; ++e) g[e] = R(2) * p.gamma[al][be] * q[e];
+      } else {
+        dAdq<D, R, R>(q, p.gamma[al][be], p.delta[al][be], p.qmin2, g);
+      }
 #pragma unroll
       for (int e = 0; e < D; ++e) {
         cell[al] += g[e] * g0[be][e];
@@ -277,7 +286,7 @@ __device__ __forceinline__ void pf_rhs(const KP<R>& p, const R (&v)[N][3][3][3],
   // grand potentials psi^b(mu, T) = -1/2 mu.chi.mu - mu.(c0[b] + mT[b] (T - T_E)) + dS[b] (T - T_E)
   R m[NC];
 #pragma unroll
-  for (int i = 0; i < NC; ++i) m[i] = p.mu_ref[i] + mu[i * p.cells + P];
+  for (int i = 0; i < NC; ++i) m[i] = p.mu_ref[i] + mu[i];
   const R tdev = (p.G != R(0)) ? p.G * (R(pos[p.pull_axis]) - tshift) : p.tdev_iso;
   R ps[N];
 #pragma unroll
@@ -315,9 +324,9 @@ __device__ __forceinline__ void pf_rhs(const KP<R>& p, const R (&v)[N][3][3][3],
 // phase is active (bulk, returned true), else the projection of
 // phi + dt/(tau eps) R over the active phases onto the simplex.  act_out, if
 // not null, receives the cell's active set.
-template <int D, int N, int NC, class R>
+template <int D, int N, int NC, class R, bool ISO>
 __device__ __forceinline__ bool phi_from_stencil(const KP<R>& p, const R (&v)[N][3][3][3],
-                                                 const R* __restrict__ mu, int x, int y, int z,
+                                                 const R (&mu)[NC], int x, int y, int z,
                                                  R tshift, R (&res)[N], uint8_t* __restrict__ act_out) {
   const unsigned active = active_of<D, N, R>(v);
   if (act_out) *act_out = (uint8_t)active;
@@ -327,7 +336,7 @@ __device__ __forceinline__ bool phi_from_stencil(const KP<R>& p, const R (&v)[N]
     return true;
   }
   R Rv[N], vv[N];
-  pf_rhs<D, N, NC, R>(p, v, mu, x, y, z, tshift, Rv);
+  pf_rhs<D, N, NC, R, ISO>(p, v, mu, x, y, z, tshift, Rv);
 #pragma unroll
   for (int b = 0; b < N; ++b) vv[b] = v[b][1][1][1] + p.rate * Rv[b];
   R theta;
@@ -497,85 +506,81 @@ __device__ __forceinline__ int wrap_or_clamp(int v, int n, int per) {
 // round-robin; renumbering gives each XCD a contiguous range of tiles, so
 // tiles that are neighbours in y and z share its L2.
 struct Tile {
-  int x0, y0, z0, z1;
-  unsigned lb;  // logical tile index: x fastest, then y, then the chunk along z
+  int x0, y0, z0;
+  unsigned lb;  // tile index: x fastest, then y, then z
 };
-__device__ __forceinline__ Tile tile_at(unsigned lb, int tiles_x, int tiles_y, int tx, int ty, int zc,
-                                        int nz, int D) {
+template <int D, int TX, int TY, int TZ> struct PhiTile {
+  static constexpr int HC = (TX + 2) * (TY + 2) * (D == 3 ? TZ + 2 : 1);  // cells with the halo
+};
+template <int TX, int TY, int TZ>
+__device__ __forceinline__ Tile tile_at(unsigned lb, int tiles_x, int tiles_y) {
   Tile t;
   t.lb = lb;
-  t.x0 = (int)(lb % (unsigned)tiles_x) * tx;
-  t.y0 = (int)((lb / (unsigned)tiles_x) % (unsigned)tiles_y) * ty;
-  const int tz = (int)(lb / ((unsigned)tiles_x * (unsigned)tiles_y));
-  t.z0 = (D == 3) ? tz * zc : 0;
-  t.z1 = (D == 3) ? min(t.z0 + zc, nz) : 1;
+  const unsigned q = lb / (unsigned)tiles_x;
+  t.x0 = (int)(lb - q * (unsigned)tiles_x) * TX;
+  t.z0 = (int)(q / (unsigned)tiles_y) * TZ;
+  t.y0 = (int)(q % (unsigned)tiles_y) * TY;
   return t;
 }
-__device__ __forceinline__ Tile tile_of(int tiles_x, int tiles_y, int tx, int ty, int zc, int nz,
-                                        int D) {
-  const unsigned nb = gridDim.x, b = blockIdx.x;
-  const unsigned per8 = nb / 8u;
-  const unsigned lb = (b < per8 * 8u) ? (b % 8u) * per8 + b / 8u : b;
-  return tile_at(lb, tiles_x, tiles_y, tx, ty, zc, nz, D);
+__device__ __forceinline__ unsigned xcd_block() {
+  const unsigned nb = gridDim.x, b = blockIdx.x, per8 = nb / 8u;
+  return (b < per8 * 8u) ? (b % 8u) * per8 + b / 8u : b;
 }
 
 // ---------------------------------------------------------------------------
-// Phase field, z-marching: a block owns a TX x TY tile and walks along z
-// through planes [z0, z1).  phi^n of the tile plus a one-cell halo is kept in
-// a four-slot LDS ring (planes z-1, z, z+1 in use, z+2 being filled), so every
-// phi^n value is read from memory once per block and the 9/19-point stencil
-// reads LDS.  The plane two ahead is fetched into registers before a plane is
-// computed and stored to the ring after it, so its loads are in flight during
-// the computation; one barrier per plane.
+// Phase field over TX x TY x TZ tiles, one cell per thread: phi^n of the tile
+// and its one-cell halo goes to LDS (all of a block's loads in flight
+// together, the cell's own mu^n with them), one barrier, then the 9/19-point
+// stencil reads LDS.  Bound by the latency of one such tile where few are
+// walked (dendrites), by VALU issue on lamellar solids.  The form before this
+// one walked 4 or 16 planes of a 64 x 4 column with a barrier per plane; us
+// per step of the phase field (todo list and walk), then and now: 28 -> 17
+// (256^3 dendrite), 24 -> 17 (64^3), 28 -> 18 (FP64 150 x 131 x 117), 81 -> 42
+// (192^3, three phases; 14 of these from ISO), 67 -> 22 (96^3, three phases),
+// 91 -> 26 (96 x 96 x 128, four phases).  Tiles of 32 x 4 x 4 cells took 46
+// and 30 us in the 192^3 and the four-phase case, 16 x 4 x 4 43 and 27,
+// 32 x 8 x 4 49 and 29.
 // ---------------------------------------------------------------------------
-// One block's walk through the planes of its tile T (the body of k_phi_z and
-// k_phi_zl).  was_bulk: phi_out, which still holds phi^{n-1}, already holds
-// phi^n on every cell of T.  Ends in a barrier after the last read of the
-// ring.
-template <int D, int N, int NC, class R, int TX, int TY, bool ACT, class Ring>
-__device__ __forceinline__ void phi_walk(const KP<R>& p, const R* __restrict__ phi, const R* __restrict__ mu,
+// One tile.  was_bulk: phi_out, which still holds phi^{n-1}, already holds
+// phi^n on every cell of T.  Ends in a barrier after the last read of sh.
+// act_out (null: none) receives each cell's active set of phases.
+template <int D, int N, int NC, class R, int TX, int TY, int TZ, bool ISO>
+__device__ __forceinline__ void phi_tile(const KP<R>& p, const R* __restrict__ phi, const R* __restrict__ mu,
                                          R* __restrict__ phi_out, bool was_bulk, uint8_t* __restrict__ bulk_out,
-                                         uint8_t* __restrict__ act_out, R tshift, const Tile& T, Ring& ring) {
-  constexpr int HX = TX + 2, HY = TY + 2, HC = HX * HY;
-  constexpr int NT = TX * TY, PER = (HC + NT - 1) / NT;  // halo-tile cells per thread
+                                         uint8_t* __restrict__ act_out, R tshift, const Tile& T,
+                                         R (&sh)[N][PhiTile<D, TX, TY, TZ>::HC]) {
+  constexpr int HX = TX + 2, HY = TY + 2, HC = PhiTile<D, TX, TY, TZ>::HC;
+  constexpr int NT = TX * TY * TZ, PER = (HC + NT - 1) / NT;  // halo-tile cells per thread
   const int tid = threadIdx.x;
-  const int lx = tid % TX, ly = tid / TX;
-  const int x = T.x0 + lx, y = T.y0 + ly;
-  const bool own = x < p.n[0] && y < p.n[1];
-  const int c0 = (ly + 1) * HX + (lx + 1);
-  int all_bulk = 1;
-
-  // in-plane offsets of this thread's halo-tile cells (fixed along z)
-  int64_t hoff[PER];
+  const int lx = tid % TX, ly = (tid / TX) % TY, lz = tid / (TX * TY);
+  const int x = T.x0 + lx, y = T.y0 + ly, z = T.z0 + lz;
+  const bool own = x < p.n[0] && y < p.n[1] && (D == 2 || z < p.n[2]);
+  const int64_t P = (int64_t)z * p.sz + (int64_t)y * p.sy + x;
+  R pre[PER][N], m[NC];
 #pragma unroll
   for (int r = 0; r < PER; ++r) {
-    const int i = min(tid + r * NT, HC - 1);
-    const int gx = wrap_or_clamp(T.x0 - 1 + i % HX, p.n[0], p.per[0]);
-    const int gy = wrap_or_clamp(T.y0 - 1 + i / HX, p.n[1], p.per[1]);
-    hoff[r] = (int64_t)gy * p.sy + gx;
+    const int i = tid + r * NT;
+    if (i < HC) {
+      const int gx = wrap_or_clamp(T.x0 - 1 + i % HX, p.n[0], p.per[0]);
+      const int gy = wrap_or_clamp(T.y0 - 1 + (i / HX) % HY, p.n[1], p.per[1]);
+      const int gz = (D == 3) ? wrap_or_clamp(T.z0 - 1 + i / (HX * HY), p.n[2], p.per[2]) : 0;
+      const int64_t o = (int64_t)gz * p.sz + (int64_t)gy * p.sy + gx;
+#pragma unroll
+      for (int q = 0; q < N; ++q) pre[r][q] = phi[q * p.cells + o];
+    }
   }
-  R pre[PER][N];
-  auto fetch = [&](int zz) {
-    const int64_t zo = (D == 3) ? (int64_t)wrap_or_clamp(zz, p.n[2], p.per[2]) * p.sz : 0;
 #pragma unroll
-    for (int r = 0; r < PER; ++r)
-      if (tid + r * NT < HC)
+  for (int i = 0; i < NC; ++i) m[i] = own ? mu[i * p.cells + P] : R(0);
 #pragma unroll
-        for (int q = 0; q < N; ++q) pre[r][q] = phi[q * p.cells + zo + hoff[r]];
-  };
-  auto store = [&](int slot) {
+  for (int r = 0; r < PER; ++r)
+    if (tid + r * NT < HC)
 #pragma unroll
-    for (int r = 0; r < PER; ++r)
-      if (tid + r * NT < HC)
-#pragma unroll
-        for (int q = 0; q < N; ++q) ring[slot][q][tid + r * NT] = pre[r][q];
-  };
-  auto update = [&](int z, int sm, int s0, int sp) {
-    if (!own) return;
-    int xq = x, yq = y;  // opaque per plane: addresses are formed anew, not carried along z
-    asm volatile("" : "+v"(xq), "+v"(yq));
+      for (int q = 0; q < N; ++q) sh[q][tid + r * NT] = pre[r][q];
+  block_sync_lds();
+  int all_bulk = 1;
+  if (own) {
+    const int c0 = ((D == 3 ? lz + 1 : 0) * HY + ly + 1) * HX + lx + 1;
     R v[N][3][3][3];
-    const int sl[3] = {sm, s0, sp};
 #pragma unroll
     for (int dz = (D == 3 ? -1 : 0); dz <= (D == 3 ? 1 : 0); ++dz)
 #pragma unroll
@@ -584,52 +589,18 @@ __device__ __forceinline__ void phi_walk(const KP<R>& p, const R* __restrict__ p
         for (int dx = -1; dx <= 1; ++dx) {
           if (dx != 0 && dy != 0 && dz != 0) continue;
 #pragma unroll
-          for (int q = 0; q < N; ++q) v[q][dz + 1][dy + 1][dx + 1] = ring[sl[dz + 1]][q][c0 + dy * HX + dx];
+          for (int q = 0; q < N; ++q) v[q][dz + 1][dy + 1][dx + 1] = sh[q][c0 + (dz * HY + dy) * HX + dx];
         }
     R res[N];
-    uint8_t* ap = nullptr;
-    if constexpr (ACT) ap = act_out + (int64_t)z * p.sz + (uint32_t)(yq * (int)p.sy + xq);  // a plane < 2^32 cells
-    const bool bulk = phi_from_stencil<D, N, NC, R>(p, v, mu, xq, yq, z, tshift, res, ap);
-    all_bulk &= bulk ? 1 : 0;
-    if (was_bulk && bulk) return;
-    const int64_t P = (int64_t)z * p.sz + (int64_t)yq * p.sy + xq;
+    const bool bulk =
+        phi_from_stencil<D, N, NC, R, ISO>(p, v, m, x, y, z, tshift, res, act_out ? act_out + P : nullptr);
+    all_bulk = bulk ? 1 : 0;
+    if (!(was_bulk && bulk))
 #pragma unroll
-    for (int q = 0; q < N; ++q) __builtin_nontemporal_store(res[q], &phi_out[q * p.cells + P]);
-  };
-  auto record_bulk = [&]() {
-    const int b = __syncthreads_and(all_bulk);
-    if (bulk_out && tid == 0) bulk_out[T.lb] = (uint8_t)b;
-  };
-
-  if (D == 2) {
-    fetch(0);
-    store(0);
-    __syncthreads();
-    update(0, 0, 0, 0);
-    record_bulk();
-    return;
+      for (int q = 0; q < N; ++q) phi_out[q * p.cells + P] = res[q];
   }
-  // ring slot of plane zz: (zz - z0 + 1) mod 4
-  fetch(T.z0 - 1);
-  store(0);
-  fetch(T.z0);
-  store(1);
-  fetch(T.z0 + 1);
-  store(2);
-  fetch(T.z0 + 2);
-  __syncthreads();
-  for (int z = T.z0; z < T.z1; ++z) {
-    const int k = z - T.z0;
-    update(z, k & 3, (k + 1) & 3, (k + 2) & 3);
-    if (z + 1 < T.z1) {
-      // plane z+2 goes to the slot of plane z-2, which every thread finished
-      // reading before the previous barrier
-      store((k + 3) & 3);
-      if (z + 2 < T.z1) fetch(z + 3);
-      __syncthreads();
-    }
-  }
-  record_bulk();
+  const int b = __syncthreads_and(all_bulk);
+  if (bulk_out && tid == 0) bulk_out[T.lb] = (uint8_t)b;
 }
 
 // Bulk flag of the tile at neighbour offset i (0..26: dx, dy, dz in -1..1,
@@ -654,58 +625,25 @@ __device__ __forceinline__ int bulk_flag_at(const uint8_t* __restrict__ bulk, un
   return bulk[t3[0] + nt[0] * (t3[1] + nt[1] * t3[2])];
 }
 
-template <int D, int N, int NC, class R, int TX, int TY, bool ACT>
-__global__ void __launch_bounds__(TX * TY)
-k_phi_z(KP<R> p, const R* __restrict__ phi, const R* __restrict__ mu, R* __restrict__ phi_out,
-        const uint8_t* __restrict__ bulk_in, uint8_t* __restrict__ bulk_out, uint8_t* __restrict__ act_out,
-        R tshift, int tiles_x, int tiles_y, int zc) {
-  constexpr int HX = TX + 2, HY = TY + 2, HC = HX * HY;
-  constexpr int NS = (D == 3) ? 4 : 1;
-  __shared__ R ring[NS][N][HC];
-  const Tile T = tile_of(tiles_x, tiles_y, TX, TY, zc, p.n[2], D);
-  const int tid = threadIdx.x;
-  // Bulk history (both null when phi_out is not the buffer that held phi^{n-1}),
-  // one flag per block (logical tile index): bulk_in[block] says every cell of
-  // this block's tile and planes was bulk in the step that produced phi^n from
-  // phi^{n-1}, so phi_out, which still holds phi^{n-1}, already holds phi^n
-  // there, and a cell that is bulk again (phi^{n+1} = phi^n) need not be
-  // stored.  bulk_out[block] records the same for this step.
-  // ACT (recomputation for the adjoint): act_out receives each cell's active
-  // set of phases, which the reverse of the step reads instead of phi^n's
-  // stencil (an instance of its own keeps the registers of the common case)
-  if (bulk_in && (D == 3 || p.live > ((int64_t)1 << 18))) {
-    // If this block and every block its stencils reach (the 26 around it, none
-    // beyond a wall) were bulk in that step, phi^n = phi^{n-1} on every stencil
-    // the block evaluates, so each cell has its previous active set and is
-    // bulk again: phi_out already holds phi^{n+1} = phi^n, nothing to do.  (On
-    // small 2D grids, whose one-plane blocks make a launch of a few
-    // microseconds, the flag loads cost what they save.)
-    int ok = 1;
-    if (tid < 27) {
-      const int nt[3] = {tiles_x, tiles_y, (int)(gridDim.x / (unsigned)(tiles_x * tiles_y))};
-      ok = bulk_flag_at(bulk_in, T.lb, tid, nt, p.per, D);
-    }
-    if (__syncthreads_and(ok)) {
-      if (bulk_out && tid == 0) bulk_out[T.lb] = 1;
-      return;
-    }
-  }
-  phi_walk<D, N, NC, R, TX, TY, ACT>(p, phi, mu, phi_out, bulk_in && bulk_in[T.lb], bulk_out, act_out, tshift, T,
-                                     ring);
-}
-
-// ---------------------------------------------------------------------------
-// Phase field over a list of tiles (3D grids with the bulk history on).  On a
-// grid that is mostly bulk nearly every block of a k_phi_z launch finds its
-// neighbourhood bulk and returns, yet the launch still pays the dispatch of
-// all of them.
-// k_phi_todo checks every tile's neighbourhood, one thread per tile, sets the
-// flag of each tile it skips and appends the others to a list; k_phi_zl,
+// Bulk history (both null when phi_out is not the buffer that held phi^{n-1}),
+// one flag per tile: bulk_in[tile] says every cell of the tile was bulk in the
+// step that produced phi^n from phi^{n-1}, so phi_out, which still holds
+// phi^{n-1}, already holds phi^n there, and a cell that is bulk again (phi^{n+1}
+// = phi^n) need not be stored.  bulk_out[tile] records the same for this step.
+// If a tile and every tile its stencils reach (the 26 around it, none beyond a
+// wall) were bulk in that step, phi^n = phi^{n-1} on every stencil the tile
+// evaluates, so each cell has its previous active set and is bulk again:
+// phi_out already holds phi^{n+1} = phi^n, nothing to do.
+//
+// On a 3D grid that is mostly bulk nearly every tile of a launch is of that
+// kind, and dispatching a block for each costs more than the others' work.
+// There k_phi_todo checks every tile's neighbourhood, one thread per tile, sets
+// the flag of each tile it skips and appends the others to a list, and k_phi,
 // launched with a grid of resident blocks, walks the listed tiles.  Each XCD
-// walks a contiguous part of the list (whose waves append in about the order
-// of the tiles), so tiles that are neighbours share its L2 as in k_phi_z.
-// count is the length of the list; it starts at zero, and the step's
-// k_mulbm, which runs after k_phi_zl, clears it for the next step.
+// walks a contiguous part of the list (whose waves append in about the order of
+// the tiles), so tiles that are neighbours share its L2.  count is the length
+// of the list; it starts at zero, and the step's k_mulbm, which runs after
+// k_phi, clears it for the next step.
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ void __launch_bounds__(256)
@@ -734,26 +672,48 @@ k_phi_todo(const uint8_t* __restrict__ bulk_in, uint8_t* __restrict__ bulk_out, 
   if (need && slot < nb) list[slot] = lb;
 }
 
-template <int D, int N, int NC, class R, int TX, int TY>
-__global__ void __launch_bounds__(TX * TY)
-k_phi_zl(KP<R> p, const R* __restrict__ phi, const R* __restrict__ mu, R* __restrict__ phi_out,
-         const uint8_t* __restrict__ bulk_in, uint8_t* __restrict__ bulk_out, const unsigned* __restrict__ list,
-         const unsigned* __restrict__ count, R tshift, int tiles_x, int tiles_y, int zc) {
-  constexpr int HX = TX + 2, HY = TY + 2, HC = HX * HY;
-  __shared__ R ring[4][N][HC];
-  const unsigned nb = (unsigned)tiles_x * (unsigned)tiles_y * (unsigned)((p.n[2] + zc - 1) / zc);
-  const unsigned cnt = min(*count, nb);
-  // gridDim.x is a multiple of 8: XCD k (blocks b = k mod 8) takes part k of the list
+// list null: every tile, each checked for the skip above where bulk_in is given
+// (not on small 2D grids, where a launch lasts a few microseconds and the flag
+// loads cost what they save).  One kernel for both: the compiler's choice of
+// fused multiply-adds is the same, so a run resumed from a checkpoint, whose
+// first step has no history, continues bit for bit.  gridDim.x is a multiple
+// of 8: XCD k (blocks b = k mod 8) takes part k of the tiles.
+template <int D, int N, int NC, class R, int TX, int TY, int TZ, bool ISO>
+__global__ void __launch_bounds__(TX * TY * TZ)
+k_phi(KP<R> p, const R* __restrict__ phi, const R* __restrict__ mu, R* __restrict__ phi_out,
+      const uint8_t* __restrict__ bulk_in, uint8_t* __restrict__ bulk_out, uint8_t* __restrict__ act_out,
+      const unsigned* __restrict__ list, const unsigned* __restrict__ count, R tshift, int tiles_x, int tiles_y,
+      int tiles_z) {
+  __shared__ R sh[N][PhiTile<D, TX, TY, TZ>::HC];
+  const unsigned nb = (unsigned)tiles_x * (unsigned)tiles_y * (unsigned)tiles_z;
+  const unsigned cnt = list ? min(*count, nb) : nb;
+  const bool check = !list && bulk_in && (D == 3 || p.live > ((int64_t)1 << 18));
   const unsigned g8 = gridDim.x / 8u, k = blockIdx.x % 8u;
   const unsigned hi = (unsigned)(((unsigned long long)cnt * (k + 1u)) / 8u);
   for (unsigned w = (unsigned)(((unsigned long long)cnt * k) / 8u) + blockIdx.x / 8u; w < hi; w += g8) {
-    const unsigned lb = list[w];
-    // entries are tile indices (the list starts zeroed); the check keeps a
-    // count that disagrees with the list inside the grid (uniform per block)
+    const unsigned lb = list ? list[w] : w;
+    // listed entries are tile indices (the list starts zeroed); the test keeps
+    // a count that disagrees with the list inside the grid (uniform per block)
     if (lb >= nb) continue;
-    const Tile T = tile_at(lb, tiles_x, tiles_y, TX, TY, zc, p.n[2], D);
-    phi_walk<D, N, NC, R, TX, TY, false>(p, phi, mu, phi_out, bulk_in[T.lb] != 0, bulk_out, nullptr, tshift, T,
-                                         ring);
+    // the parameter block (first kernel argument), read anew for every tile:
+    // carried through the loop it took 20 to 50 vector registers
+    using KPc = const __attribute__((address_space(4))) KP<R>*;
+    KPc kp = (KPc)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(kp));
+    const KP<R>& q = *(const KP<R>*)kp;
+    if (check) {
+      int ok = 1;
+      if (threadIdx.x < 27) {
+        const int nt[3] = {tiles_x, tiles_y, tiles_z};
+        ok = bulk_flag_at(bulk_in, lb, (int)threadIdx.x, nt, q.per, D);
+      }
+      if (__syncthreads_and(ok)) {
+        if (bulk_out && threadIdx.x == 0) bulk_out[lb] = 1;
+        continue;
+      }
+    }
+    phi_tile<D, N, NC, R, TX, TY, TZ, ISO>(q, phi, mu, phi_out, bulk_in && bulk_in[lb], bulk_out, act_out, tshift,
+                                           tile_at<TX, TY, TZ>(lb, tiles_x, tiles_y), sh);
   }
 }
 
@@ -823,7 +783,7 @@ k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R
     z0 = (int)z * TZ;
   }
   const int tid = threadIdx.x;
-  // the step's k_phi_zl, which read the list length, has finished: clear it
+  // the step's k_phi, which read the list length, has finished: clear it
   // for the next step's k_phi_todo
   if (todo_count && blockIdx.x == 0 && tid == 0) atomicExch(todo_count, 0u);
   const int lx = tid % TX;
@@ -1312,9 +1272,9 @@ template <int TY>
 __global__ void __launch_bounds__(64 * TY) k_probe_pull19_z(const float* __restrict__ in, float* __restrict__ out,
                                                             int n0, int n1, int n2, int zc) {
   const int64_t cells = (int64_t)n0 * n1 * n2;
-  const Tile T = tile_of(n0 / 64, n1 / TY, 64, TY, zc, n2, 3);
+  const Tile T = tile_at<64, TY, 1>(xcd_block(), n0 / 64, n1 / TY);
   const int x = T.x0 + (int)threadIdx.x % 64, y = T.y0 + (int)threadIdx.x / 64;
-  for (int z = T.z0; z < T.z1; ++z) probe_pull_cell(in, out, x, y, z, n0, n1, n2, cells);
+  for (int z = T.z0 * zc; z < min((T.z0 + 1) * zc, n2); ++z) probe_pull_cell(in, out, x, y, z, n0, n1, n2, cells);
 }
 
 // health: NaN/Inf in phi or mu, or rho <= 0, records the smallest step seen

@@ -62,11 +62,11 @@ struct gpf_ctx {
   DevBuf redout;    // final reduction values
   DevBuf badstep;   // health: smallest failing step
   DevBuf frontbuf;  // moving frame: front position found on the device
-  // per k_phi_z block: the step that produced state buffer i left phi
+  // per k_phi block: the step that produced state buffer i left phi
   // unchanged on the block's cells (valid while bulk_ok[i])
   DevBuf bulkf[2];
   bool bulk_ok[2] = {false, false};
-  // tiles that k_phi_zl walks (3D grids, bulk history on) and their
+  // tiles that k_phi walks (3D grids, bulk history on) and their
   // number, which starts at zero; zl_grid: its blocks per launch, the
   // device's resident blocks of it
   DevBuf tlist, tcount;
@@ -223,6 +223,10 @@ gpf::KP<R> make_kp(const gpf_ctx* c) {
       k.mT[a][i] = (a < c->N && i < c->nc) ? (R)p.mT[a][i] : R(0);
       if (k.mT[a][i] != R(0)) k.tdep = 1;
     }
+  k.aniso = 0;
+  for (int a = 0; a < c->N; ++a)
+    for (int b = 0; b < c->N; ++b)
+      if (a != b && k.delta[a][b] != R(0)) k.aniso = 1;
   k.dtdev = (R)(p.G != 0.0 ? -p.G * p.V : 0.0);
   k.T_E = (R)p.T_E;
   k.tau_lb = (R)p.tau_lb;
@@ -315,33 +319,26 @@ inline unsigned adj_blocks(const int64_t (&n)[3]) {
   return 8u * lin_blocks(n[0] * ((n[1] + 7) / 8) * n[2], gpf::ADJ_BLOCK);
 }
 
-// launch shape of the phase field: 64 x GPF_TILE_Y tiles, each block walks
-// GPF_ZCHUNK_PHI planes (best measured of 64 x {2, 4, 8} x {4, 8, 16, 32})
-#define GPF_TILE_Y 4
-#define GPF_ZCHUNK_PHI2 4
-#define GPF_ZCHUNK_PHI 16
-constexpr int kTileY = GPF_TILE_Y;
+// tiles of the phase field in 3D (64 x 4 cells in 2D), one cell per thread
+// (measured, see the kernel)
+#define GPF_PHI_TX 32
+#define GPF_PHI_TY 4
+#define GPF_PHI_TZ 2
 constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
 // tiles of k_mulbm in 3D (64 x 4 cells in 2D), one cell per thread (measured,
 // see the kernel)
-#ifndef GPF_MU_TX
 #define GPF_MU_TX 64
 #define GPF_MU_TY 4
 #define GPF_MU_TZ 2
-#endif
-// planes that a block of the bandwidth probe's z-marched pull walks
-constexpr int kProbeZ = 4;
-// planes per phase-field block: a two-phase step spends its phase-field time
-// in the few tiles near the interface (3D: the tiles k_phi_zl walks), whose
-// plane walk a shorter chunk shortens; three and four phases have interface
-// throughout the solid, where a longer chunk re-reads fewer halo planes
-constexpr int zchunk_phi(int N) { return N == 2 ? GPF_ZCHUNK_PHI2 : GPF_ZCHUNK_PHI; }
-// blocks of one k_phi_z launch (64 x kTileY tiles, zchunk_phi(N) planes each in 3D)
+// tile rows and planes of a block of the bandwidth probe's z-marched pull
+constexpr int kProbeY = 4, kProbeZ = 4;
+constexpr int phi_tx(int dim) { return dim == 3 ? GPF_PHI_TX : 64; }
+constexpr int phi_ty(int dim) { return dim == 3 ? GPF_PHI_TY : 4; }
+constexpr int phi_tz(int dim) { return dim == 3 ? GPF_PHI_TZ : 1; }
+// tiles of the phase field
 inline int64_t phi_blocks(const gpf_ctx* c) {
-  const int64_t tx = (c->n[0] + 63) / 64, ty = (c->n[1] + kTileY - 1) / kTileY;
-  const int zc = zchunk_phi(c->N);
-  const int64_t tz = (c->dim == 3) ? (c->n[2] + zc - 1) / zc : 1;
-  return tx * ty * tz;
+  const int64_t tx = phi_tx(c->dim), ty = phi_ty(c->dim), tz = phi_tz(c->dim);
+  return ((c->n[0] + tx - 1) / tx) * ((c->n[1] + ty - 1) / ty) * ((c->n[2] + tz - 1) / tz);
 }
 
 template <int D, int Q, int N, int NC, class R>
@@ -367,42 +364,37 @@ struct Impl {
     return SP{P(c->phi[s]), P(c->mu[s]), P(c->u[s]), P(c->f[s]), nullptr};
   }
 
-  // bulk_in / bulk_out: k_phi_z's bulk history, only for a step from one
+  // bulk_in / bulk_out: k_phi's bulk history, only for a step from one
   // state buffer into the other (null elsewhere)
   static void launch_step(gpf_ctx* c, const gpf::KP<R>& k, const SP& in, const SP& out, R ts,
                           hipStream_t st, hipEvent_t* ev, const uint8_t* bulk_in = nullptr,
                           uint8_t* bulk_out = nullptr, uint8_t* act_out = nullptr) {
-    constexpr int TX = 64, TY = kTileY, ZP = zchunk_phi(N);
+    constexpr int TX = phi_tx(D), TY = phi_ty(D), TZ = phi_tz(D);
     const int tiles_x = (int)((c->n[0] + TX - 1) / TX), tiles_y = (int)((c->n[1] + TY - 1) / TY);
-    auto grid = [&](int zc) {
-      const int tiles_z = (D == 3) ? (int)((c->n[2] + zc - 1) / zc) : 1;
-      return dim3((unsigned)tiles_x * (unsigned)tiles_y * (unsigned)tiles_z);
-    };
-    const dim3 block(TX * TY);
+    const int tiles_z = (int)((c->n[2] + TZ - 1) / TZ);
+    const unsigned nb = (unsigned)tiles_x * (unsigned)tiles_y * (unsigned)tiles_z;
+    const dim3 block(TX * TY * TZ);
     if (ev) (void)hipEventRecord(ev[0], st);
-    unsigned* counts = nullptr;  // set when the listed phase-field kernels ran
+    unsigned *list = nullptr, *counts = nullptr;  // set when the phase field walks a list of tiles
+    unsigned g = (nb + 7u) / 8u * 8u;
     if constexpr (D == 3) {
       if (bulk_in && !act_out && c->zl_grid) {
         // the tiles whose neighbourhood changed, then a walk over them only
-        const int tiles_z = (int)((c->n[2] + ZP - 1) / ZP);
-        const unsigned nb = (unsigned)tiles_x * (unsigned)tiles_y * (unsigned)tiles_z;
-        unsigned* list = static_cast<unsigned*>(c->tlist.ptr);
+        list = static_cast<unsigned*>(c->tlist.ptr);
         counts = static_cast<unsigned*>(c->tcount.ptr);
         hipLaunchKernelGGL((gpf::k_phi_todo<D>), dim3((nb + 255u) / 256u), dim3(256), 0, st, bulk_in, bulk_out, list,
                            counts, tiles_x, tiles_y, tiles_z, k.per[0], k.per[1], k.per[2]);
-        const unsigned g = std::max(8u, std::min(c->zl_grid, (nb + 7u) / 8u * 8u));
-        hipLaunchKernelGGL((gpf::k_phi_zl<D, N, NC, R, TX, TY>), dim3(g), block, 0, st, k, in.phi, in.mu, out.phi,
-                           bulk_in, bulk_out, list, counts, ts, tiles_x, tiles_y, ZP);
+        g = std::max(8u, std::min(c->zl_grid, g));
       }
     }
-    if (!counts) {
-      if (act_out)
-        hipLaunchKernelGGL((gpf::k_phi_z<D, N, NC, R, TX, TY, true>), grid(ZP), block, 0, st, k, in.phi, in.mu,
-                           out.phi, bulk_in, bulk_out, act_out, ts, tiles_x, tiles_y, ZP);
-      else
-        hipLaunchKernelGGL((gpf::k_phi_z<D, N, NC, R, TX, TY, false>), grid(ZP), block, 0, st, k, in.phi, in.mu,
-                           out.phi, bulk_in, bulk_out, act_out, ts, tiles_x, tiles_y, ZP);
-    }
+#define GPF_PHI(ISO)                                                                                               \
+  hipLaunchKernelGGL((gpf::k_phi<D, N, NC, R, TX, TY, TZ, ISO>), dim3(g), block, 0, st, k, in.phi, in.mu, out.phi, \
+                     bulk_in, bulk_out, act_out, list, counts, ts, tiles_x, tiles_y, tiles_z)
+    if (k.aniso)
+      GPF_PHI(false);
+    else
+      GPF_PHI(true);
+#undef GPF_PHI
     if (ev) (void)hipEventRecord(ev[1], st);
     constexpr int MX = D == 3 ? GPF_MU_TX : 64, MY = D == 3 ? GPF_MU_TY : 4, MZ = D == 3 ? GPF_MU_TZ : 1;
     const int mtx = (int)((c->n[0] + MX - 1) / MX), mty = (int)((c->n[1] + MY - 1) / MY);
@@ -410,7 +402,7 @@ struct Impl {
     const dim3 mgrid((unsigned)mtx * (unsigned)mty * (unsigned)mtz);
 #define GPF_MULBM(SH, MT)                                                                                        \
   hipLaunchKernelGGL((gpf::k_mulbm<D, Q, N, NC, R, MX, MY, MZ, SH, MT>), mgrid, dim3(MX * MY * MZ), 0, st, k, in.phi, \
-                     out.phi, in.mu, in.u, in.f, out.mu, out.u, out.f, out.dr, bulk_out, ilog2(TX), ilog2(TY), ilog2(ZP), ts, mtx, mty,    \
+                     out.phi, in.mu, in.u, in.f, out.mu, out.u, out.f, out.dr, bulk_out, ilog2(TX), ilog2(TY), ilog2(TZ), ts, mtx, mty,    \
                      (mty + 7) / 8, counts)
     if (k.shrink) {
       if (k.tdep)
@@ -522,10 +514,11 @@ struct Impl {
   static int step(gpf_ctx* c, int64_t nsteps, double* kernel_ms, int nk) {
     gpf::KP<R> k = make_kp<R>(c);
     if constexpr (D == 3) {
-      if (!c->zl_grid) {  // once, outside any capture: k_phi_zl's grid (a multiple of 8)
+      if (!c->zl_grid) {  // once, outside any capture: k_phi's grid (a multiple of 8)
         int per_cu = 0, cus = 0;
         HIP_OR_FAIL(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                           &per_cu, gpf::k_phi_zl<D, N, NC, R, 64, kTileY>, 64 * kTileY, 0));
+                           &per_cu, gpf::k_phi<D, N, NC, R, phi_tx(D), phi_ty(D), phi_tz(D), false>,
+                           phi_tx(D) * phi_ty(D) * phi_tz(D), 0));
         HIP_OR_FAIL(c, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
         c->zl_grid = std::max(8u, (unsigned)(std::max(per_cu, 1) * cus) / 8u * 8u);
       }
@@ -1493,7 +1486,7 @@ int gpf_reduce_noalloc(gpf_ctx* c, int32_t which, double* dev_out) {
 int gpf_bandwidth_probe(int32_t pattern, const void* dev_in, void* dev_out, const int64_t* n, int32_t reps,
                         void* stream, double* gbps) {
   if (!dev_in || !dev_out || !n || !gbps || reps < 1 || pattern < 0 || pattern > 2) return GPF_ERR_ARG;
-  if (n[0] < 64 || n[0] % 64 || n[1] < kTileY || n[1] % kTileY || n[2] < kProbeZ || n[2] % kProbeZ ||
+  if (n[0] < 64 || n[0] % 64 || n[1] < kProbeY || n[1] % kProbeY || n[2] < kProbeZ || n[2] % kProbeZ ||
       n[0] > (1 << 20) || n[1] > (1 << 20) || n[2] > 65535)
     return GPF_ERR_ARG;
   const int64_t cells = n[0] * n[1] * n[2];
@@ -1502,14 +1495,14 @@ int gpf_bandwidth_probe(int32_t pattern, const void* dev_in, void* dev_out, cons
   float* out = static_cast<float*>(dev_out);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int n0 = (int)n[0], n1 = (int)n[1], n2 = (int)n[2];
-  const unsigned zblocks = (unsigned)((n0 / 64) * (n1 / kTileY) * (n2 / kProbeZ));
+  const unsigned zblocks = (unsigned)((n0 / 64) * (n1 / kProbeY) * (n2 / kProbeZ));
   auto launch = [&]() {
     if (pattern == 0)
       hipLaunchKernelGGL(gpf::k_probe_copy19, dim3(lin_blocks(cells, 256)), dim3(256), 0, st, in, out, cells);
     else if (pattern == 1)
       hipLaunchKernelGGL(gpf::k_probe_pull19, dim3(lin_blocks(cells, 256)), dim3(256), 0, st, in, out, n0, n1, n2);
     else
-      hipLaunchKernelGGL((gpf::k_probe_pull19_z<kTileY>), dim3(zblocks), dim3(64 * kTileY), 0, st, in, out, n0, n1,
+      hipLaunchKernelGGL((gpf::k_probe_pull19_z<kProbeY>), dim3(zblocks), dim3(64 * kProbeY), 0, st, in, out, n0, n1,
                          n2, kProbeZ);
   };
   hipEvent_t e0 = nullptr, e1 = nullptr;
