@@ -800,14 +800,20 @@ struct Impl {
                          x0.mu, x1.mu, x0.u, P(c->t_w), P(li.phi), P(c->t_phil), P(lo.phi),
                          P(lo.mu), P(lo.u), P(c->t_rbar), a.rflag, rowflags(c, n), act, (R)tshift(c, n),
                          a.part + a.pstride);
+    if (!k.aniso) return;  // adj_phi2 runs k_adj_phi_iso
     const int split = small_grid(c) ? 1 : 0;
     hipLaunchKernelGGL((gpf::k_adj_vjp<D, N, NC, R>), dim3(a.g.x * (split ? D + 1 : 1)), a.b, 0, c->stream, k,
                        x0.phi, P(c->t_rbar), a.rflag, P(c->t_fbuf), a.fflag, P(c->t_cbuf), a.part + 2 * a.pstride,
                        rowflags(c, n), split);
   }
-  // gather of step n into lo.phi alone
-  static void adj_phi2(gpf_ctx* c, const gpf::KP<R>& k, int64_t n, StateBuf& lo) {
+  // gather of step n (states x0 = X^n) into lo.phi alone
+  static void adj_phi2(gpf_ctx* c, const gpf::KP<R>& k, int64_t n, const SP& x0, StateBuf& lo) {
     const AdjLaunch a = adj_launch(c);
+    if (!k.aniso) {
+      hipLaunchKernelGGL((gpf::k_adj_phi_iso<D, N, R>), a.g, a.b, 0, c->stream, k, x0.phi, P(c->t_rbar), a.rflag,
+                         P(lo.phi), rowflags(c, n), rowflags(c, n + 1));
+      return;
+    }
     hipLaunchKernelGGL((gpf::k_adj_phi2<D, N, NC, R>), a.g, a.b, 0, c->stream, k, a.rflag, P(c->t_fbuf), a.fflag,
                        P(c->t_cbuf), P(lo.phi), rowflags(c, n), rowflags(c, n + 1));
   }
@@ -968,7 +974,7 @@ struct Impl {
     // two grids side by side (one kernel boundary less per step); on larger
     // ones the combined kernel's registers (121, against 67 for the gather
     // alone) cost more than the boundary.
-    const bool fuse = small_grid(c);
+    const bool fuse = small_grid(c) && k.aniso;
     for (int64_t j = 0; j < seg_len(nseg - 1) - 1; ++j) recompute_step(0, nseg - 1, j, c->stream);
     adj_lbm(c, k, c->rec_start + total - 1, state(total - 1), state(total), *li, *lo);
     int64_t nrec = 0, jr = 0;
@@ -1006,11 +1012,11 @@ struct Impl {
         if (fuse) {
           adj_phi2_lbm(c, k, c->rec_start + m, state(m - 1), state(m), *lo, *li);
         } else {
-          adj_phi2(c, k, c->rec_start + m, *lo);
+          adj_phi2(c, k, c->rec_start + m, state(m), *lo);
           adj_lbm(c, k, c->rec_start + m - 1, state(m - 1), state(m), *lo, *li);
         }
       } else {
-        adj_phi2(c, k, c->rec_start + m, *lo);
+        adj_phi2(c, k, c->rec_start + m, state(m), *lo);
       }
       HIP_OR_FAIL(c, hipGetLastError());
       std::swap(li, lo);
