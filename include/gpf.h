@@ -180,7 +180,8 @@ int gpf_step(gpf_ctx* ctx, int64_t n);
  * each part of the step on the context's stream; kernel_ms[j] receives the
  * summed milliseconds of part j (j = 0: phase field, one kernel, or on 3D
  * grids with the bulk history the tile check and the walk of the listed
- * tiles together; 1: chemical potential + LBM), count up to n_kernels.
+ * tiles together; 1: chemical potential + LBM; 2D grids of up to 3 MiB per
+ * component step in one kernel, which is part 1), count up to n_kernels.
  * Synchronises.  For measurement only. */
 int gpf_step_timed(gpf_ctx* ctx, int64_t n, double* kernel_ms, int32_t n_kernels);
 

@@ -502,6 +502,12 @@ __device__ __forceinline__ int wrap_or_clamp(int v, int n, int per) {
   return v >= n ? (per ? min(v - n, n - 1) : n - 1) : v;
 }
 
+// the same for v >= -2 and up to n + 1, two cells past the grid
+__device__ __forceinline__ int wrap2_or_clamp(int v, int n, int per) {
+  if (v < 0) return per ? (v + n < 0 ? v + 2 * n : v + n) : 0;
+  return v >= n ? (per ? min(v - n < n ? v - n : v - 2 * n, n - 1) : n - 1) : v;
+}
+
 // Tile of a phase-field block.  Work-groups are dealt to the 8 XCDs
 // round-robin; renumbering gives each XCD a contiguous range of tiles, so
 // tiles that are neighbours in y and z share its L2.
@@ -672,9 +678,8 @@ k_phi_todo(const uint8_t* __restrict__ bulk_in, uint8_t* __restrict__ bulk_out, 
   if (need && slot < nb) list[slot] = lb;
 }
 
-// list null: every tile, each checked for the skip above where bulk_in is given
-// (not on small 2D grids, where a launch lasts a few microseconds and the flag
-// loads cost what they save).  One kernel for both: the compiler's choice of
+// list null: every tile, each checked for the skip above where bulk_in is given.
+// One kernel for both: the compiler's choice of
 // fused multiply-adds is the same, so a run resumed from a checkpoint, whose
 // first step has no history, continues bit for bit.  gridDim.x is a multiple
 // of 8: XCD k (blocks b = k mod 8) takes part k of the tiles.
@@ -687,7 +692,7 @@ k_phi(KP<R> p, const R* __restrict__ phi, const R* __restrict__ mu, R* __restric
   __shared__ R sh[N][PhiTile<D, TX, TY, TZ>::HC];
   const unsigned nb = (unsigned)tiles_x * (unsigned)tiles_y * (unsigned)tiles_z;
   const unsigned cnt = list ? min(*count, nb) : nb;
-  const bool check = !list && bulk_in && (D == 3 || p.live > ((int64_t)1 << 18));
+  const bool check = !list && bulk_in;
   const unsigned g8 = gridDim.x / 8u, k = blockIdx.x % 8u;
   const unsigned hi = (unsigned)(((unsigned long long)cnt * (k + 1u)) / 8u);
   for (unsigned w = (unsigned)(((unsigned long long)cnt * k) / 8u) + blockIdx.x / 8u; w < hi; w += g8) {
@@ -753,6 +758,85 @@ template <int D, int TX, int TY, int TZ> struct MuTile {
   static constexpr int base(int a) { return a == 2 ? 0 : (a == 1 ? 2 * HZ : 2 * (HZ + HY)); }
   static constexpr int face(int a) { return a == 2 ? HZ : (a == 1 ? HY : HX); }
 };
+
+// mu^{n+1} (mn) of a thread's cell from the tile's shared slots: sv holds mu^n,
+// c*, d (and with SH phi^{n+1}) per slot, su U_a of the tile's cells axis after
+// axis, then of the halo of the faces along a.  pos, lpos: the cell in the grid
+// and in the tile (slot tid).  g1 (SH): the differences of phi^{n+1} across the
+// cell that its normals are taken from.
+template <int D, int N, int NC, class R, int TX, int TY, int TZ, bool SH, bool MT, int NV, int NS, int NU>
+__device__ __forceinline__ void mu_update(const KP<R>& p, const int (&pos)[3], const int (&lpos)[3], int tid,
+                                          const R (&sv)[NV][NS], const R (&su)[NU], const R (&ph0)[N],
+                                          const R (&ph1)[N], const R (&m0)[NC], const R (&uc)[D], const R (&cs0)[NC],
+                                          const R (&d0)[NC], R td0, R (&mn)[NC], R (&g1)[SH ? N : 1][D]) {
+  using M = MuTile<D, TX, TY, TZ>;
+  constexpr int T = M::T;
+  // divergence of the face fluxes (diffusion and advection)
+  R divJ[NC];
+#pragma unroll
+  for (int i = 0; i < NC; ++i) divJ[i] = R(0);
+  const int text[3] = {TX, TY, TZ}, tstr[3] = {1, TX, TX * TY};
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    // index of the cell's column within a face of the tile across axis a
+    const int fi = a == 0 ? lpos[2] * TY + lpos[1] : (a == 1 ? lpos[2] * TX + lpos[0] : lpos[1] * TX + lpos[0]);
+#pragma unroll
+    for (int si = 0; si < 2; ++si) {
+      const int s = si ? 1 : -1;
+      const bool inner = si ? lpos[a] + 1 < text[a] : lpos[a] > 0;
+      const int h = M::base(a) + si * M::face(a) + fi;
+      const int slot = inner ? tid + s * tstr[a] : T + h;
+      if constexpr (SH) {
+        // (the slot beyond a wall holds the cell at the wall itself)
+#pragma unroll
+        for (int b = 0; b < N; ++b) g1[b][a] = si ? sv[3 * NC + b][slot] - g1[b][a] : sv[3 * NC + b][slot];
+      }
+      const bool wall = !p.per[a] && ((s < 0 && pos[a] == 0) || (s > 0 && pos[a] == p.n[a] - 1));
+      if (wall) continue;
+      const R uf = R(0.5) * (uc[a] + su[inner ? a * T + slot : D * T + h]) * p.conv;
+      R dm[NC];
+#pragma unroll
+      for (int k = 0; k < NC; ++k) dm[k] = R(s) * (sv[k][slot] - m0[k]) * p.idx;
+#pragma unroll
+      for (int i = 0; i < NC; ++i) {
+        const R df = -R(0.5) * (d0[i] + sv[2 * NC + i][slot]);
+        R JD = R(0);
+#pragma unroll
+        for (int k = 0; k < NC; ++k) JD += df * p.chi[i][k] * dm[k];
+        const R JA = uf * R(0.5) * (cs0[i] + sv[NC + i][slot]);
+        divJ[i] += R(s) * (JD + JA) * p.idx;
+      }
+    }
+  }
+  R h0[N], h1[N];
+  interp_h<N, R>(ph0, h0);
+  interp_h<N, R>(ph1, h1);
+  R Dl[NC];
+#pragma unroll
+  for (int i = 0; i < NC; ++i) Dl[i] = -p.dt * divJ[i];
+  // dh/dt source with C at T^n, and the dT/dt term of Eq. (conc) over the
+  // step, -sum_b h_b^{n+1} (C^b(mu^n, T^{n+1}) - C^b(mu^n, T^n)) = -sum_b
+  // h_b^{n+1} mT[b] (T^{n+1} - T^n)
+  R sh = R(0);
+#pragma unroll
+  for (int b = 0; b < N; ++b) {
+    sh += h1[b];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      Dl[i] -= comp_of<N, NC, R, MT>(p, b, i, m0, td0) * (h1[b] - h0[b]);
+      if constexpr (MT) Dl[i] -= h1[b] * (p.mT[b][i] * p.dtdev);
+    }
+  }
+  if (NC == 1) {
+    mn[0] = m0[0] + Dl[0] / (sh * p.chi[0][0]);
+  } else {
+    const R a11 = sh * p.chi[0][0], a12 = sh * p.chi[0][1];
+    const R a21 = sh * p.chi[1][0], a22 = sh * p.chi[1][NC - 1];
+    const R det = a11 * a22 - a12 * a21;
+    mn[0] = m0[0] + (a22 * Dl[0] - a12 * Dl[NC - 1]) / det;
+    mn[NC - 1] = m0[NC - 1] + (-a21 * Dl[0] + a11 * Dl[NC - 1]) / det;
+  }
+}
 
 template <int D, int Q, int N, int NC, class R, int TX, int TY, int TZ, bool SH, bool MT>
 __global__ void __launch_bounds__(TX * TY * TZ)
@@ -861,7 +945,6 @@ k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R
 #pragma unroll
     for (int q = 0; q < N; ++q) ph0[q] = *lane_at(phi0, q * p.cells + cu, cl);
   }
-  const int pos[3] = {x, y, z};
   const int pa = p.pull_axis;
   const R td0 = MT ? tdev_at(p, pa == 0 ? xw : (pa == 1 ? yw : zw), tshift) : R(0);
   R cs0[NC], d0[NC];
@@ -898,79 +981,154 @@ k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R
   block_sync_lds();
   if (!own) return;
 
-  // divergence of the face fluxes (diffusion and advection)
-  R divJ[NC];
-#pragma unroll
-  for (int i = 0; i < NC; ++i) divJ[i] = R(0);
-  R g1[SH ? N : 1][D];
-  const int lpos[3] = {lx, ly, lz}, text[3] = {TX, TY, TZ}, tstr[3] = {1, TX, TX * TY};
-#pragma unroll
-  for (int a = 0; a < D; ++a) {
-    // index of the cell's column within a face of the tile across axis a
-    const int fi = a == 0 ? lz * TY + ly : (a == 1 ? lz * TX + lx : ly * TX + lx);
-#pragma unroll
-    for (int si = 0; si < 2; ++si) {
-      const int s = si ? 1 : -1;
-      const bool inner = si ? lpos[a] + 1 < text[a] : lpos[a] > 0;
-      const int h = M::base(a) + si * M::face(a) + fi;
-      const int slot = inner ? tid + s * tstr[a] : T + h;
-      if constexpr (SH) {
-        // (the slot beyond a wall holds the cell at the wall itself)
-#pragma unroll
-        for (int b = 0; b < N; ++b) g1[b][a] = si ? sv[3 * NC + b][slot] - g1[b][a] : sv[3 * NC + b][slot];
-      }
-      const bool wall = !p.per[a] && ((s < 0 && pos[a] == 0) || (s > 0 && pos[a] == p.n[a] - 1));
-      if (wall) continue;
-      const R uf = R(0.5) * (uc[a] + su[inner ? a * T + slot : D * T + h]) * p.conv;
-      R dm[NC];
-#pragma unroll
-      for (int k = 0; k < NC; ++k) dm[k] = R(s) * (sv[k][slot] - m0[k]) * p.idx;
-#pragma unroll
-      for (int i = 0; i < NC; ++i) {
-        const R df = -R(0.5) * (d0[i] + sv[2 * NC + i][slot]);
-        R JD = R(0);
-#pragma unroll
-        for (int k = 0; k < NC; ++k) JD += df * p.chi[i][k] * dm[k];
-        const R JA = uf * R(0.5) * (cs0[i] + sv[NC + i][slot]);
-        divJ[i] += R(s) * (JD + JA) * p.idx;
-      }
-    }
-  }
   if (same0) {
 #pragma unroll
     for (int q = 0; q < N; ++q) ph0[q] = ph1[q];
   }
-  R h0[N], h1[N];
-  interp_h<N, R>(ph0, h0);
-  interp_h<N, R>(ph1, h1);
-  R Dl[NC];
-#pragma unroll
-  for (int i = 0; i < NC; ++i) Dl[i] = -p.dt * divJ[i];
-  // dh/dt source with C at T^n, and the dT/dt term of Eq. (conc) over the
-  // step, -sum_b h_b^{n+1} (C^b(mu^n, T^{n+1}) - C^b(mu^n, T^n)) = -sum_b
-  // h_b^{n+1} mT[b] (T^{n+1} - T^n)
-  R sh = R(0);
-#pragma unroll
-  for (int b = 0; b < N; ++b) {
-    sh += h1[b];
-#pragma unroll
-    for (int i = 0; i < NC; ++i) {
-      Dl[i] -= comp_of<N, NC, R, MT>(p, b, i, m0, td0) * (h1[b] - h0[b]);
-      if constexpr (MT) Dl[i] -= h1[b] * (p.mT[b][i] * p.dtdev);
-    }
-  }
-  R mn[NC];
-  if (NC == 1) {
-    mn[0] = m0[0] + Dl[0] / (sh * p.chi[0][0]);
-  } else {
-    const R a11 = sh * p.chi[0][0], a12 = sh * p.chi[0][1];
-    const R a21 = sh * p.chi[1][0], a22 = sh * p.chi[1][NC - 1];
-    const R det = a11 * a22 - a12 * a21;
-    mn[0] = m0[0] + (a22 * Dl[0] - a12 * Dl[NC - 1]) / det;
-    mn[NC - 1] = m0[NC - 1] + (-a21 * Dl[0] + a11 * Dl[NC - 1]) / det;
-  }
+  R mn[NC], g1[SH ? N : 1][D];
+  const int pos[3] = {x, y, z}, lpos[3] = {lx, ly, lz};
+  mu_update<D, N, NC, R, TX, TY, TZ, SH, MT>(p, pos, lpos, tid, sv, su, ph0, ph1, m0, uc, cs0, d0, td0, mn, g1);
 #pragma unroll
   for (int i = 0; i < NC; ++i) __builtin_nontemporal_store(mn[i], lane_at(mu_out, i * p.cells + cu, cs));
+  collide_cell<D, Q, N, NC, R, SH, MT>(p, cu, cs, f, ph0, ph1, mn, g1, td0, u_out, fout, dr_out);
+}
+
+// ---------------------------------------------------------------------------
+// One step of a 2D grid in one launch.  A block owns TX x TY cells, one per
+// thread, and has a thread more for every cell of the tile's face halo: each
+// computes phi^{n+1} of its cell from phi^n of the tile and two halo cells (in
+// LDS) and from it the face quantities that the tile shares; then the tile's
+// threads update mu and the populations as k_mulbm does.
+// Up to some 10^5 cells a 2D step is bound by latency: the launch (1.5 to 2
+// us), a chain of loads (1.5), the phase field of an interface cell (0.8), the
+// rest (0.8).  One launch for both halves and the halo's phase field on waves
+// of its own shorten that chain; a grid of some 10^5 cells and more gains from
+// reading the phase fields once.  us per step in a run, k_phi and k_mulbm in
+// turn and this kernel: 9.1 and 5.6 (256^2, FP32), 9.7 and 6.0 (128^2, FP64),
+// 13.5 and 8.4 (144 x 700, four phases), 19.7 and 17.0 (1024 x 512, three
+// phases, FP32); but 33.9 and 36 (the same in FP64) and 98 and 109 (2048^2,
+// two phases, FP32), where the halo's share of the work counts and the bulk
+// history spares k_phi most of its tiles.
+// ---------------------------------------------------------------------------
+template <int TX, int TY> struct StepTile {
+  static constexpr int T = TX * TY, H = 2 * (TX + TY), NT = T + (H + 63) / 64 * 64;
+};
+
+template <int Q, int N, int NC, class R, int TX, int TY, bool SH, bool MT>
+__global__ void __launch_bounds__((StepTile<TX, TY>::NT))
+k_step2(KP<R> p, const R* __restrict__ phi0, R* __restrict__ phi1, const R* __restrict__ mu,
+        const R* __restrict__ uold, const R* __restrict__ fin, R* __restrict__ mu_out, R* __restrict__ u_out,
+        R* __restrict__ fout, R* __restrict__ dr_out, uint8_t* __restrict__ act_out, R tshift, int tiles_x) {
+  constexpr int D = 2;
+  using M = MuTile<D, TX, TY, 1>;
+  constexpr bool ROW = TX == 64;
+  constexpr int T = StepTile<TX, TY>::T, H = StepTile<TX, TY>::H, NT = StepTile<TX, TY>::NT;
+  static_assert(T % 64 == 0 && H == M::H, "tile threads fill their waves; slots as in MuTile");
+  constexpr int FX = TX + 4, FY = TY + 4, FC = FX * FY, FP = (FC + NT - 1) / NT;
+  constexpr int NV = 3 * NC + (SH ? N : 0);
+  __shared__ R sp[N][FC];  // phi^n of the tile and two halo cells, walls repeating the last cell
+  __shared__ R sv[NV][T + H];
+  __shared__ R su[D * T + H];
+  const unsigned lb = xcd_block();
+  const int x0 = (int)(lb % (unsigned)tiles_x) * TX, y0 = (int)(lb / (unsigned)tiles_x) * TY;
+  const int tid = threadIdx.x;
+  R fpre[FP][N];
+#pragma unroll
+  for (int r = 0; r < FP; ++r) {
+    const int i = min(tid + r * NT, FC - 1);
+    const int64_t o = (int64_t)wrap2_or_clamp(y0 - 2 + i / FX, p.n[1], p.per[1]) * p.sy +
+                      wrap2_or_clamp(x0 - 2 + i % FX, p.n[0], p.per[0]);
+#pragma unroll
+    for (int q = 0; q < N; ++q) fpre[r][q] = phi0[q * p.cells + o];
+  }
+  // the thread's cell: of the tile (slot tid < T), or of the halo of a face
+  // along axis ha (slot tid = T + j)
+  const bool tile = __builtin_amdgcn_readfirstlane(tid) < T;
+  int lx = tid % TX, ly = tid / TX, ha = 0;
+  if (!tile) {
+    const int j = min(tid - T, H - 1);
+    if (j < 2 * TX) {
+      ha = 1;
+      lx = j % TX;
+      ly = (j >= TX) ? TY : -1;
+    } else {
+      ly = (j - 2 * TX) % TY;
+      lx = (j - 2 * TX >= TY) ? TX : -1;
+    }
+  }
+  const int x = x0 + lx, y = y0 + ly;
+  const int xw = wrap_or_clamp(x, p.n[0], p.per[0]), yw = wrap_or_clamp(y, p.n[1], p.per[1]);
+  // its place in sp: on a periodic axis the cell itself, at a wall the cell it repeats
+  const int c0 = ((p.per[1] ? y : yw) - y0 + 2) * FX + (p.per[0] ? x : xw) - x0 + 2;
+  const int64_t P = (int64_t)yw * p.sy + xw;
+  R m0[NC], uc[D];
+#pragma unroll
+  for (int q = 0; q < NC; ++q) m0[q] = mu[q * p.cells + P];
+  if (tile) {
+#pragma unroll
+    for (int a = 0; a < D; ++a) uc[a] = uold[a * p.cells + P];
+  } else {
+    uc[0] = uold[ha * p.cells + P];
+    uc[1] = R(0);
+  }
+#pragma unroll
+  for (int r = 0; r < FP; ++r)
+    if (tid + r * NT < FC)
+#pragma unroll
+      for (int q = 0; q < N; ++q) sp[q][tid + r * NT] = fpre[r][q];
+  // the padding of a row is computed and stored too, as in k_mulbm
+  const bool own = tile && x < (int)p.sy && y < p.n[1];
+  // (with ROW a wave of the tile shares its row)
+  const PullAt<ROW> px = pull_at<D, ROW, R>(p, xw, ROW ? __builtin_amdgcn_readfirstlane(yw) : yw, 0);
+  R f[Q];
+  if (own) pull_cell<D, Q, ROW, R>(p, fin, px, f);
+  block_sync_lds();
+  R ph0[N], ph1[N];
+  {
+    R v[N][3][3][3];
+#pragma unroll
+    for (int dy = -1; dy <= 1; ++dy)
+#pragma unroll
+      for (int dx = -1; dx <= 1; ++dx)
+#pragma unroll
+        for (int q = 0; q < N; ++q) v[q][1][dy + 1][dx + 1] = sp[q][c0 + dy * FX + dx];
+#pragma unroll
+    for (int q = 0; q < N; ++q) ph0[q] = v[q][1][1][1];
+    uint8_t* act = (act_out && tile && x < p.n[0] && y < p.n[1]) ? act_out + P : nullptr;
+    if (p.aniso)
+      phi_from_stencil<D, N, NC, R, false>(p, v, m0, xw, yw, 0, tshift, ph1, act);
+    else
+      phi_from_stencil<D, N, NC, R, true>(p, v, m0, xw, yw, 0, tshift, ph1, act);
+  }
+  const R td0 = MT ? tdev_at(p, p.pull_axis == 0 ? xw : yw, tshift) : R(0);
+  R cs0[NC], d0[NC];
+  face_quant<N, NC, R, MT>(p, ph1, m0, td0, cs0, d0);
+  if (tid < T + H) {
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      sv[q][tid] = m0[q];
+      sv[NC + q][tid] = cs0[q];
+      sv[2 * NC + q][tid] = d0[q];
+    }
+    if constexpr (SH)
+#pragma unroll
+      for (int q = 0; q < N; ++q) sv[3 * NC + q][tid] = ph1[q];
+    if (tile) {
+#pragma unroll
+      for (int a = 0; a < D; ++a) su[a * T + tid] = uc[a];
+    } else {
+      su[(D - 1) * T + tid] = uc[0];
+    }
+  }
+  block_sync_lds();
+  if (!own) return;
+  const int64_t cu = ROW ? (int64_t)__builtin_amdgcn_readfirstlane(y) * p.sy : 0;
+  const int cs = x + (ROW ? 0 : y * (int)p.sy);
+  store_comps<N, R>(p, phi1, cu, cs, ph1);
+  R mn[NC], g1[SH ? N : 1][D];
+  const int pos[3] = {x, y, 0}, lpos[3] = {lx, ly, 0};
+  mu_update<D, N, NC, R, TX, TY, 1, SH, MT>(p, pos, lpos, tid, sv, su, ph0, ph1, m0, uc, cs0, d0, td0, mn, g1);
+  store_comps<NC, R>(p, mu_out, cu, cs, mn);
   collide_cell<D, Q, N, NC, R, SH, MT>(p, cu, cs, f, ph0, ph1, mn, g1, td0, u_out, fout, dr_out);
 }
 

@@ -319,22 +319,26 @@ inline unsigned adj_blocks(const int64_t (&n)[3]) {
   return 8u * lin_blocks(n[0] * ((n[1] + 7) / 8) * n[2], gpf::ADJ_BLOCK);
 }
 
-// tiles of the phase field in 3D (64 x 4 cells in 2D), one cell per thread
-// (measured, see the kernel)
+// tiles of k_phi in 3D (64 x 4 cells in 2D) and of k_mulbm (one plane in 2D),
+// and of k_step2 on grids of more and of at most small_grid's cells; one cell
+// per thread (measured, see the kernels; 32 x 4, 16 x 8 and 16 x 4 cells are
+// alike on small grids)
 #define GPF_PHI_TX 32
 #define GPF_PHI_TY 4
 #define GPF_PHI_TZ 2
-constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
-// tiles of k_mulbm in 3D (64 x 4 cells in 2D), one cell per thread (measured,
-// see the kernel)
 #define GPF_MU_TX 64
 #define GPF_MU_TY 4
 #define GPF_MU_TZ 2
-// tile rows and planes of a block of the bandwidth probe's z-marched pull
-constexpr int kProbeY = 4, kProbeZ = 4;
+#define GPF_2D_TX 64
+#define GPF_2D_TY 8
+#define GPF_2DS_TX 32
+#define GPF_2DS_TY 4
 constexpr int phi_tx(int dim) { return dim == 3 ? GPF_PHI_TX : 64; }
 constexpr int phi_ty(int dim) { return dim == 3 ? GPF_PHI_TY : 4; }
 constexpr int phi_tz(int dim) { return dim == 3 ? GPF_PHI_TZ : 1; }
+constexpr int ilog2(int v) { return v <= 1 ? 0 : 1 + ilog2(v / 2); }
+// tile rows and planes of a block of the bandwidth probe's z-marched pull
+constexpr int kProbeY = 4, kProbeZ = 4;
 // tiles of the phase field
 inline int64_t phi_blocks(const gpf_ctx* c) {
   const int64_t tx = phi_tx(c->dim), ty = phi_ty(c->dim), tz = phi_tz(c->dim);
@@ -369,12 +373,22 @@ struct Impl {
   static void launch_step(gpf_ctx* c, const gpf::KP<R>& k, const SP& in, const SP& out, R ts,
                           hipStream_t st, hipEvent_t* ev, const uint8_t* bulk_in = nullptr,
                           uint8_t* bulk_out = nullptr, uint8_t* act_out = nullptr) {
+    if (ev) (void)hipEventRecord(ev[0], st);
+    if constexpr (D == 2) {
+      if (fused_2d(c)) {
+        if (ev) (void)hipEventRecord(ev[1], st);
+        if (small_grid(c))
+          launch_2d<GPF_2DS_TX, GPF_2DS_TY>(c, k, in, out, ts, st, act_out);
+        else
+          launch_2d<GPF_2D_TX, GPF_2D_TY>(c, k, in, out, ts, st, act_out);
+        if (ev) (void)hipEventRecord(ev[2], st);
+        return;
+      }
+    }
     constexpr int TX = phi_tx(D), TY = phi_ty(D), TZ = phi_tz(D);
     const int tiles_x = (int)((c->n[0] + TX - 1) / TX), tiles_y = (int)((c->n[1] + TY - 1) / TY);
     const int tiles_z = (int)((c->n[2] + TZ - 1) / TZ);
     const unsigned nb = (unsigned)tiles_x * (unsigned)tiles_y * (unsigned)tiles_z;
-    const dim3 block(TX * TY * TZ);
-    if (ev) (void)hipEventRecord(ev[0], st);
     unsigned *list = nullptr, *counts = nullptr;  // set when the phase field walks a list of tiles
     unsigned g = (nb + 7u) / 8u * 8u;
     if constexpr (D == 3) {
@@ -387,23 +401,23 @@ struct Impl {
         g = std::max(8u, std::min(c->zl_grid, g));
       }
     }
-#define GPF_PHI(ISO)                                                                                               \
-  hipLaunchKernelGGL((gpf::k_phi<D, N, NC, R, TX, TY, TZ, ISO>), dim3(g), block, 0, st, k, in.phi, in.mu, out.phi, \
-                     bulk_in, bulk_out, act_out, list, counts, ts, tiles_x, tiles_y, tiles_z)
+#define GPF_PHI(ISO)                                                                                             \
+  hipLaunchKernelGGL((gpf::k_phi<D, N, NC, R, TX, TY, TZ, ISO>), dim3(g), dim3(TX * TY * TZ), 0, st, k, in.phi,  \
+                     in.mu, out.phi, bulk_in, bulk_out, act_out, list, counts, ts, tiles_x, tiles_y, tiles_z)
     if (k.aniso)
       GPF_PHI(false);
     else
       GPF_PHI(true);
 #undef GPF_PHI
     if (ev) (void)hipEventRecord(ev[1], st);
-    constexpr int MX = D == 3 ? GPF_MU_TX : 64, MY = D == 3 ? GPF_MU_TY : 4, MZ = D == 3 ? GPF_MU_TZ : 1;
+    constexpr int MX = GPF_MU_TX, MY = GPF_MU_TY, MZ = D == 3 ? GPF_MU_TZ : 1;
     const int mtx = (int)((c->n[0] + MX - 1) / MX), mty = (int)((c->n[1] + MY - 1) / MY);
     const int mtz = (int)((c->n[2] + MZ - 1) / MZ);
     const dim3 mgrid((unsigned)mtx * (unsigned)mty * (unsigned)mtz);
-#define GPF_MULBM(SH, MT)                                                                                        \
-  hipLaunchKernelGGL((gpf::k_mulbm<D, Q, N, NC, R, MX, MY, MZ, SH, MT>), mgrid, dim3(MX * MY * MZ), 0, st, k, in.phi, \
-                     out.phi, in.mu, in.u, in.f, out.mu, out.u, out.f, out.dr, bulk_out, ilog2(TX), ilog2(TY), ilog2(TZ), ts, mtx, mty,    \
-                     (mty + 7) / 8, counts)
+#define GPF_MULBM(SH, MT)                                                                                          \
+  hipLaunchKernelGGL((gpf::k_mulbm<D, Q, N, NC, R, MX, MY, MZ, SH, MT>), mgrid, dim3(MX * MY * MZ), 0, st, k,      \
+                     in.phi, out.phi, in.mu, in.u, in.f, out.mu, out.u, out.f, out.dr, bulk_out, ilog2(TX),        \
+                     ilog2(TY), ilog2(TZ), ts, mtx, mty, (mty + 7) / 8, counts)
     if (k.shrink) {
       if (k.tdep)
         GPF_MULBM(true, true);
@@ -418,6 +432,32 @@ struct Impl {
     if (ev) (void)hipEventRecord(ev[2], st);
   }
 
+  // 2D grids whose step is one launch (k_step2): up to 3 MiB per component,
+  // between the 2 MiB (1024 x 512 in FP32) where it is the faster form and the
+  // 4 MiB (the same in FP64) where it is not
+  static bool fused_2d(const gpf_ctx* c) { return D == 2 && c->pcells * (int64_t)sizeof(R) <= ((int64_t)3 << 20); }
+
+  // one step of a 2D grid: a single launch
+  template <int TX, int TY>
+  static void launch_2d(gpf_ctx* c, const gpf::KP<R>& k, const SP& in, const SP& out, R ts, hipStream_t st,
+                        uint8_t* act_out) {
+    const int tx = (int)((c->n[0] + TX - 1) / TX), ty = (int)((c->n[1] + TY - 1) / TY);
+    const dim3 g((unsigned)tx * (unsigned)ty), b(gpf::StepTile<TX, TY>::NT);
+#define GPF_STEP2(SH, MT)                                                                                     \
+  hipLaunchKernelGGL((gpf::k_step2<Q, N, NC, R, TX, TY, SH, MT>), g, b, 0, st, k, in.phi, out.phi, in.mu, in.u, \
+                     in.f, out.mu, out.u, out.f, out.dr, act_out, ts, tx)
+    if (k.shrink) {
+      if (k.tdep)
+        GPF_STEP2(true, true);
+      else
+        GPF_STEP2(true, false);
+    } else if (k.tdep) {
+      GPF_STEP2(false, true);
+    } else {
+      GPF_STEP2(false, false);
+    }
+#undef GPF_STEP2
+  }
   // Moving frame.  Reading (the paper names the approach only): every
   // frame_every steps the front is the largest pull-axis index of a cell with
   // liquid fraction <= 1/2; beyond frame_front, every field of the state
@@ -517,8 +557,8 @@ struct Impl {
       if (!c->zl_grid) {  // once, outside any capture: k_phi's grid (a multiple of 8)
         int per_cu = 0, cus = 0;
         HIP_OR_FAIL(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                           &per_cu, gpf::k_phi<D, N, NC, R, phi_tx(D), phi_ty(D), phi_tz(D), false>,
-                           phi_tx(D) * phi_ty(D) * phi_tz(D), 0));
+                           &per_cu, gpf::k_phi<D, N, NC, R, GPF_PHI_TX, GPF_PHI_TY, GPF_PHI_TZ, false>,
+                           GPF_PHI_TX * GPF_PHI_TY * GPF_PHI_TZ, 0));
         HIP_OR_FAIL(c, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
         c->zl_grid = std::max(8u, (unsigned)(std::max(per_cu, 1) * cus) / 8u * 8u);
       }

@@ -15,6 +15,10 @@ GRIDS = [("binary3d", [63, 5, 3]), ("binary3d", [64, 4, 2]), ("binary3d", [65, 3
          ("ternary3d_nc2", [66, 31, 4]), ("ternary3d_nc2", [1, 2, 9]), ("quaternary3d", [32, 65, 3]),
          ("quaternary3d", [33, 4, 17]), ("binary2d", [63, 3]), ("binary2d", [65, 33]), ("ternary2d", [191, 5]),
          ("ternary2d_nc2", [2, 67]), ("quaternary2d", [129, 34]),
+         # one launch per 2D step in 32 x 4 tiles, in 64 x 8 tiles above 2^18 cells, two launches above 3 MiB
+         # per component
+         ("binary2d", [33, 5]), ("ternary2d_nc2", [31, 4]), ("quaternary2d", [1, 1]), ("binary2d", [521, 507]),
+         ("ternary2d", [801, 499]),
          # stored rows are padded to 16 values (FP64) from half a line on: the widths around that
          ("binary3d", [7, 5, 3]), ("binary3d", [8, 5, 3]), ("ternary2d", [9, 6]), ("binary2d", [17, 9])]
 
