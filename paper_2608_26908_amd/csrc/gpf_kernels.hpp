@@ -1165,17 +1165,30 @@ __global__ void k_shift(KP<R> p, const R* __restrict__ in, R* __restrict__ out, 
   for (int k = 0; k < ncomp; ++k) out[k * p.cells + P] = in[k * p.cells + P + o];
 }
 
-// f^n_k(P) = stored f*_k(P - c_k) (+ bounce-back), plus w_k rho0: the full f,
-// in dense order.
-template <int D, int Q, class R>
-__global__ void k_gather_f(KP<R> p, const R* __restrict__ fin, double* __restrict__ out) {
+// f^n_k(P) = stored f*_k(P - c_k) (+ bounce-back), plus w_k rho0 in FP64: the
+// full f in dense order, as T.  A block owns 4 rows of 64 cells.  HBM bound
+// (one read and one write of the populations; going through an FP64 copy and a
+// conversion cost 261 us on FP64 150 x 131 x 117 against GATHERUS).
+template <int D, int Q, class R, class T>
+__global__ void __launch_bounds__(256) k_gather_f(KP<R> p, const R* __restrict__ fin, T* __restrict__ out, int tiles_x,
+                                                  int tiles_y) {
   using L = Lat<Q>;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t P;
-  int x, y, z;
-  if (!dense_cell(p, i, x, y, z, P)) return;
-  for (int k = 0; k < L::Q; ++k)
-    out[k * p.live + i] = (double)pull_f<D, Q, R>(p, fin, x, y, z, P, k) + L::w(k) * (double)p.rho0;
+  const Tile t = tile_at<64, 4, 1>(xcd_block(), tiles_x, tiles_y);
+  const int x = t.x0 + (int)threadIdx.x % 64;
+  const int y = t.y0 + __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), z = (D == 3) ? t.z0 : 0;
+  if (x >= p.n[0] || y >= p.n[1]) return;
+  R f[Q];
+  pull_cell<D, Q, true, R>(p, fin, pull_at<D, true, R>(p, x, y, z), f);
+  T* q = out + ((int64_t)z * p.n[1] + y) * p.n[0];
+  opaque_ptr(q);
+#pragma unroll
+  for (int k = 0; k < L::Q; ++k) {
+    *lane_at(q, 0, x) = (T)((double)f[k] + L::w(k) * (double)p.rho0);
+    if (k + 1 < L::Q) {
+      q += p.live;
+      opaque_ptr(q);
+    }
+  }
 }
 
 // inverse of k_gather_f: the stored pre-streaming f* that streams to f^n.
@@ -1243,12 +1256,6 @@ __global__ void k_pack(KP<R> p, const T* __restrict__ in, R* __restrict__ out, i
     out[k * p.cells + P] = (R)v;
   }
 }
-template <class R>
-__global__ void k_from_double(const double* __restrict__ in, R* __restrict__ out, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = (R)in[i];
-}
-
 // derived per-cell fields in FP64: 0 rho, 1 mixture composition C (nc comps),
 // 2 temperature, 3 active-set bitmask
 template <int D, int Q, int N, int NC, class R>

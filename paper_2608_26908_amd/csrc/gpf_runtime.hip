@@ -488,8 +488,7 @@ struct Impl {
     // the populations move as the streamed f^n of the state: pull them into
     // FP64 staging, then store the f* whose pull gives f^n moved by d
     double* fs = static_cast<double*>(c->scratch.ptr);
-    hipLaunchKernelGGL((gpf::k_gather_f<D, Q, R>), dim3(lin_blocks(c->cells, 256)), dim3(256), 0, c->stream, k,
-                       P(c->f[s]), fs);
+    gather_f(c, k, fs);
     hipLaunchKernelGGL((gpf::k_scatter_f<D, Q, R>), dim3(lin_blocks(c->cells, 256)), dim3(256), 0, c->stream, k,
                        fs, P(c->f[t]), ax, (int)d);
     HIP_OR_FAIL(c, hipGetLastError());
@@ -614,6 +613,14 @@ struct Impl {
     return GPF_OK;
   }
 
+  // the full f^n of the current state, dense, as T
+  template <class T>
+  static void gather_f(gpf_ctx* c, const gpf::KP<R>& k, T* out) {
+    const int tx = (int)((c->n[0] + 63) / 64), ty = (int)((c->n[1] + 3) / 4);
+    hipLaunchKernelGGL((gpf::k_gather_f<D, Q, R, T>), dim3((unsigned)tx * (unsigned)ty * (unsigned)c->n[2]), dim3(256), 0,
+                       c->stream, k, P(c->f[c->cur]), out, tx, ty);
+  }
+
   // field -> scratch (FP64 on the device); returns the component count
   static int read(gpf_ctx* c, int field, double* comps) {
     gpf::KP<R> k = make_kp<R>(c);
@@ -637,8 +644,7 @@ struct Impl {
                          0.0);
     } else if (field == GPF_F || field == GPF_RHO) {
       ncomp = (field == GPF_F) ? Q : 1;
-      hipLaunchKernelGGL((gpf::k_gather_f<D, Q, R>), dim3(nb), dim3(256), 0, c->stream, k, P(c->f[s]),
-                         out);
+      gather_f(c, k, out);
       if (field == GPF_RHO) {
         // rho into the slot after the Q populations, then move to the front
         double* rho = out + (int64_t)Q * c->cells;
@@ -680,15 +686,7 @@ struct Impl {
         hipLaunchKernelGGL((gpf::k_unpack<R, R, true>), g, b, 0, c->stream, k, P(c->mu[s]), out, NC, k.mu_ref[0],
                            k.mu_ref[1]);
         break;
-      case GPF_F: {
-        double comps = 0;
-        int rc = read(c, GPF_F, &comps);
-        if (rc) return rc;
-        const int64_t cnt = Q * c->cells;
-        hipLaunchKernelGGL((gpf::k_from_double<R>), dim3(lin_blocks(cnt, 256)), dim3(256), 0,
-                           c->stream, static_cast<const double*>(c->scratch.ptr), out, cnt);
-        break;
-      }
+      case GPF_F: gather_f(c, k, out); break;
       default: return fail(c, GPF_ERR_ARG, "field %d has no native device copy", field);
     }
     HIP_OR_FAIL(c, hipGetLastError());
