@@ -643,28 +643,36 @@ __device__ __forceinline__ int bulk_flag_at(const uint8_t* __restrict__ bulk, un
 //
 // On a 3D grid that is mostly bulk nearly every tile of a launch is of that
 // kind, and dispatching a block for each costs more than the others' work.
-// There k_phi_todo checks every tile's neighbourhood, one thread per tile, sets
-// the flag of each tile it skips and appends the others to a list, and k_phi,
-// launched with a grid of resident blocks, walks the listed tiles.  Each XCD
-// walks a contiguous part of the list (whose waves append in about the order of
-// the tiles), so tiles that are neighbours share its L2.  count is the length
-// of the list; it starts at zero, and the step's k_mulbm, which runs after
-// k_phi, clears it for the next step.
+// There k_phi, launched with a grid of resident blocks, walks a list of the
+// other tiles, which the step before made: once its k_phi has set every flag,
+// phi_todo (on blocks of its own in the step's k_mulbm, one thread per tile)
+// checks every tile's neighbourhood, sets the next step's flag of each tile that
+// will be skipped and appends the others.  Each XCD walks a contiguous part of
+// the list (whose waves append in about the order of the tiles), so tiles that
+// are neighbours share its L2.  Two list lengths take turns: a k_mulbm counts
+// into one, zero until then, and clears the other, which its step's k_phi has
+// read.  (A launch of its own for the list cost 6 to 7 us per step: 25 us of a
+// 64^3 step, now 20.)
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ void __launch_bounds__(256)
-k_phi_todo(const uint8_t* __restrict__ bulk_in, uint8_t* __restrict__ bulk_out, unsigned* __restrict__ list,
-           unsigned* __restrict__ count, int tiles_x, int tiles_y, int tiles_z, int per0, int per1, int per2) {
-  const unsigned nb = (unsigned)tiles_x * (unsigned)tiles_y * (unsigned)tiles_z;
-  const unsigned lb = blockIdx.x * 256u + threadIdx.x;
+// What a k_mulbm is to list: nb tiles of flags `in` (x fastest, nt per axis);
+// no blocks: nothing.
+struct Todo {
+  const uint8_t* in;
+  uint8_t* out;
+  unsigned *list, *count, *clear;
+  int nt[3];
+  unsigned nb, blocks;
+};
+template <int D, int NT>
+__device__ __forceinline__ void phi_todo(const Todo& t, const int (&per)[3]) {
+  const unsigned lb = blockIdx.x * (unsigned)NT + threadIdx.x;
   bool need = false;
-  if (lb < nb) {
-    const int nt[3] = {tiles_x, tiles_y, tiles_z}, per[3] = {per0, per1, per2};
+  if (lb < t.nb) {
     int ok = 1;
 #pragma unroll
-    for (int i = 0; i < 27; ++i) ok &= bulk_flag_at(bulk_in, lb, i, nt, per, D);
+    for (int i = 0; i < 27; ++i) ok &= bulk_flag_at(t.in, lb, i, t.nt, per, D);
     if (ok)
-      bulk_out[lb] = 1;
+      t.out[lb] = 1;
     else
       need = true;
   }
@@ -672,10 +680,10 @@ k_phi_todo(const uint8_t* __restrict__ bulk_in, uint8_t* __restrict__ bulk_out, 
   const unsigned long long m = __ballot(need);
   const unsigned lane = __lane_id();
   unsigned base = 0;
-  if (m && lane == 0) base = atomicAdd(count, (unsigned)__popcll(m));
+  if (m && lane == 0) base = atomicAdd(t.count, (unsigned)__popcll(m));
   base = __shfl(base, 0);
   const unsigned slot = base + (unsigned)__popcll(m & ((1ull << lane) - 1ull));
-  if (need && slot < nb) list[slot] = lb;
+  if (need && slot < t.nb) t.list[slot] = lb;
 }
 
 // list null: every tile, each checked for the skip above where bulk_in is given.
@@ -843,7 +851,7 @@ __global__ void __launch_bounds__(TX * TY * TZ)
 k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R* __restrict__ mu,
         const R* __restrict__ uold, const R* __restrict__ fin, R* __restrict__ mu_out, R* __restrict__ u_out,
         R* __restrict__ fout, R* __restrict__ dr_out, const uint8_t* __restrict__ phi_bulk, int phi_lx, int phi_ly,
-        int phi_lz, R tshift, int tiles_x, int tiles_y, int strip, unsigned* __restrict__ todo_count) {
+        int phi_lz, R tshift, int tiles_x, int tiles_y, int strip, Todo todo) {
   using M = MuTile<D, TX, TY, TZ>;
   constexpr bool ROW = TX == 64;
   static_assert(TX * TY >= 64 && 64 % TX == 0, "a wave's lanes share a plane, and a row when TX is 64");
@@ -852,10 +860,15 @@ k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R
   constexpr int NV = 3 * NC + (SH ? N : 0);  // mu, c*, d (and phi^{n+1}) per slot
   __shared__ R sv[NV][T + H];
   __shared__ R su[D * T + H];  // U_a of the cells, axis after axis, then of the halo of the faces along a
+  if (blockIdx.x < todo.blocks) {
+    phi_todo<D, T>(todo, p.per);
+    return;
+  }
   int x0, y0, z0;
   {
-    // contiguous part of the tile order per XCD, then strips
-    const unsigned nb = gridDim.x, b = blockIdx.x, per8 = nb / 8u;
+    // contiguous part of the tile order per XCD (todo.blocks is a multiple of
+    // 8), then strips
+    const unsigned nb = gridDim.x - todo.blocks, b = blockIdx.x - todo.blocks, per8 = nb / 8u;
     const unsigned lb = (b < per8 * 8u) ? (b % 8u) * per8 + b / 8u : b;
     const unsigned tx = (unsigned)tiles_x, ty = (unsigned)tiles_y, layers = nb / (tx * ty);
     const unsigned sfull = (unsigned)strip * tx * layers;  // tiles of a full strip
@@ -867,9 +880,8 @@ k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R
     z0 = (int)z * TZ;
   }
   const int tid = threadIdx.x;
-  // the step's k_phi, which read the list length, has finished: clear it
-  // for the next step's k_phi_todo
-  if (todo_count && blockIdx.x == 0 && tid == 0) atomicExch(todo_count, 0u);
+  // the step's k_phi, which read this list length, has finished
+  if (todo.clear && blockIdx.x == todo.blocks && tid == 0) atomicExch(todo.clear, 0u);
   const int lx = tid % TX;
   const int ly = ROW ? __builtin_amdgcn_readfirstlane((tid / TX) % TY) : (tid / TX) % TY;
   const int lz = (D == 3) ? __builtin_amdgcn_readfirstlane(tid / (TX * TY)) : 0;

@@ -66,10 +66,12 @@ struct gpf_ctx {
   // unchanged on the block's cells (valid while bulk_ok[i])
   DevBuf bulkf[2];
   bool bulk_ok[2] = {false, false};
-  // tiles that k_phi walks (3D grids, bulk history on) and their
-  // number, which starts at zero; zl_grid: its blocks per launch, the
+  // tiles that the next step's k_phi walks (3D grids, bulk history on) and two
+  // list lengths that take turns, zero at first: the next step reads length
+  // list_par and counts into the other; zl_grid: k_phi's blocks per launch, the
   // device's resident blocks of it
   DevBuf tlist, tcount;
+  int list_par = 0;
   unsigned zl_grid = 0;
   int64_t frame_off = 0;  // moving frame: cells shifted so far along the pull axis
   const double* target = nullptr;  // loss target (caller's device memory, N * cells FP64)
@@ -368,11 +370,21 @@ struct Impl {
     return SP{P(c->phi[s]), P(c->mu[s]), P(c->u[s]), P(c->f[s]), nullptr};
   }
 
-  // bulk_in / bulk_out: k_phi's bulk history, only for a step from one
-  // state buffer into the other (null elsewhere)
+  // The bulk history of a step from one state buffer into the other: flags of
+  // the state it starts from and (bulk_in, null when void) of the one it makes;
+  // par: the list length it reads (list_par).  Elsewhere none.
+  struct Hist {
+    uint8_t *from = nullptr, *to = nullptr;
+    bool valid = false;
+    int par = 0;
+  };
+  static Hist hist(gpf_ctx* c, int s, bool valid, int par) {
+    return Hist{static_cast<uint8_t*>(c->bulkf[s].ptr), static_cast<uint8_t*>(c->bulkf[1 - s].ptr), valid, par};
+  }
   static void launch_step(gpf_ctx* c, const gpf::KP<R>& k, const SP& in, const SP& out, R ts,
-                          hipStream_t st, hipEvent_t* ev, const uint8_t* bulk_in = nullptr,
-                          uint8_t* bulk_out = nullptr, uint8_t* act_out = nullptr) {
+                          hipStream_t st, hipEvent_t* ev, const Hist& h = Hist(), uint8_t* act_out = nullptr) {
+    const uint8_t* bulk_in = h.valid ? h.from : nullptr;
+    uint8_t* bulk_out = h.to;
     if (ev) (void)hipEventRecord(ev[0], st);
     if constexpr (D == 2) {
       if (fused_2d(c)) {
@@ -389,21 +401,23 @@ struct Impl {
     const int tiles_x = (int)((c->n[0] + TX - 1) / TX), tiles_y = (int)((c->n[1] + TY - 1) / TY);
     const int tiles_z = (int)((c->n[2] + TZ - 1) / TZ);
     const unsigned nb = (unsigned)tiles_x * (unsigned)tiles_y * (unsigned)tiles_z;
-    unsigned *list = nullptr, *counts = nullptr;  // set when the phase field walks a list of tiles
     unsigned g = (nb + 7u) / 8u * 8u;
+    unsigned *list = nullptr, *count = nullptr;  // of the tiles to walk, when the step before made one
+    gpf::Todo todo{};
     if constexpr (D == 3) {
-      if (bulk_in && !act_out && c->zl_grid) {
-        // the tiles whose neighbourhood changed, then a walk over them only
-        list = static_cast<unsigned*>(c->tlist.ptr);
-        counts = static_cast<unsigned*>(c->tcount.ptr);
-        hipLaunchKernelGGL((gpf::k_phi_todo<D>), dim3((nb + 255u) / 256u), dim3(256), 0, st, bulk_in, bulk_out, list,
-                           counts, tiles_x, tiles_y, tiles_z, k.per[0], k.per[1], k.per[2]);
-        g = std::max(8u, std::min(c->zl_grid, g));
+      if (bulk_out) {
+        unsigned *tl = static_cast<unsigned*>(c->tlist.ptr), *tc = static_cast<unsigned*>(c->tcount.ptr);
+        todo = gpf::Todo{bulk_out, h.from, tl, tc + (1 - h.par), tc + h.par, {tiles_x, tiles_y, tiles_z}, nb, 0};
+        if (bulk_in) {
+          list = tl;
+          count = tc + h.par;
+          g = std::max(8u, std::min(c->zl_grid, g));
+        }
       }
     }
 #define GPF_PHI(ISO)                                                                                             \
   hipLaunchKernelGGL((gpf::k_phi<D, N, NC, R, TX, TY, TZ, ISO>), dim3(g), dim3(TX * TY * TZ), 0, st, k, in.phi,  \
-                     in.mu, out.phi, bulk_in, bulk_out, act_out, list, counts, ts, tiles_x, tiles_y, tiles_z)
+                     in.mu, out.phi, bulk_in, bulk_out, act_out, list, count, ts, tiles_x, tiles_y, tiles_z)
     if (k.aniso)
       GPF_PHI(false);
     else
@@ -413,11 +427,12 @@ struct Impl {
     constexpr int MX = GPF_MU_TX, MY = GPF_MU_TY, MZ = D == 3 ? GPF_MU_TZ : 1;
     const int mtx = (int)((c->n[0] + MX - 1) / MX), mty = (int)((c->n[1] + MY - 1) / MY);
     const int mtz = (int)((c->n[2] + MZ - 1) / MZ);
-    const dim3 mgrid((unsigned)mtx * (unsigned)mty * (unsigned)mtz);
+    if (todo.in) todo.blocks = (lin_blocks(nb, MX * MY * MZ) + 7u) / 8u * 8u;
+    const dim3 mgrid(todo.blocks + (unsigned)mtx * (unsigned)mty * (unsigned)mtz);
 #define GPF_MULBM(SH, MT)                                                                                          \
   hipLaunchKernelGGL((gpf::k_mulbm<D, Q, N, NC, R, MX, MY, MZ, SH, MT>), mgrid, dim3(MX * MY * MZ), 0, st, k,      \
                      in.phi, out.phi, in.mu, in.u, in.f, out.mu, out.u, out.f, out.dr, bulk_out, ilog2(TX),        \
-                     ilog2(TY), ilog2(TZ), ts, mtx, mty, (mty + 7) / 8, counts)
+                     ilog2(TY), ilog2(TZ), ts, mtx, mty, (mty + 7) / 8, todo)
     if (k.shrink) {
       if (k.tdep)
         GPF_MULBM(true, true);
@@ -520,6 +535,7 @@ struct Impl {
     const R ts = (R)tshift(c, c->step);
     std::string key(reinterpret_cast<const char*>(&k), sizeof(k));
     if (k.G != R(0)) key.append(reinterpret_cast<const char*>(&ts), sizeof(ts));
+    key.push_back((char)c->list_par);
     if (!c->gexec[s] || c->gkey[s] != key) {
       if (remaining < 2 * kGraphSteps) return GPF_OK;  // not worth a capture
       if (c->gexec[s]) {
@@ -531,7 +547,7 @@ struct Impl {
       for (int64_t j = 0; j < kGraphSteps; ++j) {
         const int a = (s + (int)j) & 1, b = 1 - a;
         launch_step(c, k, cur(c, a), cur(c, b), ts, c->gstream, nullptr,
-                    j ? static_cast<const uint8_t*>(c->bulkf[a].ptr) : nullptr, static_cast<uint8_t*>(c->bulkf[b].ptr));
+                    hist(c, a, j > 0, (c->list_par + (int)j) & 1));
       }
       hipGraph_t g = nullptr;
       HIP_OR_FAIL(c, hipStreamEndCapture(c->gstream, &g));
@@ -581,9 +597,9 @@ struct Impl {
       const int s = c->cur, t = 1 - c->cur;
       const R ts = (R)tshift(c, c->step);
       launch_step(c, k, cur(c, s), cur(c, t), ts, c->stream, kernel_ms ? ev : nullptr,
-                  c->bulk_ok[s] ? static_cast<const uint8_t*>(c->bulkf[s].ptr) : nullptr,
-                  static_cast<uint8_t*>(c->bulkf[t].ptr));
+                  hist(c, s, c->bulk_ok[s], c->list_par));
       HIP_OR_FAIL(c, hipGetLastError());
+      c->list_par ^= 1;
       c->bulk_ok[t] = true;
       if (kernel_ms) {
         HIP_OR_FAIL(c, hipEventSynchronize(ev[2]));
@@ -995,7 +1011,7 @@ struct Impl {
     auto act_of = [&](int b, int64_t j) { return static_cast<uint8_t*>(c->tape_act[b].ptr) + j * c->pcells; };
     auto recompute_step = [&](int b, int64_t sg, int64_t j, hipStream_t st) {
       launch_step(c, k, slot(b, sg, j), slot(b, sg, j + 1), (R)tshift(c, c->rec_start + sg * K + j), st, nullptr,
-                  nullptr, nullptr, act_of(b, j));
+                  Hist(), act_of(b, j));
     };
     auto tape_of = [&](int64_t sg) { return ntape == 2 ? (int)((nseg - 1 - sg) & 1) : 0; };
     // X^{rec_start + m}, m in [0, total]: the checkpoints every K steps, the
@@ -1415,10 +1431,10 @@ int gpf_init(gpf_ctx** out, const gpf_grid* grid, int32_t n_phases, int32_t n_co
   if (!rc) rc = dev_alloc(c, c->frontbuf, sizeof(int));
   for (int i = 0; i < 2 && !rc; ++i) rc = dev_alloc(c, c->bulkf[i], (size_t)phi_blocks(c));
   if (!rc) rc = dev_alloc(c, c->tlist, (size_t)phi_blocks(c) * sizeof(unsigned));
-  if (!rc) rc = dev_alloc(c, c->tcount, sizeof(unsigned));
+  if (!rc) rc = dev_alloc(c, c->tcount, 2 * sizeof(unsigned));
   if (!rc) {
     hipError_t e = hipMemsetAsync(c->badstep.ptr, 0xff, sizeof(unsigned long long), c->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(c->tcount.ptr, 0, sizeof(unsigned), c->stream);
+    if (e == hipSuccess) e = hipMemsetAsync(c->tcount.ptr, 0, 2 * sizeof(unsigned), c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->tlist.ptr, 0, c->tlist.bytes, c->stream);
     if (e != hipSuccess) rc = fail(c, GPF_ERR_DEVICE, "hipMemsetAsync: %s", hipGetErrorString(e));
   }
