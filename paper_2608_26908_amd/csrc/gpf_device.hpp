@@ -87,6 +87,7 @@ template <class R> struct KP {
   // start on a line
   int64_t sy, sz, cells;
   int64_t live;           // cells of the grid, n[0] n[1] n[2]
+  int cached;             // the state fits the last-level cache: no streaming accesses
   int potential;          // 0 obstacle, 1 well
   int pull_axis, grav_axis;
   R dx, dt, eps, rate;    // rate = dt / (tau_pf eps)

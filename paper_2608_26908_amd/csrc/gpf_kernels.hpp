@@ -60,19 +60,34 @@ __device__ __forceinline__ T* lane_at(T* base, int64_t u, int l) {
 // component's address anew costs a 64-bit multiplication each.
 template <class T> __device__ __forceinline__ void opaque_ptr(T*& q) { asm volatile("" : "+s"(q)); }
 
-// Streaming stores of the C components v of one cell: element u + l of each.
-template <int C, class R>
+// How a kernel reads the populations and writes the new state, each read once
+// and read again only in the next step: streaming (nontemporal), cached, or as
+// p.cached says (both forms in the code, which a kernel of a few microseconds
+// pays for: 495 -> 517 us in 50 steps of 144 x 700).
+enum Access { STREAM, CACHED, EITHER };
+
+// Stores of the C components v of one cell, element u + l of each.
+template <int C, Access AC, class R>
 __device__ __forceinline__ void store_comps(const KP<R>& p, R* __restrict__ out, int64_t u, int l, const R (&v)[C]) {
-  R* q = out + u;
-  opaque_ptr(q);
+  auto put = [&](auto stream) {
+    R* q = out + u;
+    opaque_ptr(q);
 #pragma unroll
-  for (int k = 0; k < C; ++k) {
-    __builtin_nontemporal_store(v[k], lane_at(q, 0, l));
-    if (k + 1 < C) {
-      q += p.cells;
-      opaque_ptr(q);
+    for (int k = 0; k < C; ++k) {
+      if constexpr (decltype(stream)::value)
+        __builtin_nontemporal_store(v[k], lane_at(q, 0, l));
+      else
+        *lane_at(q, 0, l) = v[k];
+      if (k + 1 < C) {
+        q += p.cells;
+        opaque_ptr(q);
+      }
     }
-  }
+  };
+  if (AC == CACHED || (AC == EITHER && p.cached))
+    put(std::false_type());
+  else
+    put(std::true_type());
 }
 
 // Source cells of the pulls of one lane, as element offsets: xs, ys, zs at
@@ -117,22 +132,31 @@ __device__ __forceinline__ PullAt<ROW> pull_at(const KP<R>& p, int x, int y, int
 // loaded first (clamped at walls); then the cells at a wall, in tiles at the
 // grid's faces only, take the reflected population f*_{opp k}(P) instead
 // (half-way bounce-back).
-template <int D, int Q, bool ROW, class R>
+template <int D, int Q, bool ROW, Access AC, class R>
 __device__ __forceinline__ void pull_cell(const KP<R>& p, const R* __restrict__ fin, const PullAt<ROW>& px,
                                           R (&f)[Q]) {
   using L = Lat<Q>;
-  const R* q = fin;
-  opaque_ptr(q);
+  auto get = [&](auto stream) {
+    const R* q = fin;
+    opaque_ptr(q);
 #pragma unroll
-  for (int k = 0; k < Q; ++k) {
-    const int ix = 1 - L::c(k, 0), iy = 1 - L::c(k, 1), iz = 1 - L::c(k, 2);
-    f[k] = __builtin_nontemporal_load(
-        lane_at(q, px.zs[iz] + (ROW ? (int64_t)px.ys[iy] : 0), px.xs[ix] + (ROW ? 0 : (int)px.ys[iy])));
-    if (k + 1 < Q) {
-      q += p.cells;
-      opaque_ptr(q);
+    for (int k = 0; k < Q; ++k) {
+      const int ix = 1 - L::c(k, 0), iy = 1 - L::c(k, 1), iz = 1 - L::c(k, 2);
+      const R* at = lane_at(q, px.zs[iz] + (ROW ? (int64_t)px.ys[iy] : 0), px.xs[ix] + (ROW ? 0 : (int)px.ys[iy]));
+      if constexpr (decltype(stream)::value)
+        f[k] = __builtin_nontemporal_load(at);
+      else
+        f[k] = *at;
+      if (k + 1 < Q) {
+        q += p.cells;
+        opaque_ptr(q);
+      }
     }
-  }
+  };
+  if (AC == CACHED || (AC == EITHER && p.cached))
+    get(std::false_type());
+  else
+    get(std::true_type());
   auto bounce = [&](int k) -> R {
     R val = *lane_at(fin, (int64_t)L::opp(k) * p.cells + px.zs[1] + (ROW ? (int64_t)px.ys[1] : 0),
                      px.xs[1] + (ROW ? 0 : (int)px.ys[1]));
@@ -390,7 +414,7 @@ __device__ __forceinline__ void face_quant(const KP<R>& p, const R (&ph)[N], con
 // differences phi^{n+1}_b(P + e_a) - phi^{n+1}_b(P - e_a) that the shrinkage
 // force (SH) takes its normals from; td0: T^n - T_E.
 // ---------------------------------------------------------------------------
-template <int D, int Q, int N, int NC, class R, bool SH, bool MT>
+template <int D, int Q, int N, int NC, class R, bool SH, bool MT, Access AC>
 __device__ __forceinline__ void collide_cell(const KP<R>& p, int64_t u0, int l0, const R (&f)[Q], const R (&ph0)[N],
                                              const R (&ph1)[N], const R (&mn)[NC], const R (&g1)[SH ? N : 1][D],
                                              R td0, R* __restrict__ u_out, R* __restrict__ fout,
@@ -489,8 +513,8 @@ __device__ __forceinline__ void collide_cell(const KP<R>& p, int64_t u0, int l0,
     fp[k] = keep * f[k] + (even + odd);
     fp[kb] = keep * f[kb] + (even - odd);
   }
-  store_comps<L::Q, R>(p, fout, u0, l0, fp);
-  store_comps<D, R>(p, u_out, u0, l0, u);
+  store_comps<L::Q, AC, R>(p, fout, u0, l0, fp);
+  store_comps<D, AC, R>(p, u_out, u0, l0, u);
 }
 
 // coordinate along one axis of a tile-halo cell, v >= -1: periodic axes wrap,
@@ -755,7 +779,11 @@ k_phi(KP<R> p, const R* __restrict__ phi, const R* __restrict__ mu, R* __restric
 // and now: 675 -> 631 (256^3, two phases, FP32), 1407 -> 1236 (FP64), 357 ->
 // 293 (192^3, three phases, two solutes), 117 -> 67 (96 x 96 x 128, four
 // phases), 35 -> 19 (64^3); tiles of 32 x 4 x 2 and 32 x 4 x 4 cells took 646
-// and 673 on 256^3, 64 x 2 x 2 took 664 and 64 x 4 x 1 632.
+// and 673 on 256^3, 64 x 2 x 2 took 664 and 64 x 4 x 1 632.  Two phases in FP32
+// gain from tiles of whole 1 KiB rows (256 x 2 x 1), whose x-shifted pulls share
+// their lines within a CU: 629 -> 603 us on 256^3, 265 -> 246 on 250 x 200 x
+// 128, though 95 -> 109 on 128^3, where half of their lanes idle; in FP64 (1224
+// and 1228) and with more phases (176 and 178) they gain nothing.
 // LDS-shared slots of a tile: its T cells (slot = thread), then the halo of
 // each face: z-, z+ (TX x TY cells each), y-, y+ (TX x TZ), x-, x+ (TY x TZ).
 template <int D, int TX, int TY, int TZ> struct MuTile {
@@ -853,8 +881,9 @@ k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R
         R* __restrict__ fout, R* __restrict__ dr_out, const uint8_t* __restrict__ phi_bulk, int phi_lx, int phi_ly,
         int phi_lz, R tshift, int tiles_x, int tiles_y, int strip, Todo todo) {
   using M = MuTile<D, TX, TY, TZ>;
-  constexpr bool ROW = TX == 64;
-  static_assert(TX * TY >= 64 && 64 % TX == 0, "a wave's lanes share a plane, and a row when TX is 64");
+  constexpr Access AC = N == 2 ? STREAM : EITHER;  // (two phases: nothing gained)
+  constexpr bool ROW = TX % 64 == 0;
+  static_assert(TX * TY >= 64 && (ROW || 64 % TX == 0), "a wave's lanes share a plane, and with ROW a row");
   static_assert(D == 3 || TZ == 1, "one plane in 2D");
   constexpr int T = M::T, H = M::H, HI = (H + T - 1) / T;
   constexpr int NV = 3 * NC + (SH ? N : 0);  // mu, c*, d (and phi^{n+1}) per slot
@@ -952,7 +981,7 @@ k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R
   }
   R f[Q];
   const PullAt<ROW> px = pull_at<D, ROW, R>(p, xw, yw, zw);
-  if (own) pull_cell<D, Q, ROW, R>(p, fin, px, f);
+  if (own) pull_cell<D, Q, ROW, AC, R>(p, fin, px, f);
   if (!same0) {
 #pragma unroll
     for (int q = 0; q < N; ++q) ph0[q] = *lane_at(phi0, q * p.cells + cu, cl);
@@ -1000,9 +1029,8 @@ k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R
   R mn[NC], g1[SH ? N : 1][D];
   const int pos[3] = {x, y, z}, lpos[3] = {lx, ly, lz};
   mu_update<D, N, NC, R, TX, TY, TZ, SH, MT>(p, pos, lpos, tid, sv, su, ph0, ph1, m0, uc, cs0, d0, td0, mn, g1);
-#pragma unroll
-  for (int i = 0; i < NC; ++i) __builtin_nontemporal_store(mn[i], lane_at(mu_out, i * p.cells + cu, cs));
-  collide_cell<D, Q, N, NC, R, SH, MT>(p, cu, cs, f, ph0, ph1, mn, g1, td0, u_out, fout, dr_out);
+  store_comps<NC, AC, R>(p, mu_out, cu, cs, mn);
+  collide_cell<D, Q, N, NC, R, SH, MT, AC>(p, cu, cs, f, ph0, ph1, mn, g1, td0, u_out, fout, dr_out);
 }
 
 // ---------------------------------------------------------------------------
@@ -1033,6 +1061,9 @@ k_step2(KP<R> p, const R* __restrict__ phi0, R* __restrict__ phi1, const R* __re
         R* __restrict__ fout, R* __restrict__ dr_out, uint8_t* __restrict__ act_out, R tshift, int tiles_x) {
   constexpr int D = 2;
   using M = MuTile<D, TX, TY, 1>;
+  // the wide tile is that of grids above 2^18 cells whose two states fit the
+  // last-level cache
+  constexpr Access AC = TX == 64 ? CACHED : STREAM;
   constexpr bool ROW = TX == 64;
   constexpr int T = StepTile<TX, TY>::T, H = StepTile<TX, TY>::H, NT = StepTile<TX, TY>::NT;
   static_assert(T % 64 == 0 && H == M::H, "tile threads fill their waves; slots as in MuTile");
@@ -1093,7 +1124,7 @@ k_step2(KP<R> p, const R* __restrict__ phi0, R* __restrict__ phi1, const R* __re
   // (with ROW a wave of the tile shares its row)
   const PullAt<ROW> px = pull_at<D, ROW, R>(p, xw, ROW ? __builtin_amdgcn_readfirstlane(yw) : yw, 0);
   R f[Q];
-  if (own) pull_cell<D, Q, ROW, R>(p, fin, px, f);
+  if (own) pull_cell<D, Q, ROW, AC, R>(p, fin, px, f);
   block_sync_lds();
   R ph0[N], ph1[N];
   {
@@ -1136,12 +1167,12 @@ k_step2(KP<R> p, const R* __restrict__ phi0, R* __restrict__ phi1, const R* __re
   if (!own) return;
   const int64_t cu = ROW ? (int64_t)__builtin_amdgcn_readfirstlane(y) * p.sy : 0;
   const int cs = x + (ROW ? 0 : y * (int)p.sy);
-  store_comps<N, R>(p, phi1, cu, cs, ph1);
+  store_comps<N, AC, R>(p, phi1, cu, cs, ph1);
   R mn[NC], g1[SH ? N : 1][D];
   const int pos[3] = {x, y, 0}, lpos[3] = {lx, ly, 0};
   mu_update<D, N, NC, R, TX, TY, 1, SH, MT>(p, pos, lpos, tid, sv, su, ph0, ph1, m0, uc, cs0, d0, td0, mn, g1);
-  store_comps<NC, R>(p, mu_out, cu, cs, mn);
-  collide_cell<D, Q, N, NC, R, SH, MT>(p, cu, cs, f, ph0, ph1, mn, g1, td0, u_out, fout, dr_out);
+  store_comps<NC, AC, R>(p, mu_out, cu, cs, mn);
+  collide_cell<D, Q, N, NC, R, SH, MT, AC>(p, cu, cs, f, ph0, ph1, mn, g1, td0, u_out, fout, dr_out);
 }
 
 // ---------------------------------------------------------------------------
@@ -1190,7 +1221,7 @@ __global__ void __launch_bounds__(256) k_gather_f(KP<R> p, const R* __restrict__
   const int y = t.y0 + __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), z = (D == 3) ? t.z0 : 0;
   if (x >= p.n[0] || y >= p.n[1]) return;
   R f[Q];
-  pull_cell<D, Q, true, R>(p, fin, pull_at<D, true, R>(p, x, y, z), f);
+  pull_cell<D, Q, true, STREAM, R>(p, fin, pull_at<D, true, R>(p, x, y, z), f);
   T* q = out + ((int64_t)z * p.n[1] + y) * p.n[0];
   opaque_ptr(q);
 #pragma unroll

@@ -184,6 +184,16 @@ gpf::KP<R> make_kp(const gpf_ctx* c) {
   k.sz = c->pitch * c->n[1];
   k.cells = c->pcells;
   k.live = c->cells;
+  // both states within the 256 MiB last-level cache: cached accesses keep part
+  // of them there (1024 x 512, three phases: 17.0 -> 15.8 us per step in FP32,
+  // 33.0 -> 30.7 in FP64; 96^3, three phases, 181 MiB: 44.8 -> 41.8; 96 x 96 x 128,
+  // four phases, 252 MiB: 60.5 -> 57.2); beyond it streaming ones are faster
+  // (128^3, two phases, 400 MiB: 89.7 against 93.6), and so they are up to 2^18
+  // cells, where latency counts and a host synchronisation has to write the
+  // cached lines back (144 x 700, four phases, a moving-frame check every 25 of
+  // 50 steps: 498 against 541)
+  k.cached = c->cells > ((int64_t)1 << 18) &&
+             2 * (int64_t)(c->N + c->nc + c->dim + c->Q) * c->pcells * (int64_t)sizeof(R) <= ((int64_t)256 << 20);
   k.potential = p.potential;
   k.pull_axis = p.pull_axis;
   k.grav_axis = p.grav_axis;
@@ -424,15 +434,28 @@ struct Impl {
       GPF_PHI(true);
 #undef GPF_PHI
     if (ev) (void)hipEventRecord(ev[1], st);
-    constexpr int MX = GPF_MU_TX, MY = GPF_MU_TY, MZ = D == 3 ? GPF_MU_TZ : 1;
+    // tiles of whole 1 KiB rows where they fit (see k_mulbm)
+    bool wide = false;
+    if constexpr (D == 3 && N == 2 && sizeof(R) == 4) {
+      wide = c->n[0] % 256 == 0 || c->n[0] % 256 > 224;
+      if (wide) launch_mulbm<256, 2, 1>(c, k, in, out, ts, st, bulk_out, todo, nb);
+    }
+    if (!wide) launch_mulbm<GPF_MU_TX, GPF_MU_TY, (D == 3 ? GPF_MU_TZ : 1)>(c, k, in, out, ts, st, bulk_out, todo, nb);
+    if (ev) (void)hipEventRecord(ev[2], st);
+  }
+
+  // nb: tiles of the phase field, which todo lists
+  template <int MX, int MY, int MZ>
+  static void launch_mulbm(gpf_ctx* c, const gpf::KP<R>& k, const SP& in, const SP& out, R ts, hipStream_t st,
+                           const uint8_t* bulk, gpf::Todo todo, unsigned nb) {
     const int mtx = (int)((c->n[0] + MX - 1) / MX), mty = (int)((c->n[1] + MY - 1) / MY);
     const int mtz = (int)((c->n[2] + MZ - 1) / MZ);
     if (todo.in) todo.blocks = (lin_blocks(nb, MX * MY * MZ) + 7u) / 8u * 8u;
     const dim3 mgrid(todo.blocks + (unsigned)mtx * (unsigned)mty * (unsigned)mtz);
 #define GPF_MULBM(SH, MT)                                                                                          \
   hipLaunchKernelGGL((gpf::k_mulbm<D, Q, N, NC, R, MX, MY, MZ, SH, MT>), mgrid, dim3(MX * MY * MZ), 0, st, k,      \
-                     in.phi, out.phi, in.mu, in.u, in.f, out.mu, out.u, out.f, out.dr, bulk_out, ilog2(TX),        \
-                     ilog2(TY), ilog2(TZ), ts, mtx, mty, (mty + 7) / 8, todo)
+                     in.phi, out.phi, in.mu, in.u, in.f, out.mu, out.u, out.f, out.dr, bulk, ilog2(phi_tx(D)),     \
+                     ilog2(phi_ty(D)), ilog2(phi_tz(D)), ts, mtx, mty, (mty + 7) / 8, todo)
     if (k.shrink) {
       if (k.tdep)
         GPF_MULBM(true, true);
@@ -444,7 +467,6 @@ struct Impl {
       GPF_MULBM(false, false);
     }
 #undef GPF_MULBM
-    if (ev) (void)hipEventRecord(ev[2], st);
   }
 
   // 2D grids whose step is one launch (k_step2): up to 3 MiB per component,
