@@ -1048,13 +1048,16 @@ k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R
 // 13.5 and 8.4 (144 x 700, four phases), 19.7 and 17.0 (1024 x 512, three
 // phases, FP32); but 33.9 and 36 (the same in FP64) and 98 and 109 (2048^2,
 // two phases, FP32), where the halo's share of the work counts and the bulk
-// history spares k_phi most of its tiles.
+// history spares k_phi most of its tiles.  An instance of its own without
+// anisotropy (ISO), and the populations' loads sent off before the wait for the
+// phase field's: 2 to 3 % of a step of three and four phases without it, 1 % of
+// two (before, the instance chose at run time).
 // ---------------------------------------------------------------------------
 template <int TX, int TY> struct StepTile {
   static constexpr int T = TX * TY, H = 2 * (TX + TY), NT = T + (H + 63) / 64 * 64;
 };
 
-template <int Q, int N, int NC, class R, int TX, int TY, bool SH, bool MT>
+template <int Q, int N, int NC, class R, int TX, int TY, bool SH, bool MT, bool ISO>
 __global__ void __launch_bounds__((StepTile<TX, TY>::NT))
 k_step2(KP<R> p, const R* __restrict__ phi0, R* __restrict__ phi1, const R* __restrict__ mu,
         const R* __restrict__ uold, const R* __restrict__ fin, R* __restrict__ mu_out, R* __restrict__ u_out,
@@ -1114,17 +1117,17 @@ k_step2(KP<R> p, const R* __restrict__ phi0, R* __restrict__ phi1, const R* __re
     uc[0] = uold[ha * p.cells + P];
     uc[1] = R(0);
   }
-#pragma unroll
-  for (int r = 0; r < FP; ++r)
-    if (tid + r * NT < FC)
-#pragma unroll
-      for (int q = 0; q < N; ++q) sp[q][tid + r * NT] = fpre[r][q];
   // the padding of a row is computed and stored too, as in k_mulbm
   const bool own = tile && x < (int)p.sy && y < p.n[1];
   // (with ROW a wave of the tile shares its row)
   const PullAt<ROW> px = pull_at<D, ROW, R>(p, xw, ROW ? __builtin_amdgcn_readfirstlane(yw) : yw, 0);
   R f[Q];
   if (own) pull_cell<D, Q, ROW, AC, R>(p, fin, px, f);
+#pragma unroll
+  for (int r = 0; r < FP; ++r)
+    if (tid + r * NT < FC)
+#pragma unroll
+      for (int q = 0; q < N; ++q) sp[q][tid + r * NT] = fpre[r][q];
   block_sync_lds();
   R ph0[N], ph1[N];
   {
@@ -1138,10 +1141,7 @@ k_step2(KP<R> p, const R* __restrict__ phi0, R* __restrict__ phi1, const R* __re
 #pragma unroll
     for (int q = 0; q < N; ++q) ph0[q] = v[q][1][1][1];
     uint8_t* act = (act_out && tile && x < p.n[0] && y < p.n[1]) ? act_out + P : nullptr;
-    if (p.aniso)
-      phi_from_stencil<D, N, NC, R, false>(p, v, m0, xw, yw, 0, tshift, ph1, act);
-    else
-      phi_from_stencil<D, N, NC, R, true>(p, v, m0, xw, yw, 0, tshift, ph1, act);
+    phi_from_stencil<D, N, NC, R, ISO>(p, v, m0, xw, yw, 0, tshift, ph1, act);
   }
   const R td0 = MT ? tdev_at(p, p.pull_axis == 0 ? xw : yw, tshift) : R(0);
   R cs0[NC], d0[NC];

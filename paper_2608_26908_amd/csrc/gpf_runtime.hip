@@ -480,9 +480,15 @@ struct Impl {
                         uint8_t* act_out) {
     const int tx = (int)((c->n[0] + TX - 1) / TX), ty = (int)((c->n[1] + TY - 1) / TY);
     const dim3 g((unsigned)tx * (unsigned)ty), b(gpf::StepTile<TX, TY>::NT);
-#define GPF_STEP2(SH, MT)                                                                                     \
-  hipLaunchKernelGGL((gpf::k_step2<Q, N, NC, R, TX, TY, SH, MT>), g, b, 0, st, k, in.phi, out.phi, in.mu, in.u, \
-                     in.f, out.mu, out.u, out.f, out.dr, act_out, ts, tx)
+#define GPF_STEP2(SH, MT)                                                                                          \
+  do {                                                                                                             \
+    if (k.aniso)                                                                                                   \
+      hipLaunchKernelGGL((gpf::k_step2<Q, N, NC, R, TX, TY, SH, MT, false>), g, b, 0, st, k, in.phi, out.phi, in.mu, \
+                         in.u, in.f, out.mu, out.u, out.f, out.dr, act_out, ts, tx);                               \
+    else                                                                                                           \
+      hipLaunchKernelGGL((gpf::k_step2<Q, N, NC, R, TX, TY, SH, MT, true>), g, b, 0, st, k, in.phi, out.phi, in.mu, \
+                         in.u, in.f, out.mu, out.u, out.f, out.dr, act_out, ts, tx);                               \
+  } while (0)
     if (k.shrink) {
       if (k.tdep)
         GPF_STEP2(true, true);
