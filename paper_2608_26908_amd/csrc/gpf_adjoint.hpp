@@ -54,9 +54,10 @@ __device__ __forceinline__ bool adj_cell(const int (&n)[3], int64_t sy, int64_t 
 // order (shuffle tree within each wave, then the waves in turn), added to the
 // block's running sums over the reverse sweep: every block owns its slots, so
 // no atomics are needed and the result is deterministic.
+template <int NT = ADJ_BLOCK>
 __device__ __forceinline__ void block_partials(double (&g)[NG], double* __restrict__ part,
                                                unsigned slot = blockIdx.x) {
-  constexpr int NW = ADJ_BLOCK / 64;
+  constexpr int NW = NT / 64;
   __shared__ double sh[NG][NW];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
 #pragma unroll
@@ -125,6 +126,7 @@ __device__ __forceinline__ R d2h(const R (&ph)[N], int b, int a, int g) {
 // 1. streaming transpose + collision VJP
 // ---------------------------------------------------------------------------
 // The collision depends on the pulled populations only through rho and U.
+// lu1, lmu1: the adjoints of the cell's U^n and mu^{n+1}.
 // TAPE: rho - rho0 of the step was stored by the forward recomputation and U
 // is the step's own output, so f is not read; otherwise both are recomputed
 // from the pulled f (the last step of a checkpoint segment).
@@ -133,9 +135,8 @@ __device__ __forceinline__ void adj_lbm_cell(const KP<R>& p, const int64_t P, co
                                              const int z, const R* __restrict__ fst,
                                              const R* __restrict__ dr_t, const R* __restrict__ u1,
                                              const R* __restrict__ phi1, const R* __restrict__ mu1,
-                                             const R* __restrict__ lf1, const R* __restrict__ lu1,
-                                             const R* __restrict__ lmu1, R* __restrict__ lf0,
-                                             R* __restrict__ t_phil, R* __restrict__ w,
+                                             const R* __restrict__ lf1, const R (&lu1)[D], const R (&lmu1)[NC],
+                                             R* __restrict__ lf0, R* __restrict__ t_phil, R* __restrict__ w,
                                              R* __restrict__ lmu0, R tshift1, double (&gpart)[NG]) {
   using L = Lat<Q>;
   {
@@ -228,7 +229,7 @@ __device__ __forceinline__ void adj_lbm_cell(const KP<R>& p, const int64_t P, co
     R fb[L::Q], drb = R(0), rhob = R(0), uub = R(0), uFb = R(0), ub[D], Fb[D];
 #pragma unroll
     for (int a = 0; a < D; ++a) {
-      ub[a] = lu1[a * p.cells + P];
+      ub[a] = lu1[a];
       Fb[a] = R(0);
     }
 #pragma unroll
@@ -317,7 +318,7 @@ __device__ __forceinline__ void adj_lbm_cell(const KP<R>& p, const int64_t P, co
     for (int b = 0; b < N; ++b) sh += h[b];
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
-      mt[i] = lmu1[i * p.cells + P] + mub[i];
+      mt[i] = lmu1[i] + mub[i];
       lmu0[i * p.cells + P] = mt[i];
     }
     if (NC == 1) {
@@ -341,9 +342,15 @@ k_adj_lbm(KP<R> p, const R* __restrict__ fst, const R* __restrict__ dr_t, const 
   double gpart[NG] = {0, 0, 0, 0, 0, 0};
   int64_t P;
   int x, y, z;
-  if (adj_cell(p.n, p.sy, p.sz, P, x, y, z))
-    adj_lbm_cell<D, Q, N, NC, R, TAPE>(p, P, x, y, z, fst, dr_t, u1, phi1, mu1, lf1, lu1, lmu1, lf0, t_phil, w,
+  if (adj_cell(p.n, p.sy, p.sz, P, x, y, z)) {
+    R lu[D], lm[NC];
+#pragma unroll
+    for (int a = 0; a < D; ++a) lu[a] = lu1[a * p.cells + P];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) lm[i] = lmu1[i * p.cells + P];
+    adj_lbm_cell<D, Q, N, NC, R, TAPE>(p, P, x, y, z, fst, dr_t, u1, phi1, mu1, lf1, lu, lm, lf0, t_phil, w,
                                        lmu0, tshift1, gpart);
+  }
   block_partials(gpart, part);
 }
 
@@ -538,6 +545,122 @@ __device__ __forceinline__ void mu_adj_cell(const KP<R>& p, int64_t P, int x, in
 // ---------------------------------------------------------------------------
 // 4. projection and the local phase-field terms
 // ---------------------------------------------------------------------------
+// The mu / phi-local reverse of one cell: the adjoints of U^{n-1} (handed to
+// take_lu at once, which keeps them out of the registers of the rest), of mu^n
+// besides the direct term (mub), of phi^n from the local terms (p0b), and the
+// seed Rb of the gradient energy.  The active set of phi^n: from its 9/19-point
+// stencil (ACT 0), as recorded by the forward recomputation of the step in act,
+// the stencil read for interface cells only (1), or the stencil read at once and
+// act taken where given (2: one load latency less).
+template <int D, int N, int NC, class R, int ACT, class LU>
+__device__ __forceinline__ void adj_muphi_cell(const KP<R>& p, int64_t P, int x, int y, int z,
+                                               const R* __restrict__ phi0, const R* __restrict__ phi1,
+                                               const R* __restrict__ mu0, const R* __restrict__ mu1,
+                                               const R* __restrict__ u0, const R* __restrict__ w,
+                                               const R* __restrict__ lphi1, const R* __restrict__ t_phil,
+                                               const uint8_t* __restrict__ act, R tshift, LU&& take_lu, R (&mub)[NC],
+                                               R (&p0b)[N], R (&Rb)[N], double (&gpart)[NG]) {
+  R mubf[NC], lu[D], p1bf[N], p0bf[N];
+  mu_adj_cell<D, N, NC, R>(p, P, x, y, z, phi0, phi1, mu0, mu1, u0, w, tshift, mubf, lu, p1bf, p0bf, gpart);
+  take_lu(lu);
+  unsigned active = 0u;
+  R v[N][3][3][3];
+  if constexpr (ACT != 1) {
+    load_stencil<D, N, R>(p, phi0, x, y, z, v);
+    active = active_of<D, N, R>(v);
+  }
+  if (ACT == 1 || (ACT == 2 && act)) active = act[P];
+  R pb[N];
+#pragma unroll
+  for (int b = 0; b < N; ++b) pb[b] = lphi1[b * p.cells + P] + p1bf[b];
+  pb[N - 1] += t_phil[P];
+#pragma unroll
+  for (int b = 0; b < N; ++b) {
+    p0b[b] = p0bf[b];
+    Rb[b] = R(0);
+  }
+#pragma unroll
+  for (int i = 0; i < NC; ++i) mub[i] = mubf[i];
+  if (__builtin_popcount(active) <= 1) {
+#pragma unroll
+    for (int b = 0; b < N; ++b) p0b[b] += pb[b];
+  } else {
+    if constexpr (ACT == 1) load_stencil<D, N, R>(p, phi0, x, y, z, v);
+    R Rv[N], vv[N], out[N], theta, ms[NC];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) ms[i] = mu0[i * p.cells + P];
+    pf_rhs<D, N, NC, R, false>(p, v, ms, x, y, z, tshift, Rv);
+#pragma unroll
+    for (int b = 0; b < N; ++b) vv[b] = v[b][1][1][1] + p.rate * Rv[b];
+    project_masked<N, R>(active, vv, out, theta);
+    unsigned supp = 0u;
+    int ns = 0;
+    R mean = R(0);
+#pragma unroll
+    for (int b = 0; b < N; ++b)
+      if (((active >> b) & 1u) && vv[b] - theta > R(0)) {
+        supp |= 1u << b;
+        ++ns;
+        mean += pb[b];
+      }
+    mean = mean / R(ns);
+    R vb[N], taub = R(0);
+    const R rtau = -p.rate / p.tau_pf;
+#pragma unroll
+    for (int b = 0; b < N; ++b) {
+      vb[b] = ((supp >> b) & 1u) ? pb[b] - mean : R(0);
+      p0b[b] += vb[b];
+      Rb[b] = p.rate * vb[b];
+      taub += vb[b] * Rv[b] * rtau;
+    }
+    gpart[G_TAU] += (double)taub;
+    // local terms: -dW/dphi / eps and -sum psi dh/dphi
+    R ph[N], m[NC];
+#pragma unroll
+    for (int b = 0; b < N; ++b) ph[b] = v[b][1][1][1];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) m[i] = p.mu_ref[i] + mu0[i * p.cells + P];
+#pragma unroll
+    for (int al = 0; al < N; ++al)
+#pragma unroll
+      for (int be = 0; be < N; ++be) {
+        if (be == al) continue;
+        if (p.potential == 0) {
+          p0b[be] += -Rb[al] * R(1.6211389382774044) * p.gamma[al][be] * p.ieps;  // 16 / pi^2
+        } else {
+          p0b[al] += -Rb[al] * R(18) * p.gamma[al][be] * ph[be] * ph[be] * p.ieps;
+          p0b[be] += -Rb[al] * R(36) * p.gamma[al][be] * ph[al] * ph[be] * p.ieps;
+        }
+      }
+    const R tdev = (p.G != R(0)) ? p.G * (R((p.pull_axis == 0) ? x : (p.pull_axis == 1 ? y : z)) - tshift)
+                                 : p.tdev_iso;
+    R ps[N], C[N][NC];
+#pragma unroll
+    for (int b = 0; b < N; ++b) {
+      R r = R(0);
+#pragma unroll
+      for (int i = 0; i < NC; ++i) {
+        R chimu = R(0);
+#pragma unroll
+        for (int j = 0; j < NC; ++j) chimu += p.chi[i][j] * m[j];
+        r += -R(0.5) * m[i] * chimu - m[i] * (p.c0[b][i] + p.mT[b][i] * tdev);
+        C[b][i] = p.c0[b][i] + p.mT[b][i] * tdev + chimu;
+      }
+      ps[b] = r + p.dS[b] * tdev;
+    }
+#pragma unroll
+    for (int al = 0; al < N; ++al)
+#pragma unroll
+      for (int be = 0; be < N; ++be) {
+        const R d1 = dh<N, R>(ph, be, al);
+#pragma unroll
+        for (int i = 0; i < NC; ++i) mub[i] += Rb[al] * d1 * C[be][i];
+#pragma unroll
+        for (int g = 0; g < N; ++g) p0b[g] += -Rb[al] * ps[be] * d2h<N, R>(ph, be, al, g);
+      }
+  }
+}
+
 template <int D, int N, int NC, class R, bool ACT>
 __global__ void __launch_bounds__(ADJ_BLOCK)
 k_adj_muphi(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1,
@@ -550,112 +673,13 @@ k_adj_muphi(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1,
   int64_t P;
   int x, y, z;
   if (adj_cell(p.n, p.sy, p.sz, P, x, y, z)) {
-    R mubf[NC], Ubf[D], p1bf[N], p0bf[N];
-    mu_adj_cell<D, N, NC, R>(p, P, x, y, z, phi0, phi1, mu0, mu1, u0, w, tshift, mubf, Ubf, p1bf, p0bf, gpart);
+    R mub[NC], p0b[N], Rb[N];
+    auto store_lu = [&](const R(&lu)[D]) {
 #pragma unroll
-    for (int a = 0; a < D; ++a) lu0[a * p.cells + P] = Ubf[a];
-    // the active set of phi^n: recorded by the forward recomputation of the
-    // step (ACT), else from phi^n's 9/19-point stencil, which only the
-    // interface cells need otherwise
-    unsigned active = 0u;
-    R v[N][3][3][3];
-    if constexpr (ACT) {
-      active = act[P];
-    } else {
-      load_stencil<D, N, R>(p, phi0, x, y, z, v);
-      active = active_of<D, N, R>(v);
-    }
-    R pb[N];
-#pragma unroll
-    for (int b = 0; b < N; ++b) pb[b] = lphi1[b * p.cells + P] + p1bf[b];
-    pb[N - 1] += t_phil[P];
-    R p0b[N], Rb[N];
-#pragma unroll
-    for (int b = 0; b < N; ++b) {
-      p0b[b] = p0bf[b];
-      Rb[b] = R(0);
-    }
-    R mub[NC];
-#pragma unroll
-    for (int i = 0; i < NC; ++i) mub[i] = mubf[i];
-    if (__builtin_popcount(active) <= 1) {
-#pragma unroll
-      for (int b = 0; b < N; ++b) p0b[b] += pb[b];
-    } else {
-      if constexpr (ACT) load_stencil<D, N, R>(p, phi0, x, y, z, v);
-      R Rv[N], vv[N], out[N], theta, ms[NC];
-#pragma unroll
-      for (int i = 0; i < NC; ++i) ms[i] = mu0[i * p.cells + P];
-      pf_rhs<D, N, NC, R, false>(p, v, ms, x, y, z, tshift, Rv);
-#pragma unroll
-      for (int b = 0; b < N; ++b) vv[b] = v[b][1][1][1] + p.rate * Rv[b];
-      project_masked<N, R>(active, vv, out, theta);
-      unsigned supp = 0u;
-      int ns = 0;
-      R mean = R(0);
-#pragma unroll
-      for (int b = 0; b < N; ++b)
-        if (((active >> b) & 1u) && vv[b] - theta > R(0)) {
-          supp |= 1u << b;
-          ++ns;
-          mean += pb[b];
-        }
-      mean = mean / R(ns);
-      R vb[N], taub = R(0);
-      const R rtau = -p.rate / p.tau_pf;
-#pragma unroll
-      for (int b = 0; b < N; ++b) {
-        vb[b] = ((supp >> b) & 1u) ? pb[b] - mean : R(0);
-        p0b[b] += vb[b];
-        Rb[b] = p.rate * vb[b];
-        taub += vb[b] * Rv[b] * rtau;
-      }
-      gpart[G_TAU] += (double)taub;
-      // local terms: -dW/dphi / eps and -sum psi dh/dphi
-      R ph[N], m[NC];
-#pragma unroll
-      for (int b = 0; b < N; ++b) ph[b] = v[b][1][1][1];
-#pragma unroll
-      for (int i = 0; i < NC; ++i) m[i] = p.mu_ref[i] + mu0[i * p.cells + P];
-#pragma unroll
-      for (int al = 0; al < N; ++al)
-#pragma unroll
-        for (int be = 0; be < N; ++be) {
-          if (be == al) continue;
-          if (p.potential == 0) {
-            p0b[be] += -Rb[al] * R(1.6211389382774044) * p.gamma[al][be] * p.ieps;  // 16 / pi^2
-          } else {
-            p0b[al] += -Rb[al] * R(18) * p.gamma[al][be] * ph[be] * ph[be] * p.ieps;
-            p0b[be] += -Rb[al] * R(36) * p.gamma[al][be] * ph[al] * ph[be] * p.ieps;
-          }
-        }
-      const R tdev = (p.G != R(0)) ? p.G * (R((p.pull_axis == 0) ? x : (p.pull_axis == 1 ? y : z)) - tshift)
-                                   : p.tdev_iso;
-      R ps[N], C[N][NC];
-#pragma unroll
-      for (int b = 0; b < N; ++b) {
-        R r = R(0);
-#pragma unroll
-        for (int i = 0; i < NC; ++i) {
-          R chimu = R(0);
-#pragma unroll
-          for (int j = 0; j < NC; ++j) chimu += p.chi[i][j] * m[j];
-          r += -R(0.5) * m[i] * chimu - m[i] * (p.c0[b][i] + p.mT[b][i] * tdev);
-          C[b][i] = p.c0[b][i] + p.mT[b][i] * tdev + chimu;
-        }
-        ps[b] = r + p.dS[b] * tdev;
-      }
-#pragma unroll
-      for (int al = 0; al < N; ++al)
-#pragma unroll
-        for (int be = 0; be < N; ++be) {
-          const R d1 = dh<N, R>(ph, be, al);
-#pragma unroll
-          for (int i = 0; i < NC; ++i) mub[i] += Rb[al] * d1 * C[be][i];
-#pragma unroll
-          for (int g = 0; g < N; ++g) p0b[g] += -Rb[al] * ps[be] * d2h<N, R>(ph, be, al, g);
-        }
-    }
+      for (int a = 0; a < D; ++a) lu0[a * p.cells + P] = lu[a];
+    };
+    adj_muphi_cell<D, N, NC, R, ACT ? 1 : 0>(p, P, x, y, z, phi0, phi1, mu0, mu1, u0, w, lphi1, t_phil, act, tshift,
+                                             store_lu, mub, p0b, Rb, gpart);
 #pragma unroll
     for (int i = 0; i < NC; ++i) lmu0[i * p.cells + P] += mub[i];
     bool nz = false;
@@ -689,7 +713,7 @@ __device__ __forceinline__ bool owner_coord(int v, int n, int per, int& out) {
 // Jb[phase]: the adjoints pfb of the face value of phi and grb of its face
 // gradient, which give the contribution to the adjoint of phi at each role
 // cell (0 L, 1 R, then per tangential axis b in order: L-e_b, L+e_b, R-e_b,
-// R+e_b; face_store).  dd: derivative in delta (pairs with delta != 0).
+// R+e_b; face_values).  dd: derivative in delta (pairs with delta != 0).
 template <int D, int N, class R>
 __device__ __forceinline__ void face_vjp(const KP<R>& p, const R* __restrict__ phi, const int (&Lc)[3],
                                          int a, const R (&Jb)[N], R (&pfb)[N], R (&grb)[N][D], R& dd) {
@@ -779,20 +803,24 @@ __device__ __forceinline__ void face_vjp(const KP<R>& p, const R* __restrict__ p
 // 2N + b (D - 1) + t: the one at the roles along the t-th tangential axis,
 // with sign - at L-e, R-e and + at L+e, R+e.
 template <int D, int N, class R>
-__device__ __forceinline__ void face_store(const KP<R>& p, int a, const R (&pfb)[N], const R (&grb)[N][D],
-                                           R* __restrict__ fb, int64_t L) {
+__device__ __forceinline__ void face_values(const KP<R>& p, int a, const R (&pfb)[N], const R (&grb)[N][D],
+                                            R (&val)[N * (1 + D)]) {
   const R idx = R(1) / p.dx, ih2 = R(0.5) / p.dx;
 #pragma unroll
   for (int b = 0; b < N; ++b) {
-    fb[(int64_t)b * p.cells + L] = R(0.5) * pfb[b] - grb[b][a] * idx;
-    fb[(int64_t)(N + b) * p.cells + L] = R(0.5) * pfb[b] + grb[b][a] * idx;
+    R gn = R(0);
     int t = 0;
 #pragma unroll
     for (int e = 0; e < D; ++e) {
-      if (e == a) continue;
-      fb[(int64_t)(2 * N + b * (D - 1) + t) * p.cells + L] = R(0.5) * grb[b][e] * ih2;
+      if (e == a) {
+        gn = grb[b][e];
+        continue;
+      }
+      val[2 * N + b * (D - 1) + t] = R(0.5) * grb[b][e] * ih2;
       ++t;
     }
+    val[b] = R(0.5) * pfb[b] - gn * idx;
+    val[N + b] = R(0.5) * pfb[b] + gn * idx;
   }
 }
 // Contribution of face (a, L) to the adjoint of phi_b at its role cell r
@@ -807,7 +835,7 @@ __device__ __forceinline__ R face_role(const KP<R>& p, const R* __restrict__ fb,
 // Reverse of the cell-centre term at P seeded with cb = -eps Rbar(P): the
 // adjoints phb of phi at P and gcb of its central gradient, which give the
 // contribution at each role cell (0 P, then per axis b: P-e_b, P+e_b;
-// cell_store).
+// cell_values).
 template <int D, int N, class R>
 __device__ __forceinline__ void cell_vjp(const KP<R>& p, const R* __restrict__ phi, const int (&Pc)[3],
                                          const R (&cb)[N], R (&phb)[N], R (&gcb)[N][D], R& dd) {
@@ -871,14 +899,14 @@ __device__ __forceinline__ void cell_vjp(const KP<R>& p, const R* __restrict__ p
 // contribution to phi_b at role 0 (P), N + b D + e: the one at P+e_e (at
 // P-e_e with sign -).
 template <int D, int N, class R>
-__device__ __forceinline__ void cell_store(const KP<R>& p, const R (&phb)[N], const R (&gcb)[N][D],
-                                           R* __restrict__ cb, int64_t P) {
+__device__ __forceinline__ void cell_values(const KP<R>& p, const R (&phb)[N], const R (&gcb)[N][D],
+                                            R (&val)[N * (1 + D)]) {
   const R ih2 = R(0.5) / p.dx;
 #pragma unroll
   for (int b = 0; b < N; ++b) {
-    cb[(int64_t)b * p.cells + P] = phb[b];
+    val[b] = phb[b];
 #pragma unroll
-    for (int e = 0; e < D; ++e) cb[(int64_t)(N + b * D + e) * p.cells + P] = gcb[b][e] * ih2;
+    for (int e = 0; e < D; ++e) val[N + b * D + e] = gcb[b][e] * ih2;
   }
 }
 // Contribution of the cell term at P to the adjoint of phi_b at its role cell r
@@ -893,7 +921,7 @@ __device__ __forceinline__ R cell_role(const KP<R>& p, const R* __restrict__ cb,
 // 5a. Writer: every cell computes, once, the reverse of the face fluxes it
 // owns (its +e_a faces) and of its cell-centre term, and stores the N (1 + D)
 // values that give their contributions at the role cells: fbuf[a NFV + k][L],
-// cbuf[k][P] (face_store, cell_store).  Only entries with a non-zero seed are
+// cbuf[k][P] (face_values, cell_values).  Only entries with a non-zero seed are
 // written; fflag[a][L] / rflag[P] (written by k_adj_muphi) say which.
 template <int D, int N, int NC, class R>
 __global__ void __launch_bounds__(ADJ_BLOCK)
@@ -950,7 +978,10 @@ k_adj_vjp(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ rbar,
             R pfb[N], grb[N][D], dd;
             face_vjp<D, N, R>(p, phi0, Lc, a, Jb, pfb, grb, dd);
             dd_sum += dd;
-            face_store<D, N, R>(p, a, pfb, grb, fbuf + (int64_t)a * NFV * p.cells, L);
+            R val[NFV];
+            face_values<D, N, R>(p, a, pfb, grb, val);
+#pragma unroll
+            for (int k = 0; k < NFV; ++k) fbuf[((int64_t)a * NFV + k) * p.cells + L] = val[k];
             flag = 1;
           }
         }
@@ -964,7 +995,10 @@ k_adj_vjp(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ rbar,
       R phb[N], gcb[N][D], dd;
       cell_vjp<D, N, R>(p, phi0, Lc, cbv, phb, gcb, dd);
       dd_sum += dd;
-      cell_store<D, N, R>(p, phb, gcb, cbuf, L);
+      R val[NFV];
+      cell_values<D, N, R>(p, phb, gcb, val);
+#pragma unroll
+      for (int k = 0; k < NFV; ++k) cbuf[(int64_t)k * p.cells + L] = val[k];
     }
     gpart[G_DELTA] = (double)dd_sum;
   }
@@ -1320,11 +1354,188 @@ k_adj_phi2_lbm(KP<R> p, const uint8_t* __restrict__ rflag, const R* __restrict__
   } else {
     const unsigned blk = blockIdx.x - nb;
     double gpart[NG] = {0, 0, 0, 0, 0, 0};
-    if (adj_cell(p.n, p.sy, p.sz, P, xc[0], xc[1], xc[2], blk))
-      adj_lbm_cell<D, Q, N, NC, R, TAPE>(p, P, xc[0], xc[1], xc[2], fst, dr_t, u1, phi1, mu1, lf1, lu1, lmu1,
+    if (adj_cell(p.n, p.sy, p.sz, P, xc[0], xc[1], xc[2], blk)) {
+      R lu[D], lm[NC];
+#pragma unroll
+      for (int a = 0; a < D; ++a) lu[a] = lu1[a * p.cells + P];
+#pragma unroll
+      for (int i = 0; i < NC; ++i) lm[i] = lmu1[i * p.cells + P];
+      adj_lbm_cell<D, Q, N, NC, R, TAPE>(p, P, xc[0], xc[1], xc[2], fst, dr_t, u1, phi1, mu1, lf1, lu, lm,
                                          lf0, t_phil, w, lmu0, tshift1, gpart);
+    }
     block_partials(gpart, part, blk);
   }
+}
+
+// ---------------------------------------------------------------------------
+// One reverse step of a small 2D grid in one launch: k_adj_muphi, k_adj_vjp and
+// k_adj_phi2 of step n, then k_adj_lbm of step n - 1, whose inputs from step n
+// are the cell's own (and the populations' adjoint, which the launch before
+// wrote).  A block owns TX x TY cells; every thread computes the mu / phi-local
+// reverse of one cell of the tile widened by two, the threads of the tile
+// widened by one the reverse of their cell's face fluxes and cell term, and the
+// tile's threads gather.  t_w and t_phil take turns between two buffers: other
+// blocks still read step n's.  Bound by the latency of its chain (15 us at 256^2,
+// FP32): three dependent launches of 5 to 6 us and the gaps between them before
+// (24.6 us per step of a sweep, 20.7 now; 100^2: 21.1 and 14.9).  Not kept: the
+// faces along each axis, the cell terms and the LBM reverse on thread groups of
+// their own in wider blocks (an inversion of 100 steps 3.28 ms against 3.02); tiles
+// of 8 x 8 (3.22), 16 x 16 and 32 x 8 (3.04 to 3.08).
+// ---------------------------------------------------------------------------
+template <int TX, int TY> struct AdjTile {
+  static constexpr int EX = TX + 4, EY = TY + 4, NT = (EX * EY + 63) / 64 * 64;
+};
+template <class R> struct AdjStep {
+  // step n: X^n and X^{n+1}, the adjoint of X^{n+1} (lphi1) and what step n's LBM
+  // reverse left (w, phil, and in lmu0 the direct term)
+  const R *phi0, *phi1, *mu0, *mu1, *u0, *w, *lphi1, *phil;
+  R *lphi0, *lmu0, *lu0;
+  const uint8_t* act;  // active sets of phi^n, or null
+  // LBM reverse of step n - 1 (lf0 null: none): f* of X^{n-1} or rho - rho0 of
+  // the step, the populations' adjoints, and what it leaves for step n - 1
+  const R *fst, *dr, *lf1;
+  R *lf0, *phil_out, *w_out, *lmu_out;
+};
+
+template <int Q, int N, int NC, class R, int TX, int TY, bool TAPE>
+__global__ void __launch_bounds__((AdjTile<TX, TY>::NT))
+k_adj_step2(KP<R> p, AdjStep<R> s, R tshift, int tiles_x, double* __restrict__ part) {
+  constexpr int D = 2, EX = AdjTile<TX, TY>::EX, EY = AdjTile<TX, TY>::EY, NT = AdjTile<TX, TY>::NT;
+  constexpr int NFV = N * (1 + D), GX = TX + 2, GY = TY + 2;
+  __shared__ R sr[N][EX * EY];            // Rbar on the tile widened by two
+  __shared__ R sf[D + 1][NFV][GX * GY];   // face and cell values on the tile widened by one
+  const unsigned lb = xcd_block();
+  const int x0 = (int)(lb % (unsigned)tiles_x) * TX, y0 = (int)(lb / (unsigned)tiles_x) * TY;
+  const int tid = threadIdx.x;
+  const int ex = tid % EX - 2, ey = tid / EX - 2;  // in the tile
+  const bool on = tid < EX * EY;
+  // does the cell exist (periodic axes wrap), and where
+  int xc[3] = {0, 0, 0};
+  const bool ok = on && owner_coord(x0 + ex, p.n[0], p.per[0], xc[0]) && owner_coord(y0 + ey, p.n[1], p.per[1], xc[1]);
+  const int64_t P = (int64_t)xc[1] * p.sy + xc[0];
+  // the tile's own cells: those of the grid, each once
+  const bool own = ok && ex >= 0 && ex < TX && ey >= 0 && ey < TY && x0 + ex < p.n[0] && y0 + ey < p.n[1];
+  double gpart[NG] = {0, 0, 0, 0, 0, 0};
+  R p0b[N], Rb[N], lu[D], lm[NC];
+#pragma unroll
+  for (int b = 0; b < N; ++b) p0b[b] = Rb[b] = R(0);
+  if (ok) {
+    R mub[NC];
+    auto keep_lu = [&](const R(&v)[D]) {
+#pragma unroll
+      for (int a = 0; a < D; ++a) lu[a] = v[a];
+    };
+    adj_muphi_cell<D, N, NC, R, 2>(p, P, xc[0], xc[1], 0, s.phi0, s.phi1, s.mu0, s.mu1, s.u0, s.w, s.lphi1, s.phil,
+                                   s.act, tshift, keep_lu, mub, p0b, Rb, gpart);
+    if (own) {
+#pragma unroll
+      for (int i = 0; i < NC; ++i) {
+        lm[i] = s.lmu0[i * p.cells + P] + mub[i];
+        s.lmu0[i * p.cells + P] = lm[i];
+      }
+#pragma unroll
+      for (int a = 0; a < D; ++a) s.lu0[a * p.cells + P] = lu[a];
+    }
+  }
+  if (!own) {
+#pragma unroll
+    for (int i = 0; i < NG; ++i) gpart[i] = 0.0;
+  }
+  if (on)
+#pragma unroll
+    for (int b = 0; b < N; ++b) sr[b][tid] = Rb[b];
+  block_sync_lds();
+  // face fluxes and cell term owned by a cell of the tile widened by one
+  const bool wide = on && ex >= -1 && ex <= TX && ey >= -1 && ey <= TY;
+  const int gi = (ey + 1) * GX + ex + 1;
+  if (wide) {
+    R dd_sum = R(0);
+#pragma unroll
+    for (int a = 0; a <= D; ++a) {
+      R val[NFV];
+#pragma unroll
+      for (int k = 0; k < NFV; ++k) val[k] = R(0);
+      int t = 0;
+      if (ok && (a == D || owner_coord(xc[a] + 1, p.n[a], p.per[a], t))) {
+        R seed[N];
+        bool any = false;
+#pragma unroll
+        for (int b = 0; b < N; ++b) {
+          seed[b] = (a == D) ? -p.eps * Rb[b] : p.eps * (Rb[b] - sr[b][tid + (a == 0 ? 1 : EX)]) / p.dx;
+          any = any || seed[b] != R(0);
+        }
+        if (any) {
+          R v0[N], v1[N][D], dd;
+          if (a == D)
+            cell_vjp<D, N, R>(p, s.phi0, xc, seed, v0, v1, dd);
+          else
+            face_vjp<D, N, R>(p, s.phi0, xc, a, seed, v0, v1, dd);
+          dd_sum += dd;
+          if (a == D)
+            cell_values<D, N, R>(p, v0, v1, val);
+          else
+            face_values<D, N, R>(p, a, v0, v1, val);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < NFV; ++k) sf[a][k][gi] = val[k];
+    }
+    if (own) gpart[G_DELTA] = (double)dd_sum;
+  }
+  block_sync_lds();
+  if (own) {
+    // Roles that land on the cell: of the face along a of the cell itself and of
+    // the one before it along a; of those, the sideways roles +-e of their
+    // neighbours across e, and at a wall of e their own, which repeat the cell.
+    R acc[N];
+#pragma unroll
+    for (int b = 0; b < N; ++b) acc[b] = R(0);
+    bool in[D][2];  // the neighbour at -e, +e exists
+#pragma unroll
+    for (int e = 0; e < D; ++e) {
+      in[e][0] = p.per[e] || xc[e] > 0;
+      in[e][1] = p.per[e] || xc[e] + 1 < p.n[e];
+    }
+    const int st[2] = {1, GX};
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      const int e = 1 - a;
+#pragma unroll
+      for (int side = 0; side < 2; ++side) {
+        if (side && !in[a][0]) continue;
+        const int L = gi - (side ? st[a] : 0);
+#pragma unroll
+        for (int b = 0; b < N; ++b) {
+          acc[b] += sf[a][side * N + b][L];
+          // role -e of the owner at +e (or of the own face at the wall below), then role +e
+          acc[b] -= in[e][1] ? sf[a][2 * N + b][L + st[e]] : R(0);
+          acc[b] -= in[e][0] ? R(0) : sf[a][2 * N + b][L];
+          acc[b] += in[e][0] ? sf[a][2 * N + b][L - st[e]] : R(0);
+          acc[b] += in[e][1] ? R(0) : sf[a][2 * N + b][L];
+        }
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < N; ++b) {
+      acc[b] += sf[D][b][gi];
+#pragma unroll
+      for (int e = 0; e < D; ++e) {
+        acc[b] -= in[e][1] ? sf[D][N + b * D + e][gi + st[e]] : R(0);
+        acc[b] -= in[e][0] ? R(0) : sf[D][N + b * D + e][gi];
+        acc[b] += in[e][0] ? sf[D][N + b * D + e][gi - st[e]] : R(0);
+        acc[b] += in[e][1] ? R(0) : sf[D][N + b * D + e][gi];
+      }
+      s.lphi0[b * p.cells + P] = p0b[b] + acc[b];
+    }
+    if (s.lf0) {
+      double gl[NG] = {0, 0, 0, 0, 0, 0};
+      adj_lbm_cell<D, Q, N, NC, R, TAPE>(p, P, xc[0], xc[1], 0, s.fst, s.dr, s.u0, s.phi0, s.mu0, s.lf1, lu, lm, s.lf0,
+                                         s.phil_out, s.w_out, s.lmu_out, tshift, gl);
+#pragma unroll
+      for (int i = 0; i < NG; ++i) gpart[i] += gl[i];
+    }
+  }
+  block_partials<NT>(gpart, part);
 }
 
 // Sum the per-block running sums of the reverse sweep in a fixed order: each

@@ -91,7 +91,7 @@ struct gpf_ctx {
   hipStream_t side = nullptr;
   hipEvent_t ev_free[2] = {nullptr, nullptr}, ev_done[2] = {nullptr, nullptr};
   StateBuf lam[2];                 // adjoint state (phi, mu, U, post-streaming f)
-  DevBuf t_phil, t_w, t_rbar, t_part, t_acc, t_slices, t_rflag, t_fflag, t_fbuf, t_cbuf;
+  DevBuf t_phil, t_w, t_phil2, t_w2, t_rbar, t_part, t_acc, t_slices, t_rflag, t_fflag, t_fbuf, t_cbuf;
   DevBuf t_rowflag;                // per (y, z) row seed flags, two step parities
   int lam_cur = 0;                 // lam[lam_cur] holds the adjoint of the earliest state reached
   bool have_adjoint = false;
@@ -345,6 +345,8 @@ inline unsigned adj_blocks(const int64_t (&n)[3]) {
 #define GPF_2D_TY 8
 #define GPF_2DS_TX 32
 #define GPF_2DS_TY 4
+#define GPF_ADJ2_TX 16
+#define GPF_ADJ2_TY 8
 constexpr int phi_tx(int dim) { return dim == 3 ? GPF_PHI_TX : 64; }
 constexpr int phi_ty(int dim) { return dim == 3 ? GPF_PHI_TY : 4; }
 constexpr int phi_tz(int dim) { return dim == 3 ? GPF_PHI_TZ : 1; }
@@ -850,6 +852,26 @@ struct Impl {
     return {dim3(nb), dim3(gpf::ADJ_BLOCK), static_cast<double*>(c->t_part.ptr), (int64_t)nb * gpf::NG,
             static_cast<uint8_t*>(c->t_rflag.ptr), static_cast<uint8_t*>(c->t_fflag.ptr)};
   }
+  // One launch per reverse step (k_adj_step2, adj_step_2d) of two and three
+  // phases up to 768 KiB per component, but not of three without anisotropy.  us per
+  // step of a sweep with checkpoints every 20 steps, three launches and one:
+  // two phases 21.1 and 14.9 (100^2, FP32), 24.4 and 22.1 (300^2), 27.6 and 25.0
+  // (362^2), 34.7 and 37.6 (512^2); FP64 21.8 and 16.6 (100^2), 30.1 and 27.6
+  // (300^2), 35.6 and 37.2 (362^2); three phases 45.3 and 29.7 (256^2, FP32), and
+  // without anisotropy, where k_adj_phi_iso runs, 23.6 and 23.9; four phases 54.7
+  // and 38.5 (144 x 256, FP32), but 63.7 and 69.1 in FP64 (registers).  The limit
+  // lies where the work on the tiles' halo (70 % of the cells) outweighs the launches.
+  static bool adj_one_fits(const gpf_ctx* c) {
+    return D == 2 && N <= 3 && c->n[0] * c->n[1] * (int64_t)sizeof(R) <= 768 << 10;
+  }
+  static bool adj_one_launch(const gpf_ctx* c, const gpf::KP<R>& k) { return adj_one_fits(c) && (N == 2 || k.aniso); }
+  // rows of running sums, one per block: the LBM reverse, then the mu / phi-local
+  // and (up to D + 1 grids) VJP reverses, or adj_step_2d
+  static int64_t part_rows(const gpf_ctx* c) {
+    const int64_t nb = adj_blocks(c->n);
+    const int64_t t2 = ((c->n[0] + GPF_ADJ2_TX - 1) / GPF_ADJ2_TX) * ((c->n[1] + GPF_ADJ2_TY - 1) / GPF_ADJ2_TY);
+    return nb + std::max<int64_t>((D + 2) * nb, adj_one_fits(c) ? t2 : 0);
+  }
   // row seed flags of reverse step n (parity n mod 2)
   static uint8_t* rowflags(gpf_ctx* c, int64_t n) {
     return static_cast<uint8_t*>(c->t_rowflag.ptr) + (n & 1) * c->n[1] * c->n[2];
@@ -918,6 +940,30 @@ struct Impl {
                          P(lo.u), P(lo.mu), P(li.f), P(c->t_phil), P(c->t_w), P(li.mu), (R)tshift(c, n), a.part);
   }
 
+  // Reverse of step n (X^n -> X^{n+1}) on a small 2D grid in one launch, with the
+  // LBM reverse of step n - 1 (last: not).  x0, x1: X^n, X^{n+1}; xm: X^{n-1}; flip:
+  // which set of t_w / t_phil step n's LBM reverse wrote.
+  static void adj_step_2d(gpf_ctx* c, const gpf::KP<R>& k, int64_t n, const SP& xm, const SP& x0, const SP& x1,
+                          StateBuf& li, StateBuf& lo, const uint8_t* act, bool last, int flip) {
+    if constexpr (D == 2 && N <= 3) {
+      constexpr int TX = GPF_ADJ2_TX, TY = GPF_ADJ2_TY;
+      DevBuf* w[2] = {&c->t_w, &c->t_w2};
+      DevBuf* ph[2] = {&c->t_phil, &c->t_phil2};
+      const int tx = (int)((c->n[0] + TX - 1) / TX), ty = (int)((c->n[1] + TY - 1) / TY);
+      const gpf::AdjStep<R> s{x0.phi,     x1.phi,   x0.mu,   x1.mu, x0.u, P(*w[flip]),      P(li.phi),     P(*ph[flip]),
+                              P(lo.phi),  P(lo.mu), P(lo.u), act,   xm.f, x0.dr,            P(lo.f),
+                              last ? nullptr : P(li.f), P(*ph[1 - flip]), P(*w[1 - flip]), P(li.mu)};
+      const dim3 g((unsigned)tx * (unsigned)ty), b(gpf::AdjTile<TX, TY>::NT);
+      double* part = static_cast<double*>(c->t_part.ptr) + adj_launch(c).pstride;
+      if (x0.dr)
+        hipLaunchKernelGGL((gpf::k_adj_step2<Q, N, NC, R, TX, TY, true>), g, b, 0, c->stream, k, s, (R)tshift(c, n), tx,
+                           part);
+      else
+        hipLaunchKernelGGL((gpf::k_adj_step2<Q, N, NC, R, TX, TY, false>), g, b, 0, c->stream, k, s, (R)tshift(c, n), tx,
+                           part);
+    }
+  }
+
   // seed: dL/dphi at the current (final) state, FP64, N * cells values, in
   // host memory or (seed_on_device) device memory
   static int adjoint(gpf_ctx* c, const double* seed, bool seed_on_device, double* grads) {
@@ -931,12 +977,14 @@ struct Impl {
     int rc = GPF_OK;
     if (!c->lam[0].phi.ptr) {
       for (int i = 0; i < 2 && !rc; ++i) rc = alloc_state(c, c->lam[i]);
-      const unsigned nb = adj_blocks(c->n);
       if (!rc) rc = dev_alloc(c, c->t_phil, cs);
       if (!rc) rc = dev_alloc(c, c->t_w, NC * cs);
+      if (adj_one_fits(c)) {  // adj_step_2d's second set
+        if (!rc) rc = dev_alloc(c, c->t_phil2, cs);
+        if (!rc) rc = dev_alloc(c, c->t_w2, NC * cs);
+      }
       if (!rc) rc = dev_alloc(c, c->t_rbar, N * cs);
-      // running sums: the LBM, mu / phi-local and (up to D + 1 grids) VJP reverses
-      if (!rc) rc = dev_alloc(c, c->t_part, (size_t)(D + 3) * nb * gpf::NG * sizeof(double));
+      if (!rc) rc = dev_alloc(c, c->t_part, (size_t)part_rows(c) * gpf::NG * sizeof(double));
       if (!rc) rc = dev_alloc(c, c->t_acc, gpf::NG * sizeof(double));
       if (!rc) rc = dev_alloc(c, c->t_slices, (size_t)gpf::GA * gpf::NG * sizeof(double));
       if (!rc) rc = dev_alloc(c, c->t_rflag, (size_t)c->pcells);
@@ -1021,7 +1069,7 @@ struct Impl {
     // per-block running sums of the parameter derivatives over the sweep
     hipLaunchKernelGGL((gpf::k_fill<uint8_t>), dim3(lin_blocks(2 * c->n[1] * c->n[2], 256)), dim3(256), 0,
                        c->stream, static_cast<uint8_t*>(c->t_rowflag.ptr), 2 * c->n[1] * c->n[2], (uint8_t)0);
-    const int64_t nparts = (int64_t)(D + 3) * adj_blocks(c->n);
+    const int64_t nparts = part_rows(c);
     hipLaunchKernelGGL((gpf::k_fill<double>), dim3(lin_blocks(nparts * gpf::NG, 256)), dim3(256), 0, c->stream,
                        static_cast<double*>(c->t_part.ptr), nparts * gpf::NG, 0.0);
     // slot j of segment sg in tape b holds X^{n0 + j} (slot 0 is the
@@ -1052,14 +1100,17 @@ struct Impl {
       if (m == total) return cur(c, c->cur);
       return slot(tape_of(sg), sg, j);
     };
-    // On small grids the gather and the next LBM reverse share a launch, as
-    // two grids side by side (one kernel boundary less per step); on larger
-    // ones the combined kernel's registers (121, against 67 for the gather
-    // alone) cost more than the boundary.
-    const bool fuse = small_grid(c) && k.aniso;
+    // On small 2D grids a reverse step is one launch (adj_step_2d).  On other
+    // small grids the gather and the next LBM reverse share a launch, as two
+    // grids side by side (one kernel boundary less per step); on larger ones
+    // the combined kernel's registers (121, against 67 for the gather alone)
+    // cost more than the boundary.
+    const bool one = adj_one_launch(c, k);
+    const bool fuse = !one && small_grid(c) && k.aniso;
     for (int64_t j = 0; j < seg_len(nseg - 1) - 1; ++j) recompute_step(0, nseg - 1, j, c->stream);
     adj_lbm(c, k, c->rec_start + total - 1, state(total - 1), state(total), *li, *lo);
     int64_t nrec = 0, jr = 0;
+    int flip = 0;  // set of t_w / t_phil that the LBM reverse of step m wrote (adj_step_2d)
     for (int64_t m = total - 1; m >= 0; --m) {
       const int64_t sg = m / K, j = m % K;
       const int b = tape_of(sg);
@@ -1078,7 +1129,8 @@ struct Impl {
       // the active sets of step m were recorded unless its successor is a
       // checkpoint or the final state (the step was not recomputed)
       const uint8_t* act = (j < seg_len(sg) - 1) ? act_of(b, j) : nullptr;
-      adj_muphi_vjp(c, k, state(m), state(m + 1), c->rec_start + m, *li, *lo, act);
+      bool part_done = false;
+      if (!one) adj_muphi_vjp(c, k, state(m), state(m + 1), c->rec_start + m, *li, *lo, act);
       if (jr < nrec) recompute_step(1 - b, sg - 1, jr++, c->side);
       if (m > 0) {
         if (j == 0 && ntape == 2) {
@@ -1087,21 +1139,33 @@ struct Impl {
           HIP_OR_FAIL(c, hipEventRecord(c->ev_done[1 - b], c->side));
           HIP_OR_FAIL(c, hipStreamWaitEvent(c->stream, c->ev_done[1 - b], 0));
         } else if (j == 0) {
-          // one tape: the previous segment replaces this one, whose last
-          // reader (the reverse of step m) is already queued
+          // one tape: the previous segment replaces this one, once its last
+          // reader (the reverse of step m) is queued
+          if (one) {
+            adj_step_2d(c, k, c->rec_start + m, state(m), state(m), state(m + 1), *li, *lo, act, true, flip);
+            part_done = true;
+          }
           for (int64_t jj = 0; jj < K - 1; ++jj) recompute_step(0, sg - 1, jj, c->stream);
         }
-        if (fuse) {
+        if (part_done) {
+          adj_lbm(c, k, c->rec_start + m - 1, state(m - 1), state(m), *lo, *li);
+          flip = 1;  // (the next step's inputs are in the first set)
+        } else if (one) {
+          adj_step_2d(c, k, c->rec_start + m, state(m - 1), state(m), state(m + 1), *li, *lo, act, false, flip);
+        } else if (fuse) {
           adj_phi2_lbm(c, k, c->rec_start + m, state(m - 1), state(m), *lo, *li);
         } else {
           adj_phi2(c, k, c->rec_start + m, state(m), *lo);
           adj_lbm(c, k, c->rec_start + m - 1, state(m - 1), state(m), *lo, *li);
         }
+      } else if (one) {
+        adj_step_2d(c, k, c->rec_start + m, state(m), state(m), state(m + 1), *li, *lo, act, true, flip);
       } else {
         adj_phi2(c, k, c->rec_start + m, state(m), *lo);
       }
       HIP_OR_FAIL(c, hipGetLastError());
       std::swap(li, lo);
+      flip ^= 1;
     }
     hipLaunchKernelGGL(gpf::k_grad_slices, dim3(gpf::GA), dim3(gpf::ADJ_BLOCK), 0, c->stream,
                        static_cast<const double*>(c->t_part.ptr), nparts, static_cast<double*>(c->t_slices.ptr));
@@ -1372,6 +1436,8 @@ void free_all(gpf_ctx* c) {
   rel(c->lam[1]);
   dev_release(c, c->t_phil);
   dev_release(c, c->t_w);
+  dev_release(c, c->t_phil2);
+  dev_release(c, c->t_w2);
   dev_release(c, c->t_rbar);
   dev_release(c, c->t_part);
   dev_release(c, c->t_acc);
