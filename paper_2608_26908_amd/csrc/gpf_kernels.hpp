@@ -784,6 +784,12 @@ k_phi(KP<R> p, const R* __restrict__ phi, const R* __restrict__ mu, R* __restric
 // their lines within a CU: 629 -> 603 us on 256^3, 265 -> 246 on 250 x 200 x
 // 128, though 95 -> 109 on 128^3, where half of their lanes idle; in FP64 (1224
 // and 1228) and with more phases (176 and 178) they gain nothing.
+// Tiles of 32 x 4 x 2 where those of 64 columns leave at least a quarter of their
+// lanes without a cell (rows of up to 32 and of 65 to 96 cells); us per step with
+// 64 and with 32 columns: 49.1 and 45.8 (96^3, two phases, FP32), 83.8 and 78.8
+// (FP64), 48.8 and 44.7 (three phases), 23.9 and 18.1 (24 x 80 x 80), 47.1 and
+// 40.1 (66 x 70 x 60, FP64); but 107.6 and 110.4 on 150 x 131 x 117, where 64
+// leave 22 %.
 // LDS-shared slots of a tile: its T cells (slot = thread), then the halo of
 // each face: z-, z+ (TX x TY cells each), y-, y+ (TX x TZ), x-, x+ (TY x TZ).
 template <int D, int TX, int TY, int TZ> struct MuTile {

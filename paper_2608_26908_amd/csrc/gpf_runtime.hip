@@ -436,13 +436,21 @@ struct Impl {
       GPF_PHI(true);
 #undef GPF_PHI
     if (ev) (void)hipEventRecord(ev[1], st);
-    // tiles of whole 1 KiB rows where they fit (see k_mulbm)
-    bool wide = false;
-    if constexpr (D == 3 && N == 2 && sizeof(R) == 4) {
-      wide = c->n[0] % 256 == 0 || c->n[0] % 256 > 224;
-      if (wide) launch_mulbm<256, 2, 1>(c, k, in, out, ts, st, bulk_out, todo, nb);
-    }
-    if (!wide) launch_mulbm<GPF_MU_TX, GPF_MU_TY, (D == 3 ? GPF_MU_TZ : 1)>(c, k, in, out, ts, st, bulk_out, todo, nb);
+    // tiles of whole 1 KiB rows where they fit, and tiles of 32 columns where
+    // 64 leave a quarter of the lanes and more without a cell (see k_mulbm; a
+    // plane's offsets are 32-bit there)
+    bool done = false;
+    if constexpr (D == 3 && N == 2 && sizeof(R) == 4)
+      if (c->n[0] % 256 == 0 || c->n[0] % 256 > 224) {
+        launch_mulbm<256, 2, 1>(c, k, in, out, ts, st, bulk_out, todo, nb);
+        done = true;
+      }
+    if constexpr (D == 3)
+      if ((c->n[0] <= 32 || (c->n[0] > 64 && c->n[0] <= 96)) && k.sz <= (int64_t)1 << 28) {
+        launch_mulbm<32, GPF_MU_TY, GPF_MU_TZ>(c, k, in, out, ts, st, bulk_out, todo, nb);
+        done = true;
+      }
+    if (!done) launch_mulbm<GPF_MU_TX, GPF_MU_TY, (D == 3 ? GPF_MU_TZ : 1)>(c, k, in, out, ts, st, bulk_out, todo, nb);
     if (ev) (void)hipEventRecord(ev[2], st);
   }
 

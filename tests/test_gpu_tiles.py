@@ -38,6 +38,14 @@ def test_tile_edges(oracle, kind, n):
     _check(busy_config(kind, n), 2)
 
 
+@pytest.mark.parametrize("kind,n", [("binary3d", [32, 4, 2]), ("ternary3d_nc2", [33, 5, 3]), ("quaternary3d", [64, 3, 2]),
+                                    ("ternary3d_nc2", [96, 9, 5]), ("binary3d", [97, 4, 3])])
+def test_narrow_tiles(oracle, kind, n):
+    """rows of up to 32 and of 65 to 96 cells take tiles of 32 columns; one cell
+    to either side of the limits, in the walls' and the periodic directions"""
+    _check(busy_config(kind, n), 2)
+
+
 @pytest.mark.parametrize("n", [[65, 5, 3], [31, 34, 2]])
 def test_tile_edges_q27_shrinkage(oracle, n):
     """the 27-velocity lattice with walls on every axis, and the shrinkage
