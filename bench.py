@@ -336,7 +336,7 @@ def main():
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic,
-                     "kernel": "k_mulbm_z (chemical potential + LBM collide/stream, z-marching)",
+                     "kernel": "k_mulbm (chemical potential + LBM collide/stream)",
                      "bytes_per_lup": b32,
                      "step_frac": round(b32 * cells / (r32["ms_per_step"] * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                      "copy_GBps": round(copy_gbs, 1),

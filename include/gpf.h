@@ -235,9 +235,9 @@ int gpf_reduce_noalloc(gpf_ctx* ctx, int32_t which, double* dev_out);
  * that the access pattern of the population update reaches without its
  * arithmetic, the achievable side of the HBM roofline beside the published
  * peak.  pattern 0: copy of 19 FP32 arrays; 1: the D3Q19 pull out_k(P) =
- * in_k(P - c_k) (all axes periodic), one thread per cell; 2: the same pull in
- * the launch shape of the step's dominant kernel (64 x 4 tiles walking 4
- * planes).  dev_in, dev_out: caller-owned device buffers of 19 * n[0] * n[1]
+ * in_k(P - c_k) (all axes periodic), one thread per cell (as the step's
+ * dominant kernel reads); 2: the same pull by 64 x 4 tiles walking 4 planes.
+ * dev_in, dev_out: caller-owned device buffers of 19 * n[0] * n[1]
  * * n[2] floats each, layout [k][z][y][x]; out is overwritten with the copied
  * or pulled values.  n[0] a multiple of 64, n[1] and n[2] multiples of 4.
  * Two untimed launches, then `reps` launches timed with HIP events on
@@ -272,7 +272,9 @@ int gpf_set_param(gpf_ctx* ctx, const char* name, double value);
  *
  * gpf_record: the current state becomes checkpoint 0 of a recording; every
  * later gpf_step stores a full-state checkpoint each `checkpoint_every`
- * steps (device memory: (N + nc + dim + Q) * cells values per checkpoint;
+ * steps (device memory: (N + nc + dim + Q) * cells values per checkpoint, cells
+ * counted with rows of half a line and more padded to a multiple of 128 bytes;
+ * on large grids only where that adds at most an eighth;
  * gpf_adjoint adds a tape of checkpoint_every - 1 states of
  * (N + nc + dim + 1) * cells values, two population buffers and the adjoint
  * state; with more than one segment a second tape, into which the previous

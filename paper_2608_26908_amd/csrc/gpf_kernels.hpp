@@ -1355,7 +1355,10 @@ __global__ void k_derived(KP<R> p, int which, const R* __restrict__ phi, const R
 }
 
 // FP64 block partial sums in a fixed order: solute (NC values, which 0),
-// mass (which 1) or the loss 1/2 sum_a (phi_a - target_a)^2 (which 2).
+// mass (which 1) or the loss 1/2 sum_a (phi_a - target_a)^2 (which 2).  The mass
+// reads all populations: all of a cell's are loaded before the first is added
+// (us per call, added as each came and now: 449 and 270 on 256^3, FP32, 95 and 60
+// on 96^3, 27 velocities, FP64; some 25 of them are the host's).
 constexpr int RED_BLOCK = 256;
 template <int D, int Q, int N, int NC, class R>
 __global__ void __launch_bounds__(RED_BLOCK)
@@ -1388,9 +1391,11 @@ k_partial(KP<R> p, int which, const R* __restrict__ phi, const R* __restrict__ m
         acc[i] += c;
       }
     } else if (which == 1) {
+      R g[Q];
+      pull_cell<D, Q, true, STREAM, R>(p, f, pull_at<D, true, R>(p, x, y, z), g);
       double r = 0.0;
-      for (int k = 0; k < L::Q; ++k)
-        r += (double)pull_f<D, Q, R>(p, f, x, y, z, P, k) + L::w(k) * (double)p.rho0;
+#pragma unroll
+      for (int k = 0; k < L::Q; ++k) r += (double)g[k] + L::w(k) * (double)p.rho0;
       acc[0] += r;
     } else {
       double r = 0.0;

@@ -457,7 +457,7 @@ PROBES = {"copy19": 0, "pull19": 1, "pull19_zmarch": 2}
 def bandwidth_probe(pattern, n, reps=20, buffers=None):
     """Read + write GB/s of an access pattern of the population update
     without its arithmetic (gpf_bandwidth_probe): 'copy19', 'pull19' (one
-    thread per cell) or 'pull19_zmarch' (the dominant kernel's launch shape),
+    thread per cell) or 'pull19_zmarch' (64 x 4 tiles walking 4 planes),
     on an n[0] x n[1] x n[2] FP32 grid; buffers: (in, out) torch tensors of
     19 * cells floats each (allocated when None).  Returns (GB/s, in, out)."""
     import torch
