@@ -1141,18 +1141,21 @@ struct Impl {
       if (!one) adj_muphi_vjp(c, k, state(m), state(m + 1), c->rec_start + m, *li, *lo, act);
       if (jr < nrec) recompute_step(1 - b, sg - 1, jr++, c->side);
       if (m > 0) {
+        if (one && j == 0) {
+          // the LBM reverse of the segment before goes separately: with one tape
+          // that segment is not there yet, and with two the rest need not wait
+          // for it (the same launches either way, so the same bits)
+          adj_step_2d(c, k, c->rec_start + m, state(m), state(m), state(m + 1), *li, *lo, act, true, flip);
+          part_done = true;
+        }
         if (j == 0 && ntape == 2) {
           // step m - 1 lies in the previous segment: its tape must be complete
           while (jr < nrec) recompute_step(1 - b, sg - 1, jr++, c->side);
           HIP_OR_FAIL(c, hipEventRecord(c->ev_done[1 - b], c->side));
           HIP_OR_FAIL(c, hipStreamWaitEvent(c->stream, c->ev_done[1 - b], 0));
         } else if (j == 0) {
-          // one tape: the previous segment replaces this one, once its last
-          // reader (the reverse of step m) is queued
-          if (one) {
-            adj_step_2d(c, k, c->rec_start + m, state(m), state(m), state(m + 1), *li, *lo, act, true, flip);
-            part_done = true;
-          }
+          // one tape: the previous segment replaces this one, whose last
+          // reader (the reverse of step m) is already queued
           for (int64_t jj = 0; jj < K - 1; ++jj) recompute_step(0, sg - 1, jj, c->stream);
         }
         if (part_done) {

@@ -11,7 +11,7 @@ tests."""
 import numpy as np
 import pytest
 
-from gpu_helpers import gpu_from, oracle_from
+from gpu_helpers import STATE, gpu_from, oracle_from
 from inputs import busy_config, random_state
 
 pytestmark = pytest.mark.gpu
@@ -32,6 +32,39 @@ def test_dot_product_at_tile_edges(oracle, kind, n, periodic, steps, K):
 
 def test_dot_product_two_phases_without_anisotropy(oracle):
     _dot_product(oracle, busy_config("binary2d", [33, 17], delta=[[0, 0], [0, 0]]), 5, 3)
+
+
+def test_one_tape_bitwise():
+    """a second tape that does not fit: the segments' ends are reversed by the
+    same launches, so gradients and adjoint state keep their bits"""
+    cfg = busy_config("binary2d", [48, 40])
+    st = random_state(cfg, 5)
+    steps, K, names = 14, 4, ["delta", "tau_pf", "D"]
+    from paper_2608_26908_amd.gpf import Sim
+
+    def sim(**kw):
+        s = Sim(cfg, precision="fp64", **kw)
+        for k in STATE:
+            s.write(k, st[k])
+        return s
+
+    a = sim()
+    a.record(K)
+    a.step(steps)
+    seed = np.cos(np.arange(2 * 48 * 40)).reshape(a.read("phi").shape)
+    ga = a.adjoint(seed, names)
+    la = {f: a.adjoint_state(f) for f in ("phi", "mu", "u", "f")}
+    two = a.device_bytes
+    tape = ((K - 1) * (2 + 1 + 2 + 1) + 2 * 9) * 48 * 40 * 8
+    a.close()
+    b = sim(memory_limit=two - tape // 2)
+    b.record(K)
+    b.step(steps)
+    assert np.array_equal(ga, b.adjoint(seed, names))
+    assert b.device_bytes <= two - tape + 4096
+    for f in la:
+        assert np.array_equal(la[f], b.adjoint_state(f)), f
+    b.close()
 
 
 def _dot_product(oracle, cfg, steps, K):
