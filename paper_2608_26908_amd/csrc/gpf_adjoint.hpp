@@ -13,7 +13,8 @@
 //   k_adj_phi2  gather of the contributions they imply      -> lam phi^n
 //   (k_adj_phi_iso in place of these two when no pair is anisotropic)
 // k_adj_lbm of step n - 1 does not read lam phi^n, so k_adj_phi2_lbm runs it
-// in the same launch as the gather of step n (used on small grids).
+// in the same launch as the gather of step n (used on small grids), and on small
+// 2D grids k_adj_step2 runs all of these in one launch.
 // Every kernel gathers into the cells it owns: no atomics, deterministic.
 // Parameter derivatives are reduced per block in FP64 and summed in a fixed
 // order.  Hessian-vector products of the gradient energy come from forward

@@ -1,10 +1,11 @@
 // gpf_kernels.hpp -- HIP kernels of the coupled GP phase-field / LBM step.
 //
 // One step = two launches over tiles of cells:
-//   k_phi    phi^n, mu^n            -> phi^{n+1}          (Eq. PhfGrand, Sec. 2.1)
-//   k_mulbm    phi^n, phi^{n+1}, mu^n, U^{n-1}, f*^{n-1}
+//   k_phi    phi^n, mu^n              -> phi^{n+1}          (Eq. PhfGrand, Sec. 2.1)
+//   k_mulbm  phi^n, phi^{n+1}, mu^n, U^{n-1}, f*^{n-1}
 //                                     -> mu^{n+1}, U^n, f*^n (Eq. conc; Eqs. LBMEq_1,
 //                                        f^eq, discreteForce, buoyancy, rhovel)
+// or one, k_step2, on 2D grids of up to 3 MiB per component.
 // f buffers hold post-collision, pre-streaming populations as deviations
 // f - w_k rho0; streaming is a pull at the start of k_mulbm, with half-way
 // bounce-back where the source lies behind a wall.  All buffers are A-B:
@@ -13,7 +14,6 @@
 #include "gpf_device.hpp"
 
 namespace gpf {
-
 
 // Population k of f^n at cell (x, y, z) = P, as a deviation from w_k rho0:
 // pulled from the stored post-collision f* of the upstream cell P - c_k, or,
@@ -771,7 +771,7 @@ k_phi(KP<R> p, const R* __restrict__ phi, const R* __restrict__ mu, R* __restric
 // Threads past the grid's edge hold the wrapped (periodic) or clamped (wall)
 // cell, which only serves as a neighbour.
 // ---------------------------------------------------------------------------
-// HBM bound in 3D (FP32, 256^3: 195 B/cell moved of the 168 that the state
+// HBM bound in 3D (FP32, 256^3: 197 B/cell moved of the 168 that the state
 // needs), VALU issue beside it for three and four phases.  The form before
 // this one walked 64 x 4 columns plane by plane, held the next plane's values
 // in registers (127 to 186 of them, 2 to 4 waves per SIMD) and formed
