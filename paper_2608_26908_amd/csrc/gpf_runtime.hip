@@ -132,8 +132,10 @@ int dev_alloc(gpf_ctx* c, DevBuf& b, size_t bytes) {
     if (!p) return fail(c, GPF_ERR_NOMEM, "dev_alloc callback returned NULL for %zu bytes", bytes);
   } else {
     hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess)
+    if (e != hipSuccess) {
+      (void)hipGetLastError();  // else the next launch's check would report it
       return fail(c, GPF_ERR_NOMEM, "hipMalloc of %zu bytes failed: %s", bytes, hipGetErrorString(e));
+    }
   }
   b.ptr = p;
   b.bytes = bytes;
@@ -149,6 +151,38 @@ void dev_release(gpf_ctx* c, DevBuf& b) {
   }
   b.ptr = nullptr;
   b.bytes = 0;
+}
+
+void release_state(gpf_ctx* c, StateBuf& s) {
+  dev_release(c, s.phi);
+  dev_release(c, s.mu);
+  dev_release(c, s.u);
+  dev_release(c, s.f);
+  dev_release(c, s.dr);
+}
+
+// the buffer's memory, if it has none yet
+int dev_need(gpf_ctx* c, DevBuf& b, size_t bytes) { return b.ptr ? GPF_OK : dev_alloc(c, b, bytes); }
+
+// the fields of one full state, those that are not there yet
+int need_state(gpf_ctx* c, StateBuf& s) {
+  const size_t cs = (size_t)c->pcells * c->esize;
+  int rc = dev_need(c, s.phi, c->N * cs);
+  if (!rc) rc = dev_need(c, s.mu, c->nc * cs);
+  if (!rc) rc = dev_need(c, s.u, c->dim * cs);
+  if (!rc) rc = dev_need(c, s.f, c->Q * cs);
+  return rc;
+}
+
+// a checkpoint at the end of the recording; nothing is kept when it does not fit
+int push_ckpt(gpf_ctx* c) {
+  StateBuf s;
+  const int rc = need_state(c, s);
+  if (rc)
+    release_state(c, s);
+  else
+    c->ckpt.push_back(s);
+  return rc;
 }
 
 // ---------------------------------------------------------------------------
@@ -801,14 +835,6 @@ struct Impl {
   }
 
   // ---------------- adjoint ----------------
-  static int alloc_state(gpf_ctx* c, StateBuf& s) {
-    const size_t cs = (size_t)c->pcells * sizeof(R);
-    int rc = dev_alloc(c, s.phi, N * cs);
-    if (!rc) rc = dev_alloc(c, s.mu, NC * cs);
-    if (!rc) rc = dev_alloc(c, s.u, D * cs);
-    if (!rc) rc = dev_alloc(c, s.f, Q * cs);
-    return rc;
-  }
   static int copy_state(gpf_ctx* c, const StateBuf& dst, const StateBuf& src) {
     HIP_OR_FAIL(c, hipMemcpyAsync(dst.phi.ptr, src.phi.ptr, dst.phi.bytes, hipMemcpyDeviceToDevice, c->stream));
     HIP_OR_FAIL(c, hipMemcpyAsync(dst.mu.ptr, src.mu.ptr, dst.mu.bytes, hipMemcpyDeviceToDevice, c->stream));
@@ -823,12 +849,8 @@ struct Impl {
     if (c->step < c->rec_start || m > (int64_t)c->ckpt.size())
       return fail(c, GPF_ERR_STATE, "step %lld is outside the recording started at step %lld",
                   (long long)c->step, (long long)c->rec_start);
-    if (m == (int64_t)c->ckpt.size()) {
-      StateBuf s;
-      int rc = alloc_state(c, s);
-      if (rc) return rc;
-      c->ckpt.push_back(s);
-    }
+    if (m == (int64_t)c->ckpt.size())
+      if (int rc = push_ckpt(c)) return rc;
     StateBuf& s = c->ckpt[m];
     StateBuf cur_s;
     cur_s.phi = c->phi[c->cur];
@@ -981,29 +1003,35 @@ struct Impl {
       return fail(c, GPF_ERR_STATE, "nothing recorded: call gpf_record before stepping");
     if (c->n[0] * ((c->n[1] + 7) / 8) * c->n[2] >= ((int64_t)1 << 31))
       return fail(c, GPF_ERR_UNSUPPORTED, "grid too large for the adjoint's 32-bit cell slots");
-    const size_t cs = (size_t)c->pcells * sizeof(R);
-    int rc = GPF_OK;
-    if (!c->lam[0].phi.ptr) {
-      for (int i = 0; i < 2 && !rc; ++i) rc = alloc_state(c, c->lam[i]);
-      if (!rc) rc = dev_alloc(c, c->t_phil, cs);
-      if (!rc) rc = dev_alloc(c, c->t_w, NC * cs);
-      if (adj_one_fits(c)) {  // adj_step_2d's second set
-        if (!rc) rc = dev_alloc(c, c->t_phil2, cs);
-        if (!rc) rc = dev_alloc(c, c->t_w2, NC * cs);
-      }
-      if (!rc) rc = dev_alloc(c, c->t_rbar, N * cs);
-      if (!rc) rc = dev_alloc(c, c->t_part, (size_t)part_rows(c) * gpf::NG * sizeof(double));
-      if (!rc) rc = dev_alloc(c, c->t_acc, gpf::NG * sizeof(double));
-      if (!rc) rc = dev_alloc(c, c->t_slices, (size_t)gpf::GA * gpf::NG * sizeof(double));
-      if (!rc) rc = dev_alloc(c, c->t_rflag, (size_t)c->pcells);
-      if (!rc) rc = dev_alloc(c, c->t_rowflag, (size_t)2 * c->n[1] * c->n[2]);
-      if (!rc) rc = dev_alloc(c, c->t_fflag, (size_t)D * c->pcells);
-      // reverse of the face fluxes and cell terms: N (1 + D) values per face / cell
-      if (!rc) rc = dev_alloc(c, c->t_fbuf, (size_t)D * N * (1 + D) * cs);
-      if (!rc) rc = dev_alloc(c, c->t_cbuf, (size_t)N * (1 + D) * cs);
-      if (rc) return rc;
-    }
+    // segment sg starts from checkpoint sg (missing where one did not fit)
     const int64_t nseg = (total + K - 1) / K;
+    if (nseg > (int64_t)c->ckpt.size())
+      return fail(c, GPF_ERR_STATE, "the recording holds %lld of the %lld checkpoints that the steps need",
+                  (long long)c->ckpt.size(), (long long)nseg);
+    const size_t cs = (size_t)c->pcells * sizeof(R);
+    // each buffer by itself: an earlier call may have failed between them
+    int rc = GPF_OK;
+    auto need = [&](DevBuf& b, size_t bytes) {
+      if (!rc) rc = dev_need(c, b, bytes);
+    };
+    for (int i = 0; i < 2 && !rc; ++i) rc = need_state(c, c->lam[i]);
+    need(c->t_phil, cs);
+    need(c->t_w, NC * cs);
+    if (adj_one_fits(c)) {  // adj_step_2d's second set
+      need(c->t_phil2, cs);
+      need(c->t_w2, NC * cs);
+    }
+    need(c->t_rbar, N * cs);
+    need(c->t_part, (size_t)part_rows(c) * gpf::NG * sizeof(double));
+    need(c->t_acc, gpf::NG * sizeof(double));
+    need(c->t_slices, (size_t)gpf::GA * gpf::NG * sizeof(double));
+    need(c->t_rflag, (size_t)c->pcells);
+    need(c->t_rowflag, (size_t)2 * c->n[1] * c->n[2]);
+    need(c->t_fflag, (size_t)D * c->pcells);
+    // reverse of the face fluxes and cell terms: N (1 + D) values per face / cell
+    need(c->t_fbuf, (size_t)D * N * (1 + D) * cs);
+    need(c->t_cbuf, (size_t)N * (1 + D) * cs);
+    if (rc) return rc;
     auto alloc_tape = [&](int b) -> int {
       while ((int64_t)c->tape[b].size() < K - 1) {
         StateBuf s;
@@ -1012,9 +1040,7 @@ struct Impl {
         if (!r) r = dev_alloc(c, s.u, D * cs);
         if (!r) r = dev_alloc(c, s.dr, cs);
         if (r) {
-          dev_release(c, s.phi);
-          dev_release(c, s.mu);
-          dev_release(c, s.u);
+          release_state(c, s);
           return r;
         }
         c->tape[b].push_back(s);
@@ -1039,17 +1065,11 @@ struct Impl {
       if (alloc_tape(1) == GPF_OK) {
         ntape = 2;
       } else {
-        for (auto& st : c->tape[1]) {
-          dev_release(c, st.phi);
-          dev_release(c, st.mu);
-          dev_release(c, st.u);
-          dev_release(c, st.dr);
-        }
+        for (auto& st : c->tape[1]) release_state(c, st);
         c->tape[1].clear();
         dev_release(c, c->tape_f[1][0]);
         dev_release(c, c->tape_f[1][1]);
         dev_release(c, c->tape_act[1]);
-        (void)hipGetLastError();  // a failed hipMalloc leaves its error behind
         c->err.clear();
       }
     }
@@ -1417,22 +1437,15 @@ void free_all(gpf_ctx* c) {
   dev_release(c, c->bulkf[1]);
   dev_release(c, c->tlist);
   dev_release(c, c->tcount);
-  auto rel = [&](StateBuf& s) {
-    dev_release(c, s.phi);
-    dev_release(c, s.mu);
-    dev_release(c, s.u);
-    dev_release(c, s.f);
-    dev_release(c, s.dr);
-  };
   if (c->side) {
     (void)hipStreamSynchronize(c->side);
     (void)hipStreamDestroy(c->side);
     c->side = nullptr;
   }
-  for (auto& s : c->ckpt) rel(s);
+  for (auto& s : c->ckpt) release_state(c, s);
   c->ckpt.clear();
   for (int b = 0; b < 2; ++b) {
-    for (auto& s : c->tape[b]) rel(s);
+    for (auto& s : c->tape[b]) release_state(c, s);
     c->tape[b].clear();
     dev_release(c, c->tape_f[b][0]);
     dev_release(c, c->tape_f[b][1]);
@@ -1443,8 +1456,8 @@ void free_all(gpf_ctx* c) {
     if (c->ev_done[b]) (void)hipEventDestroy(c->ev_done[b]);
     c->ev_free[b] = c->ev_done[b] = nullptr;
   }
-  rel(c->lam[0]);
-  rel(c->lam[1]);
+  release_state(c, c->lam[0]);
+  release_state(c, c->lam[1]);
   dev_release(c, c->t_phil);
   dev_release(c, c->t_w);
   dev_release(c, c->t_phil2);
@@ -1724,37 +1737,24 @@ int gpf_record(gpf_ctx* c, int64_t checkpoint_every) {
   if (!c) return GPF_ERR_ARG;
   if (checkpoint_every < 1) return fail(c, GPF_ERR_ARG, "checkpoint_every must be >= 1");
   (void)hipStreamSynchronize(c->stream);
-  auto rel = [&](StateBuf& s) {
-    dev_release(c, s.phi);
-    dev_release(c, s.mu);
-    dev_release(c, s.u);
-    dev_release(c, s.f);
-    dev_release(c, s.dr);
-  };
-  for (auto& s : c->ckpt) rel(s);
+  for (auto& s : c->ckpt) release_state(c, s);
   c->ckpt.clear();
   for (int b = 0; b < 2; ++b)
     if ((int64_t)c->tape[b].size() > checkpoint_every) {
-      for (auto& s : c->tape[b]) rel(s);
+      for (auto& s : c->tape[b]) release_state(c, s);
       c->tape[b].clear();
     }
   c->rec_every = checkpoint_every;
   c->rec_start = c->step;
   c->have_adjoint = false;
-  StateBuf s;
-  const size_t cs = (size_t)c->pcells * c->esize;
-  int rc = dev_alloc(c, s.phi, c->N * cs);
-  if (!rc) rc = dev_alloc(c, s.mu, c->nc * cs);
-  if (!rc) rc = dev_alloc(c, s.u, c->dim * cs);
-  if (!rc) rc = dev_alloc(c, s.f, c->Q * cs);
+  int rc = push_ckpt(c);
   if (rc) return rc;
-  c->ckpt.push_back(s);
   StateBuf cur_s;
   cur_s.phi = c->phi[c->cur];
   cur_s.mu = c->mu[c->cur];
   cur_s.u = c->u[c->cur];
   cur_s.f = c->f[c->cur];
-  rc = c->ops->copy_state(c, s, cur_s);
+  rc = c->ops->copy_state(c, c->ckpt[0], cur_s);
   if (rc) return rc;
   HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));
   return GPF_OK;
