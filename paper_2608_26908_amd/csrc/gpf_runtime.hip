@@ -1009,7 +1009,11 @@ struct Impl {
       return fail(c, GPF_ERR_STATE, "the recording holds %lld of the %lld checkpoints that the steps need",
                   (long long)c->ckpt.size(), (long long)nseg);
     const size_t cs = (size_t)c->pcells * sizeof(R);
-    // each buffer by itself: an earlier call may have failed between them
+    gpf::KP<R> k = make_kp<R>(c);
+    // On small 2D grids a reverse step is one launch (adj_step_2d).
+    const bool one = adj_one_launch(c, k);
+    // What this sweep's kernels use, each buffer by itself: an earlier call may
+    // have failed between them, or run other kernels.
     int rc = GPF_OK;
     auto need = [&](DevBuf& b, size_t bytes) {
       if (!rc) rc = dev_need(c, b, bytes);
@@ -1017,20 +1021,23 @@ struct Impl {
     for (int i = 0; i < 2 && !rc; ++i) rc = need_state(c, c->lam[i]);
     need(c->t_phil, cs);
     need(c->t_w, NC * cs);
-    if (adj_one_fits(c)) {  // adj_step_2d's second set
-      need(c->t_phil2, cs);
-      need(c->t_w2, NC * cs);
-    }
-    need(c->t_rbar, N * cs);
     need(c->t_part, (size_t)part_rows(c) * gpf::NG * sizeof(double));
     need(c->t_acc, gpf::NG * sizeof(double));
     need(c->t_slices, (size_t)gpf::GA * gpf::NG * sizeof(double));
-    need(c->t_rflag, (size_t)c->pcells);
-    need(c->t_rowflag, (size_t)2 * c->n[1] * c->n[2]);
-    need(c->t_fflag, (size_t)D * c->pcells);
-    // reverse of the face fluxes and cell terms: N (1 + D) values per face / cell
-    need(c->t_fbuf, (size_t)D * N * (1 + D) * cs);
-    need(c->t_cbuf, (size_t)N * (1 + D) * cs);
+    if (one) {  // its second set
+      need(c->t_phil2, cs);
+      need(c->t_w2, NC * cs);
+    } else {
+      need(c->t_rbar, N * cs);
+      need(c->t_rflag, (size_t)c->pcells);
+      need(c->t_rowflag, (size_t)2 * c->n[1] * c->n[2]);
+    }
+    if (!one && k.aniso) {
+      // reverse of the face fluxes and cell terms: N (1 + D) values per face / cell
+      need(c->t_fflag, (size_t)D * c->pcells);
+      need(c->t_fbuf, (size_t)D * N * (1 + D) * cs);
+      need(c->t_cbuf, (size_t)N * (1 + D) * cs);
+    }
     if (rc) return rc;
     auto alloc_tape = [&](int b) -> int {
       while ((int64_t)c->tape[b].size() < K - 1) {
@@ -1080,7 +1087,6 @@ struct Impl {
         HIP_OR_FAIL(c, hipEventCreateWithFlags(&c->ev_done[b], hipEventDisableTiming));
       }
     }
-    gpf::KP<R> k = make_kp<R>(c);
     // lam^N = (seed, 0, 0, 0)
     StateBuf* li = &c->lam[0];
     StateBuf* lo = &c->lam[1];
@@ -1094,9 +1100,10 @@ struct Impl {
     fill(c, li->f, Q * c->pcells);
     hipLaunchKernelGGL((gpf::k_fill<double>), dim3(1), dim3(gpf::NG), 0, c->stream,
                        static_cast<double*>(c->t_acc.ptr), (int64_t)gpf::NG, 0.0);
+    if (!one)
+      hipLaunchKernelGGL((gpf::k_fill<uint8_t>), dim3(lin_blocks(2 * c->n[1] * c->n[2], 256)), dim3(256), 0,
+                         c->stream, static_cast<uint8_t*>(c->t_rowflag.ptr), 2 * c->n[1] * c->n[2], (uint8_t)0);
     // per-block running sums of the parameter derivatives over the sweep
-    hipLaunchKernelGGL((gpf::k_fill<uint8_t>), dim3(lin_blocks(2 * c->n[1] * c->n[2], 256)), dim3(256), 0,
-                       c->stream, static_cast<uint8_t*>(c->t_rowflag.ptr), 2 * c->n[1] * c->n[2], (uint8_t)0);
     const int64_t nparts = part_rows(c);
     hipLaunchKernelGGL((gpf::k_fill<double>), dim3(lin_blocks(nparts * gpf::NG, 256)), dim3(256), 0, c->stream,
                        static_cast<double*>(c->t_part.ptr), nparts * gpf::NG, 0.0);
@@ -1128,12 +1135,10 @@ struct Impl {
       if (m == total) return cur(c, c->cur);
       return slot(tape_of(sg), sg, j);
     };
-    // On small 2D grids a reverse step is one launch (adj_step_2d).  On other
-    // small grids the gather and the next LBM reverse share a launch, as two
-    // grids side by side (one kernel boundary less per step); on larger ones
-    // the combined kernel's registers (121, against 67 for the gather alone)
-    // cost more than the boundary.
-    const bool one = adj_one_launch(c, k);
+    // On small grids that are not of that kind the gather and the next LBM
+    // reverse share a launch, as two grids side by side (one kernel boundary less
+    // per step); on larger ones the combined kernel's registers (121, against 67
+    // for the gather alone) cost more than the boundary.
     const bool fuse = !one && small_grid(c) && k.aniso;
     for (int64_t j = 0; j < seg_len(nseg - 1) - 1; ++j) recompute_step(0, nseg - 1, j, c->stream);
     adj_lbm(c, k, c->rec_start + total - 1, state(total - 1), state(total), *li, *lo);

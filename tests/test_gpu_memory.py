@@ -102,3 +102,29 @@ def test_failed_checkpoint():
         s.adjoint(np.ones((2, 10, 48)), ["D"])
     assert e.value.code == -6
     s.close()
+
+
+@pytest.mark.parametrize("kind,n,over", [
+    ("ternary3d_nc2", [32, 24, 20], dict(delta=[[0] * 3] * 3)),  # three dimensions without anisotropy
+    ("binary2d", [160, 64], {}),                                 # a 2D reverse step in one launch
+])
+def test_sweep_holds_what_it_uses(kind, n, over):
+    """without anisotropy, and in the one-launch reverse step, no values per
+    face are stored, so no memory is held for them"""
+    cfg, K = busy_config(kind, n, **over), 3
+    D, N, nc, Q = cfg["dim"], cfg["N"], cfg["nc"], 9 if cfg["dim"] == 2 else 19
+    s = _sim(cfg, "fp32")
+    s.record(K)
+    s.step(2 * K - 1)
+    before = s.device_bytes
+    s.adjoint(np.ones([N] + n[::-1]), ["D"])
+    # values per cell: two adjoint states, what the LBM reverse leaves (twice in one launch) and the seeds; two tapes
+    # of K - 1 states and two sets of populations
+    comps = 2 * (N + nc + D + Q) + (2 * (1 + nc) if D == 2 else 1 + nc + N) + 2 * ((K - 1) * (N + nc + D + 1) + 2 * Q)
+    cells = int(np.prod(n))
+    # bytes per cell: seed flags and the tapes' active sets; running sums of the gradients, 48 bytes per 256 cells and
+    # kernel (D + 3 of them), or per 128, in 8 parts rounded up each, and 256 slices
+    flags = (1 if D == 3 else 0) + 2 * (K - 1)
+    sums = 48 * ((D + 3) * (cells / 256 + 8) + cells / 128 + 64 + 257) + 2 * n[1] * (n[2] if D == 3 else 1)
+    assert s.device_bytes - before <= 4 * comps * cells + flags * cells + sums
+    s.close()
