@@ -274,7 +274,10 @@ int gpf_set_param(gpf_ctx* ctx, const char* name, double value);
  * later gpf_step stores a full-state checkpoint each `checkpoint_every`
  * steps (device memory: (N + nc + dim + Q) * cells values per checkpoint, cells
  * counted with rows of half a line and more padded to a multiple of 128 bytes;
- * on large grids only where that adds at most an eighth;
+ * on large grids only where that adds at most an eighth, and no longer, for
+ * the context's whole state, once an allocation has failed: what fits with
+ * rows as they come fits, unless the caller has captured the context's work
+ * into a graph, which holds the padded buffers;
  * gpf_adjoint adds a tape of checkpoint_every - 1 states of
  * (N + nc + dim + 1) * cells values, two population buffers and the adjoint
  * state; with more than one segment a second tape, into which the previous
@@ -297,7 +300,7 @@ int gpf_set_param(gpf_ctx* ctx, const char* name, double value);
  * The forward state is left unchanged.  Parameter derivatives are
  * accumulated in FP64 in a fixed order; the adjoint fields have the
  * context's precision.  Synchronises.  Errors: GPF_ERR_STATE (nothing
- * recorded), GPF_ERR_ARG (count, unknown name, more than 6 names),
+ * recorded, or a checkpoint that the steps need did not fit), GPF_ERR_ARG (count, unknown name, more than 6 names),
  * GPF_ERR_UNSUPPORTED (shrinkage force on: eta != 0, or a moving frame),
  * GPF_ERR_NOMEM.
  *

@@ -1305,12 +1305,12 @@ __global__ void k_pack(KP<R> p, const T* __restrict__ in, R* __restrict__ out, i
     out[k * p.cells + P] = (R)v;
   }
 }
-// derived per-cell fields in FP64: 0 rho, 1 mixture composition C (nc comps),
-// 2 temperature, 3 active-set bitmask
+// derived per-cell fields in FP64: 0 rho (out may be fgathered: a cell's sum goes
+// over its own first population), 1 mixture composition C (nc comps), 2
+// temperature, 3 active-set bitmask
 template <int D, int Q, int N, int NC, class R>
 __global__ void k_derived(KP<R> p, int which, const R* __restrict__ phi, const R* __restrict__ mu,
-                          const double* __restrict__ fgathered, double tshift_d,
-                          double* __restrict__ out) {
+                          const double* fgathered, double tshift_d, double* out) {
   using L = Lat<Q>;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   int64_t P;

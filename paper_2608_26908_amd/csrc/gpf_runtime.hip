@@ -50,14 +50,17 @@ struct gpf_ctx {
   int64_t n[3] = {1, 1, 1};
   int64_t cells = 0;
   // stored rows (elements) and stored elements per component of the state:
-  // see row_pitch
+  // row_pitch's, or n[0] once memory ran out (try_dense); pinned: a caller's
+  // capture holds the buffers' addresses, so the rows stay as they are; lost:
+  // memory ran out while the rows were moved, the state is gone
   int64_t pitch = 0, pcells = 0;
+  bool pinned = false, lost = false;
   size_t esize = 8;  // bytes per stored value
   hipStream_t stream = nullptr;
   DevBuf phi[2], mu[2], u[2], f[2];
   int cur = 0;  // index of the buffers holding step `step`
   int64_t step = 0;
-  DevBuf scratch;   // FP64 staging for read / write (components * cells doubles)
+  DevBuf scratch;   // FP64 staging for read / write (Q * cells doubles)
   DevBuf partial;   // reduction partials
   DevBuf redout;    // final reduction values
   DevBuf badstep;   // health: smallest failing step
@@ -174,15 +177,9 @@ int need_state(gpf_ctx* c, StateBuf& s) {
   return rc;
 }
 
-// a checkpoint at the end of the recording; nothing is kept when it does not fit
-int push_ckpt(gpf_ctx* c) {
-  StateBuf s;
-  const int rc = need_state(c, s);
-  if (rc)
-    release_state(c, s);
-  else
-    c->ckpt.push_back(s);
-  return rc;
+void set_pitch(gpf_ctx* c, int64_t pitch) {
+  c->pitch = pitch;
+  c->pcells = pitch * c->n[1] * c->n[2];
 }
 
 // ---------------------------------------------------------------------------
@@ -193,7 +190,8 @@ int push_ckpt(gpf_ctx* c) {
 // of a width that is no multiple of a line leave the chip as partial lines
 // (255 x 256 x 128, FP32: k_mulbm took 560 us, 256 x 256 x 128 took 317; with
 // cached stores 427).  Rows shorter than half a line stay as they are, and so
-// do large grids whose memory would grow by more than an eighth.
+// do large grids whose memory would grow by more than an eighth.  Where memory
+// runs out the padding is given up (try_dense).
 int64_t row_pitch(int64_t n0, int64_t cells, size_t esize) {
   const int64_t line = 128 / (int64_t)esize, p = (n0 + line - 1) / line * line;
   if (p > 2 * n0 || (cells > ((int64_t)1 << 24) && 8 * p > 9 * n0)) return n0;
@@ -322,7 +320,55 @@ struct Ops {
   int (*adjoint)(gpf_ctx*, const double*, bool, double*);  // seed, seed in device memory, grads
   int (*copy_state)(gpf_ctx*, const StateBuf&, const StateBuf&);
   int (*lam_read)(gpf_ctx*, int, double*);
+  int (*to_dense)(gpf_ctx*);
 };
+
+// Runs `alloc`; if memory runs out while rows are padded, gives the padding up
+// and runs it again: a context, a recording or a sweep that fits with rows as
+// they come fits.
+template <class F> int try_dense(gpf_ctx* c, F&& alloc) {
+  int rc = alloc();
+  if (rc != GPF_ERR_NOMEM || c->pitch == c->n[0] || c->pinned) return rc;
+  if ((rc = c->ops->to_dense(c))) return rc;
+  rc = alloc();
+  if (!rc) c->err.clear();
+  return rc;
+}
+
+// a checkpoint at the end of the recording; nothing is kept when it does not fit
+int push_ckpt(gpf_ctx* c) {
+  return try_dense(c, [c] {
+    StateBuf s;
+    const int rc = need_state(c, s);
+    if (rc)
+      release_state(c, s);
+    else
+      c->ckpt.push_back(s);
+    return rc;
+  });
+}
+
+// What a sweep allocates besides the two adjoint states; a sweep that finds
+// one missing allocates it again.
+void release_sweep(gpf_ctx* c) {
+  for (int b = 0; b < 2; ++b) {
+    for (auto& s : c->tape[b]) release_state(c, s);
+    c->tape[b].clear();
+    dev_release(c, c->tape_f[b][0]);
+    dev_release(c, c->tape_f[b][1]);
+    dev_release(c, c->tape_act[b]);
+  }
+  for (DevBuf* b : {&c->t_phil, &c->t_w, &c->t_phil2, &c->t_w2, &c->t_rbar, &c->t_part, &c->t_acc, &c->t_slices,
+                    &c->t_rflag, &c->t_rowflag, &c->t_fflag, &c->t_fbuf, &c->t_cbuf})
+    dev_release(c, *b);
+}
+
+void drop_graphs(gpf_ctx* c) {
+  for (int b = 0; b < 2; ++b) {
+    if (c->gexec[b]) (void)hipGraphExecDestroy(c->gexec[b]);
+    c->gexec[b] = nullptr;
+  }
+}
 
 inline unsigned lin_blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 // blocks of the partial-sum kernel of the FP64 totals: at most kRedBlocks
@@ -516,7 +562,11 @@ struct Impl {
   // 2D grids whose step is one launch (k_step2): up to 3 MiB per component,
   // between the 2 MiB (1024 x 512 in FP32) where it is the faster form and the
   // 4 MiB (the same in FP64) where it is not
-  static bool fused_2d(const gpf_ctx* c) { return D == 2 && c->pcells * (int64_t)sizeof(R) <= ((int64_t)3 << 20); }
+  // (by the layout that row_pitch gives, so the choice stays when the padding is
+  // given up)
+  static bool fused_2d(const gpf_ctx* c) {
+    return D == 2 && row_pitch(c->n[0], c->cells, sizeof(R)) * c->n[1] * (int64_t)sizeof(R) <= ((int64_t)3 << 20);
+  }
 
   // one step of a 2D grid: a single launch
   template <int TX, int TY>
@@ -694,6 +744,7 @@ struct Impl {
       if (c->rec_every > 0 && (c->step - c->rec_start) % c->rec_every == 0) {
         int rc = save_ckpt(c);
         if (rc) return rc;
+        k = make_kp<R>(c);  // the checkpoint's memory may have cost the rows' padding
       }
     }
     if (kernel_ms)
@@ -733,14 +784,9 @@ struct Impl {
     } else if (field == GPF_F || field == GPF_RHO) {
       ncomp = (field == GPF_F) ? Q : 1;
       gather_f(c, k, out);
-      if (field == GPF_RHO) {
-        // rho into the slot after the Q populations, then move to the front
-        double* rho = out + (int64_t)Q * c->cells;
+      if (field == GPF_RHO)  // over the cell's first population
         hipLaunchKernelGGL((gpf::k_derived<D, Q, N, NC, R>), dim3(nb), dim3(256), 0, c->stream, k, 0,
-                           P(c->phi[s]), P(c->mu[s]), out, 0.0, rho);
-        HIP_OR_FAIL(c, hipMemcpyAsync(out, rho, c->cells * sizeof(double), hipMemcpyDeviceToDevice,
-                                      c->stream));
-      }
+                           P(c->phi[s]), P(c->mu[s]), out, 0.0, out);
     } else if (field == GPF_C || field == GPF_T || field == GPF_FLAGS) {
       const int which = field == GPF_C ? 1 : field == GPF_T ? 2 : 3;
       ncomp = field == GPF_C ? NC : 1;
@@ -1008,38 +1054,11 @@ struct Impl {
     if (nseg > (int64_t)c->ckpt.size())
       return fail(c, GPF_ERR_STATE, "the recording holds %lld of the %lld checkpoints that the steps need",
                   (long long)c->ckpt.size(), (long long)nseg);
-    const size_t cs = (size_t)c->pcells * sizeof(R);
     gpf::KP<R> k = make_kp<R>(c);
     // On small 2D grids a reverse step is one launch (adj_step_2d).
     const bool one = adj_one_launch(c, k);
-    // What this sweep's kernels use, each buffer by itself: an earlier call may
-    // have failed between them, or run other kernels.
-    int rc = GPF_OK;
-    auto need = [&](DevBuf& b, size_t bytes) {
-      if (!rc) rc = dev_need(c, b, bytes);
-    };
-    for (int i = 0; i < 2 && !rc; ++i) rc = need_state(c, c->lam[i]);
-    need(c->t_phil, cs);
-    need(c->t_w, NC * cs);
-    need(c->t_part, (size_t)part_rows(c) * gpf::NG * sizeof(double));
-    need(c->t_acc, gpf::NG * sizeof(double));
-    need(c->t_slices, (size_t)gpf::GA * gpf::NG * sizeof(double));
-    if (one) {  // its second set
-      need(c->t_phil2, cs);
-      need(c->t_w2, NC * cs);
-    } else {
-      need(c->t_rbar, N * cs);
-      need(c->t_rflag, (size_t)c->pcells);
-      need(c->t_rowflag, (size_t)2 * c->n[1] * c->n[2]);
-    }
-    if (!one && k.aniso) {
-      // reverse of the face fluxes and cell terms: N (1 + D) values per face / cell
-      need(c->t_fflag, (size_t)D * c->pcells);
-      need(c->t_fbuf, (size_t)D * N * (1 + D) * cs);
-      need(c->t_cbuf, (size_t)N * (1 + D) * cs);
-    }
-    if (rc) return rc;
     auto alloc_tape = [&](int b) -> int {
+      const size_t cs = (size_t)c->pcells * sizeof(R);
       while ((int64_t)c->tape[b].size() < K - 1) {
         StateBuf s;
         int r = dev_alloc(c, s.phi, N * cs);
@@ -1063,10 +1082,41 @@ struct Impl {
       }
       return GPF_OK;
     };
+    // What this sweep's kernels use, each buffer by itself: an earlier call may
+    // have failed between them, or run other kernels.
+    auto alloc_sweep = [&]() -> int {
+      const size_t cs = (size_t)c->pcells * sizeof(R);
+      int rc = GPF_OK;
+      auto need = [&](DevBuf& b, size_t bytes) {
+        if (!rc) rc = dev_need(c, b, bytes);
+      };
+      for (int i = 0; i < 2 && !rc; ++i) rc = need_state(c, c->lam[i]);
+      need(c->t_phil, cs);
+      need(c->t_w, NC * cs);
+      need(c->t_part, (size_t)part_rows(c) * gpf::NG * sizeof(double));
+      need(c->t_acc, gpf::NG * sizeof(double));
+      need(c->t_slices, (size_t)gpf::GA * gpf::NG * sizeof(double));
+      if (one) {  // its second set
+        need(c->t_phil2, cs);
+        need(c->t_w2, NC * cs);
+      } else {
+        need(c->t_rbar, N * cs);
+        need(c->t_rflag, (size_t)c->pcells);
+        need(c->t_rowflag, (size_t)2 * c->n[1] * c->n[2]);
+      }
+      if (!one && k.aniso) {
+        // reverse of the face fluxes and cell terms: N (1 + D) values per face / cell
+        need(c->t_fflag, (size_t)D * c->pcells);
+        need(c->t_fbuf, (size_t)D * N * (1 + D) * cs);
+        need(c->t_cbuf, (size_t)N * (1 + D) * cs);
+      }
+      return rc ? rc : alloc_tape(0);
+    };
     // tape 0; with several segments, tape 1 for recomputing the previous
     // segment on the second stream.  If tape 1 does not fit, each segment is
     // recomputed into tape 0 on the library's stream before its reverse.
-    if ((rc = alloc_tape(0))) return rc;
+    if (int rc = try_dense(c, alloc_sweep)) return rc;
+    k = make_kp<R>(c);
     int ntape = 1;
     if (nseg > 1) {
       if (alloc_tape(1) == GPF_OK) {
@@ -1216,6 +1266,56 @@ struct Impl {
     return GPF_OK;
   }
 
+  // Gives the padding of the rows up: every state the context holds is packed
+  // through the staging buffer into memory of the dense size, and what the next
+  // call makes anew is given back (the other buffer set is void: the bulk history
+  // goes with it).
+  static int to_dense(gpf_ctx* c) {
+    const gpf::KP<R> k = make_kp<R>(c);
+    HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));
+    if (c->side) HIP_OR_FAIL(c, hipStreamSynchronize(c->side));
+    drop_graphs(c);
+    release_sweep(c);
+    if (!c->have_adjoint)
+      for (StateBuf& l : c->lam) release_state(c, l);
+    const int t = 1 - c->cur;
+    for (DevBuf* b : {&c->phi[t], &c->mu[t], &c->u[t], &c->f[t]}) dev_release(c, *b);
+    c->bulk_ok[0] = c->bulk_ok[1] = false;
+    c->lost = true;  // until all of it is there again
+    set_pitch(c, c->n[0]);
+    const size_t cs = (size_t)c->pcells * sizeof(R);
+    auto pack = [&](DevBuf& b, int ncomp) -> int {
+      if (!b.ptr) return GPF_OK;
+      hipLaunchKernelGGL((gpf::k_unpack<R, R, false>), dim3(lin_blocks(c->cells, 256)), dim3(256), 0, c->stream, k, P(b),
+                         P(c->scratch), ncomp, R(0), R(0));
+      HIP_OR_FAIL(c, hipGetLastError());
+      HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));
+      dev_release(c, b);
+      if (int rc = dev_alloc(c, b, ncomp * cs)) return rc;
+      HIP_OR_FAIL(c, hipMemcpyAsync(b.ptr, c->scratch.ptr, ncomp * cs, hipMemcpyDeviceToDevice, c->stream));
+      return GPF_OK;
+    };
+    auto pack_state = [&](DevBuf& phi, DevBuf& mu, DevBuf& u, DevBuf& f) -> int {
+      int rc = pack(phi, N);
+      if (!rc) rc = pack(mu, NC);
+      if (!rc) rc = pack(u, D);
+      return rc ? rc : pack(f, Q);
+    };
+    int rc = pack_state(c->phi[c->cur], c->mu[c->cur], c->u[c->cur], c->f[c->cur]);
+    for (StateBuf& s : c->ckpt)
+      if (!rc) rc = pack_state(s.phi, s.mu, s.u, s.f);
+    for (StateBuf& l : c->lam)
+      if (!rc) rc = pack_state(l.phi, l.mu, l.u, l.f);
+    if (!rc) rc = dev_alloc(c, c->phi[t], N * cs);
+    if (!rc) rc = dev_alloc(c, c->mu[t], NC * cs);
+    if (!rc) rc = dev_alloc(c, c->u[t], D * cs);
+    if (!rc) rc = dev_alloc(c, c->f[t], Q * cs);
+    if (rc) return rc;
+    HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));
+    c->lost = false;
+    return GPF_OK;
+  }
+
   // adjoint of the recorded initial state, field by field, as FP64
   static int lam_read(gpf_ctx* c, int field, double* host) {
     StateBuf& l = c->lam[c->lam_cur];
@@ -1238,7 +1338,7 @@ struct Impl {
 
   static const Ops* ops() {
     static const Ops o = {&step,      &frame,   &read,       &write,      &reduce,  &reduce_dev,
-                          &loss_seed, &read_native, &adjoint, &copy_state, &lam_read};
+                          &loss_seed, &read_native, &adjoint, &copy_state, &lam_read, &to_dense};
     return &o;
   }
 };
@@ -1449,13 +1549,7 @@ void free_all(gpf_ctx* c) {
   }
   for (auto& s : c->ckpt) release_state(c, s);
   c->ckpt.clear();
-  for (int b = 0; b < 2; ++b) {
-    for (auto& s : c->tape[b]) release_state(c, s);
-    c->tape[b].clear();
-    dev_release(c, c->tape_f[b][0]);
-    dev_release(c, c->tape_f[b][1]);
-    dev_release(c, c->tape_act[b]);
-  }
+  release_sweep(c);
   for (int b = 0; b < 2; ++b) {
     if (c->ev_free[b]) (void)hipEventDestroy(c->ev_free[b]);
     if (c->ev_done[b]) (void)hipEventDestroy(c->ev_done[b]);
@@ -1463,27 +1557,43 @@ void free_all(gpf_ctx* c) {
   }
   release_state(c, c->lam[0]);
   release_state(c, c->lam[1]);
-  dev_release(c, c->t_phil);
-  dev_release(c, c->t_w);
-  dev_release(c, c->t_phil2);
-  dev_release(c, c->t_w2);
-  dev_release(c, c->t_rbar);
-  dev_release(c, c->t_part);
-  dev_release(c, c->t_acc);
-  dev_release(c, c->t_slices);
-  dev_release(c, c->t_rflag);
-  dev_release(c, c->t_rowflag);
-  dev_release(c, c->t_fflag);
-  dev_release(c, c->t_fbuf);
-  dev_release(c, c->t_cbuf);
-  for (int b = 0; b < 2; ++b) {
-    if (c->gexec[b]) (void)hipGraphExecDestroy(c->gexec[b]);
-    c->gexec[b] = nullptr;
-  }
+  drop_graphs(c);
   if (c->gstream) {
     (void)hipStreamDestroy(c->gstream);
     c->gstream = nullptr;
   }
+}
+
+// the buffers that a context holds from the start
+int alloc_context(gpf_ctx* c) {
+  const size_t cs = (size_t)c->pcells * c->esize;
+  int rc = GPF_OK;
+  for (int s = 0; s < 2 && !rc; ++s) {
+    if (!rc) rc = dev_alloc(c, c->phi[s], c->N * cs);
+    if (!rc) rc = dev_alloc(c, c->mu[s], c->nc * cs);
+    if (!rc) rc = dev_alloc(c, c->u[s], c->dim * cs);
+    if (!rc) rc = dev_alloc(c, c->f[s], c->Q * cs);
+  }
+  if (!rc) rc = dev_alloc(c, c->scratch, (size_t)c->Q * c->cells * sizeof(double));
+  if (!rc) rc = dev_alloc(c, c->partial, kRedBlocks * 2 * sizeof(double));
+  if (!rc) rc = dev_alloc(c, c->redout, 4 * sizeof(double));
+  if (!rc) rc = dev_alloc(c, c->badstep, sizeof(unsigned long long));
+  if (!rc) rc = dev_alloc(c, c->frontbuf, sizeof(int));
+  for (int i = 0; i < 2 && !rc; ++i) rc = dev_alloc(c, c->bulkf[i], (size_t)phi_blocks(c));
+  if (!rc) rc = dev_alloc(c, c->tlist, (size_t)phi_blocks(c) * sizeof(unsigned));
+  if (!rc) rc = dev_alloc(c, c->tcount, 2 * sizeof(unsigned));
+  return rc;
+}
+
+// Every entry that touches the state: refused when the state is gone; async: one
+// that a caller may capture, whose graph then holds the buffers' addresses
+int enter(gpf_ctx* c, bool async = false) {
+  if (c->lost) return fail(c, GPF_ERR_STATE, "the state was lost when device memory ran out");
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (async && c->pitch > c->n[0] && c->stream && hipStreamIsCapturing(c->stream, &cap) == hipSuccess &&
+      cap != hipStreamCaptureStatusNone)
+    c->pinned = true;
+  return GPF_OK;
 }
 
 int set_named(gpf_ctx* c, gpf_params& p, const char* name, double v) {
@@ -1536,25 +1646,16 @@ int gpf_init(gpf_ctx** out, const gpf_grid* grid, int32_t n_phases, int32_t n_co
   for (int a = 0; a < 3; ++a) c->n[a] = (a < c->dim) ? grid->n[a] : 1;
   c->cells = c->n[0] * c->n[1] * c->n[2];
   c->esize = (params->precision == GPF_FP64) ? 8 : 4;
-  c->pitch = row_pitch(c->n[0], c->cells, c->esize);
-  c->pcells = c->pitch * c->n[1] * c->n[2];
+  set_pitch(c, row_pitch(c->n[0], c->cells, c->esize));
   c->ops = pick(c->Q, c->N, c->nc, params->precision);
   rc = resolve_scratch(c);
-  const size_t cs = (size_t)c->pcells * c->esize;
-  for (int s = 0; s < 2 && !rc; ++s) {
-    if (!rc) rc = dev_alloc(c, c->phi[s], c->N * cs);
-    if (!rc) rc = dev_alloc(c, c->mu[s], c->nc * cs);
-    if (!rc) rc = dev_alloc(c, c->u[s], c->dim * cs);
-    if (!rc) rc = dev_alloc(c, c->f[s], c->Q * cs);
+  if (!rc) rc = alloc_context(c);
+  if (rc == GPF_ERR_NOMEM && c->pitch > c->n[0]) {  // perhaps with rows as they come
+    free_all(c);
+    set_pitch(c, c->n[0]);
+    rc = alloc_context(c);
+    if (!rc) c->err.clear();
   }
-  if (!rc) rc = dev_alloc(c, c->scratch, (size_t)(c->Q + 1) * c->cells * sizeof(double));
-  if (!rc) rc = dev_alloc(c, c->partial, kRedBlocks * 2 * sizeof(double));
-  if (!rc) rc = dev_alloc(c, c->redout, 4 * sizeof(double));
-  if (!rc) rc = dev_alloc(c, c->badstep, sizeof(unsigned long long));
-  if (!rc) rc = dev_alloc(c, c->frontbuf, sizeof(int));
-  for (int i = 0; i < 2 && !rc; ++i) rc = dev_alloc(c, c->bulkf[i], (size_t)phi_blocks(c));
-  if (!rc) rc = dev_alloc(c, c->tlist, (size_t)phi_blocks(c) * sizeof(unsigned));
-  if (!rc) rc = dev_alloc(c, c->tcount, 2 * sizeof(unsigned));
   if (!rc) {
     hipError_t e = hipMemsetAsync(c->badstep.ptr, 0xff, sizeof(unsigned long long), c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->tcount.ptr, 0, 2 * sizeof(unsigned), c->stream);
@@ -1590,6 +1691,7 @@ static int check_health_result(gpf_ctx* c) {
 
 int gpf_step(gpf_ctx* c, int64_t n) {
   if (!c) return GPF_ERR_ARG;
+  if (int rc = enter(c, true)) return rc;
   if (n < 0) return fail(c, GPF_ERR_ARG, "negative step count");
   int rc = c->ops->step(c, n, nullptr, 0);
   if (rc) return rc;
@@ -1599,6 +1701,7 @@ int gpf_step(gpf_ctx* c, int64_t n) {
 
 int gpf_step_timed(gpf_ctx* c, int64_t n, double* kernel_ms, int32_t n_kernels) {
   if (!c || !kernel_ms || n_kernels < 1) return GPF_ERR_ARG;
+  if (int rc = enter(c)) return rc;
   if (n < 0) return fail(c, GPF_ERR_ARG, "negative step count");
   int rc = c->ops->step(c, n, kernel_ms, n_kernels);
   if (rc) return rc;
@@ -1609,6 +1712,7 @@ int gpf_step_timed(gpf_ctx* c, int64_t n, double* kernel_ms, int32_t n_kernels) 
 
 int gpf_read(gpf_ctx* c, int32_t field, double* dst, size_t count) {
   if (!c || !dst) return GPF_ERR_ARG;
+  if (int rc = enter(c)) return rc;
   const int comps = components(c, field);
   if (comps < 0) return fail(c, GPF_ERR_ARG, "unknown field %d", field);
   if (count != (size_t)comps * (size_t)c->cells)
@@ -1623,6 +1727,7 @@ int gpf_read(gpf_ctx* c, int32_t field, double* dst, size_t count) {
 
 int gpf_read_device(gpf_ctx* c, int32_t field, void* dst, size_t bytes) {
   if (!c || !dst) return GPF_ERR_ARG;
+  if (int rc = enter(c, true)) return rc;
   const int comps = components(c, field);
   if (field != GPF_PHI && field != GPF_MU && field != GPF_U && field != GPF_F)
     return fail(c, GPF_ERR_ARG, "field %d has no native device copy", field);
@@ -1633,6 +1738,7 @@ int gpf_read_device(gpf_ctx* c, int32_t field, void* dst, size_t bytes) {
 
 int gpf_write(gpf_ctx* c, int32_t field, const double* src, size_t count) {
   if (!c || !src) return GPF_ERR_ARG;
+  if (int rc = enter(c)) return rc;
   int rc = write_host(c, field, src, count);
   if (rc) return rc;
   c->bulk_ok[0] = c->bulk_ok[1] = false;  // the buffers no longer hold consecutive states
@@ -1644,6 +1750,7 @@ int gpf_write(gpf_ctx* c, int32_t field, const double* src, size_t count) {
 
 int gpf_reduce(gpf_ctx* c, int32_t which, double* out) {
   if (!c || !out) return GPF_ERR_ARG;
+  if (int rc = enter(c)) return rc;
   if (which != GPF_SUM_SOLUTE && which != GPF_SUM_MASS && which != GPF_LOSS)
     return fail(c, GPF_ERR_ARG, "unknown reduction %d", which);
   if (which == GPF_LOSS && !c->target) return fail(c, GPF_ERR_STATE, "GPF_LOSS needs a target (gpf_set_target)");
@@ -1652,6 +1759,7 @@ int gpf_reduce(gpf_ctx* c, int32_t which, double* out) {
 
 int gpf_reduce_noalloc(gpf_ctx* c, int32_t which, double* dev_out) {
   if (!c || !dev_out) return GPF_ERR_ARG;
+  if (int rc = enter(c, true)) return rc;
   if (which != GPF_SUM_SOLUTE && which != GPF_SUM_MASS && which != GPF_LOSS)
     return fail(c, GPF_ERR_ARG, "unknown reduction %d", which);
   if (which == GPF_LOSS && !c->target) return fail(c, GPF_ERR_STATE, "GPF_LOSS needs a target (gpf_set_target)");
@@ -1721,6 +1829,7 @@ int gpf_set_target(gpf_ctx* c, const void* dev_target, size_t count) {
 
 int gpf_loss_seed_device(gpf_ctx* c, void* dev_seed, size_t count) {
   if (!c || !dev_seed) return GPF_ERR_ARG;
+  if (int rc = enter(c, true)) return rc;
   if (count != (size_t)c->N * (size_t)c->cells)
     return fail(c, GPF_ERR_ARG, "count %zu, expected %zu", count, (size_t)c->N * (size_t)c->cells);
   if (!c->target) return fail(c, GPF_ERR_STATE, "no loss target (gpf_set_target)");
@@ -1740,6 +1849,7 @@ int gpf_set_param(gpf_ctx* c, const char* name, double value) {
 
 int gpf_record(gpf_ctx* c, int64_t checkpoint_every) {
   if (!c) return GPF_ERR_ARG;
+  if (int rc = enter(c)) return rc;
   if (checkpoint_every < 1) return fail(c, GPF_ERR_ARG, "checkpoint_every must be >= 1");
   (void)hipStreamSynchronize(c->stream);
   for (auto& s : c->ckpt) release_state(c, s);
@@ -1779,6 +1889,7 @@ namespace {
 int adjoint_entry(gpf_ctx* c, const double* dL_dphi, bool on_device, size_t count, const char* const* names,
                   int32_t n_names, double* grads_out) {
   if (!c || !dL_dphi || (n_names > 0 && (!names || !grads_out)) || n_names < 0) return GPF_ERR_ARG;
+  if (int rc = enter(c)) return rc;
   if (count != (size_t)c->N * (size_t)c->cells)
     return fail(c, GPF_ERR_ARG, "count %zu, expected %zu", count, (size_t)c->N * (size_t)c->cells);
   if (n_names > gpf::NG) return fail(c, GPF_ERR_ARG, "at most %d parameters", gpf::NG);
@@ -1812,6 +1923,7 @@ int gpf_adjoint_device(gpf_ctx* c, const void* dev_dL_dphi, size_t count, const 
 
 int gpf_adjoint_state(gpf_ctx* c, int32_t field, double* host_dst, size_t count) {
   if (!c || !host_dst) return GPF_ERR_ARG;
+  if (int rc = enter(c)) return rc;
   if (!c->have_adjoint) return fail(c, GPF_ERR_STATE, "no adjoint computed yet");
   const int comps = field == GPF_PHI ? c->N : field == GPF_MU ? c->nc : field == GPF_U ? c->dim
                   : field == GPF_F ? c->Q : -1;

@@ -128,3 +128,143 @@ def test_sweep_holds_what_it_uses(kind, n, over):
     sums = 48 * ((D + 3) * (cells / 256 + 8) + cells / 128 + 64 + 257) + 2 * n[1] * (n[2] if D == 3 else 1)
     assert s.device_bytes - before <= 4 * comps * cells + flags * cells + sums
     s.close()
+
+
+# Stored rows are padded to whole 128-byte lines where that at most doubles them; each of these is.
+PADDED = [("binary3d", [65, 6, 5], "fp32"), ("ternary2d", [17, 12], "fp64"), ("quaternary2d", [20, 9], "fp32")]
+
+
+def _recorded_run(cfg, precision, limit=None, arm=0):
+    """states, totals, gradients and the memory held at the end of a recorded run of seven steps and its sweep;
+    allocation number `arm` of the recording, the steps and the sweep fails"""
+    s = _sim(cfg, precision, limit)
+    s.step(3)
+    if limit is not None:
+        limit.fail(arm)
+    s.record(3)
+    s.step(7)
+    seed = np.cos(np.arange(cfg["N"] * s.cells)).reshape((cfg["N"],) + s.shape)
+    out = {k: s.read(k) for k in STATE + ("rho",)}
+    out["device"] = s.read_device("f").cpu().numpy()
+    out["mass"] = np.array(s.reduce("mass"))
+    out["grad"] = s.adjoint(seed, ["tau_pf", "D"])
+    out.update({"lam_" + k: s.adjoint_state(k) for k in STATE})
+    # steps, and a second sweep, after it all
+    s.step(2)
+    out["later"] = s.read("phi")
+    out["grad2"] = s.adjoint(seed, ["tau_pf", "D"])
+    total = s.device_bytes
+    s.close()
+    return out, total
+
+
+@pytest.mark.parametrize("kind,n,precision", PADDED)
+def test_padding_is_given_up_when_memory_runs_out(kind, n, precision):
+    """whichever allocation of a recorded run and its sweep does not fit, the
+    run goes on with rows as they come, with the same bits"""
+    cfg = busy_config(kind, n)
+    want, padded = _recorded_run(cfg, precision)
+    at = given_up = 0
+    while True:
+        at += 1
+        limit = FailAt()
+        got, total = _recorded_run(cfg, precision, limit, at)
+        for k in want:
+            assert np.array_equal(got[k], want[k]), (at, k)
+        given_up += total < padded
+        if limit.at > limit.seen:
+            assert total == padded
+            break
+    assert given_up > 20  # (not where only the first sweep's second tape did not fit)
+
+
+def _dense_bytes(cfg, precision):
+    """what a context holds with rows as they come: two states, the staging buffer, per-tile flags and lists (2D tiles
+    of 64 x 4, 3D ones of 32 x 4 x 2 cells) and small fixed buffers"""
+    n, D = list(cfg["n"])[: cfg["dim"]], cfg["dim"]
+    Q, cells = (9 if D == 2 else 19), int(np.prod(n))
+    tile = [64, 4] if D == 2 else [32, 4, 2]
+    tiles = int(np.prod([-(-a // b) for a, b in zip(n, tile)]))
+    S, es = cfg["N"] + cfg["nc"] + D + Q, 8 if precision == "fp64" else 4
+    return 2 * S * cells * es + Q * cells * 8 + 6 * tiles + 2048 * 16 + 32 + 8 + 4 + 8, S * cells * es
+
+
+@pytest.mark.parametrize("kind,n,precision", PADDED)
+def test_fits_in_the_memory_of_dense_rows(kind, n, precision):
+    """a context, and its checkpoints, fit in the memory that rows without
+    padding take"""
+    cfg = busy_config(kind, n)
+    context, ckpt = _dense_bytes(cfg, precision)
+    a, b, c = _sim(cfg, precision), _sim(cfg, precision, context), _sim(cfg, precision, context + 4 * ckpt)
+    assert a.device_bytes > context and b.device_bytes <= context
+    c.record(2)
+    for s in (a, b, c):
+        s.step(6)
+    assert c.device_bytes <= context + 4 * ckpt
+    for k in STATE:
+        ref = a.read(k)
+        assert np.array_equal(b.read(k), ref), k
+        assert np.array_equal(c.read(k), ref), k
+    for s in (a, b, c):
+        s.close()
+
+
+def test_memory_that_runs_out_twice():
+    """no memory even for dense rows: the recording fails, what is left of the
+    context says so, and another context is not touched"""
+    from paper_2608_26908_amd.gpf import GPFError
+
+    class Full(FailAt):
+        def __lt__(self, wanted):
+            self.seen += 1
+            return 0 < self.at <= self.seen
+
+    cfg, limit = busy_config("binary3d", [65, 6, 5]), Full()
+    s, other = _sim(cfg, "fp32", limit), _sim(cfg, "fp32")
+    limit.fail(1)
+    with pytest.raises(GPFError) as e:
+        s.record(2)
+    assert e.value.code == -3
+    limit.fail(0)
+    for call in (lambda: s.step(1), lambda: s.read("phi"), lambda: s.read_device("phi"), lambda: s.reduce("mass"),
+                 lambda: s.write("phi", np.zeros((2, 5, 6, 65))), lambda: s.record(2),
+                 lambda: s.adjoint(np.zeros((2, 5, 6, 65)), ["D"])):
+        with pytest.raises(GPFError) as e:
+            call()
+        assert e.value.code == -6
+    s.close()
+    other.step(2)
+    assert np.isfinite(other.read("phi")).all()
+    other.close()
+
+
+def test_captured_rows_stay():
+    """a caller's graph of steps holds the buffers' addresses: the rows then
+    keep their padding, and a recording that does not fit fails as such"""
+    import torch
+    from paper_2608_26908_amd.gpf import GPFError
+    cfg, limit = busy_config("binary2d", [33, 10], V=0.0), FailAt()
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        s, ref = _sim(cfg, "fp32", limit), _sim(cfg, "fp32")
+        s.step(2)
+        ref.step(2)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            s.step(2)
+        graph.replay()
+        ref.step(2)
+        stream.synchronize()
+        held = s.device_bytes
+        limit.fail(1)
+        with pytest.raises(GPFError) as e:
+            s.record(2)
+        assert e.value.code == -3 and s.device_bytes == held
+        for _ in range(3):
+            graph.replay()
+            ref.step(2)
+            stream.synchronize()
+            for k in STATE:
+                assert np.array_equal(s.read(k), ref.read(k)), k
+        s.close()
+        ref.close()
