@@ -72,10 +72,10 @@ struct gpf_ctx {
   // tiles that the next step's k_phi walks (3D grids, bulk history on) and two
   // list lengths that take turns, zero at first: the next step reads length
   // list_par and counts into the other; zl_grid: k_phi's blocks per launch, the
-  // device's resident blocks of it
+  // device's resident blocks of it, with anisotropy and without
   DevBuf tlist, tcount;
   int list_par = 0;
-  unsigned zl_grid = 0;
+  unsigned zl_grid[2] = {0, 0};
   int64_t frame_off = 0;  // moving frame: cells shifted so far along the pull axis
   const double* target = nullptr;  // loss target (caller's device memory, N * cells FP64)
   int device = 0;                    // HIP device current at gpf_init
@@ -503,7 +503,7 @@ struct Impl {
         if (bulk_in) {
           list = tl;
           count = tc + h.par;
-          g = std::max(8u, std::min(c->zl_grid, g));
+          g = std::max(8u, std::min(c->zl_grid[k.aniso ? 0 : 1], g));
         }
       }
     }
@@ -691,13 +691,16 @@ struct Impl {
   static int step(gpf_ctx* c, int64_t nsteps, double* kernel_ms, int nk) {
     gpf::KP<R> k = make_kp<R>(c);
     if constexpr (D == 3) {
-      if (!c->zl_grid) {  // once, outside any capture: k_phi's grid (a multiple of 8)
+      unsigned& blocks = c->zl_grid[k.aniso ? 0 : 1];
+      if (!blocks) {  // once, outside any capture: k_phi's grid (a multiple of 8)
+        constexpr int NT = GPF_PHI_TX * GPF_PHI_TY * GPF_PHI_TZ;
+        const void* fn =
+            k.aniso ? (const void*)gpf::k_phi<D, N, NC, R, GPF_PHI_TX, GPF_PHI_TY, GPF_PHI_TZ, false>
+                    : (const void*)gpf::k_phi<D, N, NC, R, GPF_PHI_TX, GPF_PHI_TY, GPF_PHI_TZ, true>;
         int per_cu = 0, cus = 0;
-        HIP_OR_FAIL(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                           &per_cu, gpf::k_phi<D, N, NC, R, GPF_PHI_TX, GPF_PHI_TY, GPF_PHI_TZ, false>,
-                           GPF_PHI_TX * GPF_PHI_TY * GPF_PHI_TZ, 0));
+        HIP_OR_FAIL(c, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, NT, 0));
         HIP_OR_FAIL(c, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
-        c->zl_grid = std::max(8u, (unsigned)(std::max(per_cu, 1) * cus) / 8u * 8u);
+        blocks = std::max(8u, (unsigned)(std::max(per_cu, 1) * cus) / 8u * 8u);
       }
     }
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};
