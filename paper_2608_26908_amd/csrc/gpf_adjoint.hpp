@@ -1392,13 +1392,15 @@ template <class R> struct AdjStep {
   const R *phi0, *phi1, *mu0, *mu1, *u0, *w, *lphi1, *phil;
   R *lphi0, *lmu0, *lu0;
   const uint8_t* act;  // active sets of phi^n, or null
-  // LBM reverse of step n - 1 (lf0 null: none): f* of X^{n-1} or rho - rho0 of
-  // the step, the populations' adjoints, and what it leaves for step n - 1
-  const R *fst, *dr, *lf1;
+  // LBM reverse of step n - 1: rho - rho0 of that step, the populations'
+  // adjoints, and what it leaves for step n - 1
+  const R *dr, *lf1;
   R *lf0, *phil_out, *w_out, *lmu_out;
 };
 
-template <int Q, int N, int NC, class R, int TX, int TY, bool TAPE>
+// LBM: with the LBM reverse of step n - 1 (X^n comes from the tape, which holds
+// rho - rho0); without, at the first step of a segment, where it is a launch of its own
+template <int Q, int N, int NC, class R, int TX, int TY, bool LBM>
 __global__ void __launch_bounds__((AdjTile<TX, TY>::NT))
 k_adj_step2(KP<R> p, AdjStep<R> s, R tshift, int tiles_x, double* __restrict__ part) {
   constexpr int D = 2, EX = AdjTile<TX, TY>::EX, EY = AdjTile<TX, TY>::EY, NT = AdjTile<TX, TY>::NT;
@@ -1528,10 +1530,10 @@ k_adj_step2(KP<R> p, AdjStep<R> s, R tshift, int tiles_x, double* __restrict__ p
       }
       s.lphi0[b * p.cells + P] = p0b[b] + acc[b];
     }
-    if (s.lf0) {
+    if constexpr (LBM) {
       double gl[NG] = {0, 0, 0, 0, 0, 0};
-      adj_lbm_cell<D, Q, N, NC, R, TAPE>(p, P, xc[0], xc[1], 0, s.fst, s.dr, s.u0, s.phi0, s.mu0, s.lf1, lu, lm, s.lf0,
-                                         s.phil_out, s.w_out, s.lmu_out, tshift, gl);
+      adj_lbm_cell<D, Q, N, NC, R, true>(p, P, xc[0], xc[1], 0, nullptr, s.dr, s.u0, s.phi0, s.mu0, s.lf1, lu, lm,
+                                         s.lf0, s.phil_out, s.w_out, s.lmu_out, tshift, gl);
 #pragma unroll
       for (int i = 0; i < NG; ++i) gpart[i] += gl[i];
     }

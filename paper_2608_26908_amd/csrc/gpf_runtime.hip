@@ -1020,21 +1020,21 @@ struct Impl {
   }
 
   // Reverse of step n (X^n -> X^{n+1}) on a small 2D grid in one launch, with the
-  // LBM reverse of step n - 1 (last: not).  x0, x1: X^n, X^{n+1}; xm: X^{n-1}; flip:
-  // which set of t_w / t_phil step n's LBM reverse wrote.
-  static void adj_step_2d(gpf_ctx* c, const gpf::KP<R>& k, int64_t n, const SP& xm, const SP& x0, const SP& x1,
-                          StateBuf& li, StateBuf& lo, const uint8_t* act, bool last, int flip) {
+  // LBM reverse of step n - 1 (lbm; X^n is then a state of the tape).  x0, x1: X^n,
+  // X^{n+1}; flip: which set of t_w / t_phil step n's LBM reverse wrote.
+  static void adj_step_2d(gpf_ctx* c, const gpf::KP<R>& k, int64_t n, const SP& x0, const SP& x1, StateBuf& li,
+                          StateBuf& lo, const uint8_t* act, bool lbm, int flip) {
     if constexpr (D == 2 && N <= 3) {
       constexpr int TX = GPF_ADJ2_TX, TY = GPF_ADJ2_TY;
       DevBuf* w[2] = {&c->t_w, &c->t_w2};
       DevBuf* ph[2] = {&c->t_phil, &c->t_phil2};
       const int tx = (int)((c->n[0] + TX - 1) / TX), ty = (int)((c->n[1] + TY - 1) / TY);
-      const gpf::AdjStep<R> s{x0.phi,     x1.phi,   x0.mu,   x1.mu, x0.u, P(*w[flip]),      P(li.phi),     P(*ph[flip]),
-                              P(lo.phi),  P(lo.mu), P(lo.u), act,   xm.f, x0.dr,            P(lo.f),
-                              last ? nullptr : P(li.f), P(*ph[1 - flip]), P(*w[1 - flip]), P(li.mu)};
+      const gpf::AdjStep<R> s{x0.phi,    x1.phi,   x0.mu,   x1.mu, x0.u,  P(*w[flip]), P(li.phi), P(*ph[flip]),
+                              P(lo.phi), P(lo.mu), P(lo.u), act,   x0.dr, P(lo.f),     P(li.f),   P(*ph[1 - flip]),
+                              P(*w[1 - flip]), P(li.mu)};
       const dim3 g((unsigned)tx * (unsigned)ty), b(gpf::AdjTile<TX, TY>::NT);
       double* part = static_cast<double*>(c->t_part.ptr) + adj_launch(c).pstride;
-      if (x0.dr)
+      if (lbm)
         hipLaunchKernelGGL((gpf::k_adj_step2<Q, N, NC, R, TX, TY, true>), g, b, 0, c->stream, k, s, (R)tshift(c, n), tx,
                            part);
       else
@@ -1223,7 +1223,7 @@ struct Impl {
           // the LBM reverse of the segment before goes separately: with one tape
           // that segment is not there yet, and with two the rest need not wait
           // for it (the same launches either way, so the same bits)
-          adj_step_2d(c, k, c->rec_start + m, state(m), state(m), state(m + 1), *li, *lo, act, true, flip);
+          adj_step_2d(c, k, c->rec_start + m, state(m), state(m + 1), *li, *lo, act, false, flip);
           part_done = true;
         }
         if (j == 0 && ntape == 2) {
@@ -1240,7 +1240,7 @@ struct Impl {
           adj_lbm(c, k, c->rec_start + m - 1, state(m - 1), state(m), *lo, *li);
           flip = 1;  // (the next step's inputs are in the first set)
         } else if (one) {
-          adj_step_2d(c, k, c->rec_start + m, state(m - 1), state(m), state(m + 1), *li, *lo, act, false, flip);
+          adj_step_2d(c, k, c->rec_start + m, state(m), state(m + 1), *li, *lo, act, true, flip);
         } else if (fuse) {
           adj_phi2_lbm(c, k, c->rec_start + m, state(m - 1), state(m), *lo, *li);
         } else {
@@ -1248,7 +1248,7 @@ struct Impl {
           adj_lbm(c, k, c->rec_start + m - 1, state(m - 1), state(m), *lo, *li);
         }
       } else if (one) {
-        adj_step_2d(c, k, c->rec_start + m, state(m), state(m), state(m + 1), *li, *lo, act, true, flip);
+        adj_step_2d(c, k, c->rec_start + m, state(m), state(m + 1), *li, *lo, act, false, flip);
       } else {
         adj_phi2(c, k, c->rec_start + m, state(m), *lo);
       }
