@@ -273,8 +273,8 @@ int gpf_set_param(gpf_ctx* ctx, const char* name, double value);
  * gpf_record: the current state becomes checkpoint 0 of a recording; every
  * later gpf_step stores a full-state checkpoint each `checkpoint_every`
  * steps (device memory: (N + nc + dim + Q) * cells values per checkpoint, cells
- * counted with rows of half a line and more padded to a multiple of 128 bytes;
- * on large grids only where that adds at most an eighth, and no longer, for
+ * counted with rows padded to a multiple of 128 bytes where that adds at most
+ * an eighth, and up to 2^24 cells also where it pays in time; and no longer, for
  * the context's whole state, once an allocation has failed: what fits with
  * rows as they come fits, unless the caller has captured the context's work
  * into a graph, which holds the padded buffers;

@@ -185,16 +185,37 @@ void set_pitch(gpf_ctx* c, int64_t pitch) {
 // ---------------------------------------------------------------------------
 // kernel parameter block
 // ---------------------------------------------------------------------------
+// Both states within the 256 MiB last-level cache, on a grid whose work lies in
+// the kernels and not in their latency: see make_kp's `cached`.
+bool fits_cache(const gpf_ctx* c, int64_t pcells) {
+  return c->cells > ((int64_t)1 << 18) &&
+         2 * (int64_t)(c->N + c->nc + c->dim + c->Q) * pcells * (int64_t)c->esize <= ((int64_t)256 << 20);
+}
+
 // Elements per stored row.  Rows start on 128-byte lines: a wave then stores
 // whole lines.  With rows of n[0] elements as they come, the streaming stores
 // of a width that is no multiple of a line leave the chip as partial lines
 // (255 x 256 x 128, FP32: k_mulbm took 560 us, 256 x 256 x 128 took 317; with
-// cached stores 427).  Rows shorter than half a line stay as they are, and so
-// do large grids whose memory would grow by more than an eighth.  Where memory
-// runs out the padding is given up (try_dense).
-int64_t row_pitch(int64_t n0, int64_t cells, size_t esize) {
-  const int64_t line = 128 / (int64_t)esize, p = (n0 + line - 1) / line * line;
-  if (p > 2 * n0 || (cells > ((int64_t)1 << 24) && 8 * p > 9 * n0)) return n0;
+// cached stores 427).  The padding is computed, stored and held as well, so
+// where it adds more than an eighth it has to earn that.  us per step, rows as
+// they come and padded, 3D and FP32 unless stated:
+//   rows of up to 64 cells do not: 16 x 256 x 256 71 and 101, 33 x 256 x 256
+//     131 and 178 (FP64 239 and 260), 48 x 256 x 256 148 and 172; 20 x 100 x 90
+//     19.0 and 22.4; in 2D three phases 33 x 20000 27 and 29, but four phases 33 x
+//     100 7.7 and 7.0, where latency counts and memory does not;
+//   cached accesses (k_mulbm's of three and four phases) put partial lines
+//     together: 65 x 100 x 90 38.8 and 44.3, 100 x 100 x 90 52 and 58;
+//   the others do: two phases 65 x 100 x 90 68 and 46, 129 x 200 x 200 401 and
+//     266 (three phases, beyond the cache, 415 and 309).
+// Shorter than half a line nothing is padded, and above 2^24 cells nothing by
+// more than an eighth: the memory counts there.  Where memory runs out all
+// padding is given up (try_dense).
+int64_t row_pitch(const gpf_ctx* c) {
+  const int64_t n0 = c->n[0], line = 128 / (int64_t)c->esize, p = (n0 + line - 1) / line * line;
+  if (8 * p <= 9 * n0) return p;
+  if (p > 2 * n0 || c->cells > ((int64_t)1 << 24)) return n0;
+  if (n0 <= 64 && (c->dim == 3 || c->cells > ((int64_t)1 << 17))) return n0;
+  if (c->N >= 3 && fits_cache(c, c->cells)) return n0;
   return p;
 }
 
@@ -224,8 +245,7 @@ gpf::KP<R> make_kp(const gpf_ctx* c) {
   // cells, where latency counts and a host synchronisation has to write the
   // cached lines back (144 x 700, four phases, a moving-frame check every 25 of
   // 50 steps: 498 against 541)
-  k.cached = c->cells > ((int64_t)1 << 18) &&
-             2 * (int64_t)(c->N + c->nc + c->dim + c->Q) * c->pcells * (int64_t)sizeof(R) <= ((int64_t)256 << 20);
+  k.cached = fits_cache(c, c->pcells);
   k.potential = p.potential;
   k.pull_axis = p.pull_axis;
   k.grav_axis = p.grav_axis;
@@ -565,7 +585,7 @@ struct Impl {
   // (by the layout that row_pitch gives, so the choice stays when the padding is
   // given up)
   static bool fused_2d(const gpf_ctx* c) {
-    return D == 2 && row_pitch(c->n[0], c->cells, sizeof(R)) * c->n[1] * (int64_t)sizeof(R) <= ((int64_t)3 << 20);
+    return D == 2 && row_pitch(c) * c->n[1] * (int64_t)sizeof(R) <= ((int64_t)3 << 20);
   }
 
   // one step of a 2D grid: a single launch
@@ -1649,7 +1669,7 @@ int gpf_init(gpf_ctx** out, const gpf_grid* grid, int32_t n_phases, int32_t n_co
   for (int a = 0; a < 3; ++a) c->n[a] = (a < c->dim) ? grid->n[a] : 1;
   c->cells = c->n[0] * c->n[1] * c->n[2];
   c->esize = (params->precision == GPF_FP64) ? 8 : 4;
-  set_pitch(c, row_pitch(c->n[0], c->cells, c->esize));
+  set_pitch(c, row_pitch(c));
   c->ops = pick(c->Q, c->N, c->nc, params->precision);
   rc = resolve_scratch(c);
   if (!rc) rc = alloc_context(c);

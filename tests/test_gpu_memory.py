@@ -209,6 +209,20 @@ def test_fits_in_the_memory_of_dense_rows(kind, n, precision):
         s.close()
 
 
+@pytest.mark.parametrize("kind,n,precision", [
+    ("binary3d", [33, 6, 5], "fp32"), ("ternary3d_nc2", [20, 4, 3], "fp64"),  # rows of up to 64 cells in 3D
+    ("binary2d", [40, 3300], "fp32"),                                         # and in 2D above 2^17 cells
+    ("ternary3d_nc2", [65, 64, 64], "fp32"),                                  # three phases in the cache
+])
+def test_rows_that_stay_as_they_come(kind, n, precision):
+    """where padding would add more than an eighth and costs more than it gains, a context holds no more than rows
+    as they come"""
+    cfg = busy_config(kind, n)
+    s = _sim(cfg, precision)
+    assert s.device_bytes <= _dense_bytes(cfg, precision)[0]
+    s.close()
+
+
 def test_memory_that_runs_out_twice():
     """no memory even for dense rows: the recording fails, what is left of the
     context says so, and another context is not touched"""

@@ -61,3 +61,11 @@ def test_row_tiles_fp32(oracle, n, over):
     and multiples; 224 does not): one step within 1e-5 of each field's largest
     value, a hundred and more roundings of 6e-8 on values of order one."""
     _check(busy_config("binary3d", n, **over), 1, "fp32", 1e-5)
+
+
+@pytest.mark.parametrize("kind,n", [("binary3d", [33, 9, 5]), ("quaternary3d", [50, 5, 4]), ("binary2d", [40, 3300]),
+                                    ("ternary3d_nc2", [65, 64, 64])])
+def test_rows_without_padding(oracle, kind, n):
+    """widths whose rows are stored as they come, none a multiple of a line: up to 64 cells, in 2D above 2^17 cells,
+    and three phases whose state fits the last-level cache"""
+    _check(busy_config(kind, n), 2)
