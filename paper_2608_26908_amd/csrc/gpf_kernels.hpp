@@ -1278,32 +1278,74 @@ __global__ void k_scatter_f(KP<R> p, const double* __restrict__ fn, R* __restric
   }
 }
 
-// Components between the stored form (padded rows, precision R) and a dense
-// array of T.  MU: component i is stored less r0 (i = 0) or r1, the reference
-// chemical potentials.
-template <class R, class T, bool MU>
-__global__ void k_unpack(KP<R> p, const R* __restrict__ in, T* __restrict__ out, int ncomp, T r0, T r1) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t P;
-  int x, y, z;
-  if (!dense_cell(p, i, x, y, z, P)) return;
-  for (int k = 0; k < ncomp; ++k) {
-    T v = (T)in[k * p.cells + P];
-    if (MU) v += k == 0 ? r0 : r1;
-    out[k * p.live + i] = v;
-  }
+// Copies between the stored form (precision R) and a dense array of T, and the
+// loss seed.  HBM bound, or by the host's call on small grids: they take the few
+// sizes they need instead of the parameter block (0.4 us per call).  A block
+// takes copy_cells(C) * 256 consecutive cells of the dense array, whose lines it fills
+// (64 x 4 tiles leave partial lines at every row's end); rows are sy apart in every
+// plane, so a cell's stored element is its dense one and its row's number times
+// the padding.  All of a thread's loads are in flight before its first store.
+// us per phi read to the device, FP32, 150 x 131 x 117, the host's 8 among them:
+// 9.1, with one cell per thread 11.2, with tiles 11.7.
+constexpr int copy_cells(int comps) { return comps <= 4 ? 4 : 1; }
+struct Rows {
+  int n0, pad;  // cells of a row, padding behind it
+  int64_t cells, live;
+};
+__device__ __forceinline__ int64_t stored_at(const Rows& g, int64_t i) {
+  if (g.pad == 0) return i;
+  // 32-bit divisions are a quarter of the 64-bit ones
+  const int64_t row = g.live <= (int64_t)0xffffffff ? (int64_t)((unsigned)i / (unsigned)g.n0) : i / g.n0;
+  return i + row * g.pad;
 }
-template <class R, class T, bool MU>
-__global__ void k_pack(KP<R> p, const T* __restrict__ in, R* __restrict__ out, int ncomp, T r0, T r1) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t P;
-  int x, y, z;
-  if (!dense_cell(p, i, x, y, z, P)) return;
-  for (int k = 0; k < ncomp; ++k) {
-    T v = in[k * p.live + i];
-    if (MU) v -= k == 0 ? r0 : r1;
-    out[k * p.cells + P] = (R)v;
+// get(P, i, v) and put(P, i, v) of the cells of a thread: P stored, i dense
+template <class V, int CELLS, class GET, class PUT>
+__device__ __forceinline__ void copy_block(const Rows& g, GET&& get, PUT&& put) {
+  V v[CELLS];
+  int64_t P[CELLS];
+  const int64_t i0 = (int64_t)blockIdx.x * (CELLS * 256) + threadIdx.x;
+#pragma unroll
+  for (int j = 0; j < CELLS; ++j) {
+    const int64_t i = i0 + j * 256;
+    P[j] = stored_at(g, i);
+    if (i < g.live) get(P[j], i, v[j]);
   }
+#pragma unroll
+  for (int j = 0; j < CELLS; ++j)
+    if (i0 + j * 256 < g.live) put(P[j], i0 + j * 256, v[j]);
+}
+template <class T, int C> struct CellOf {
+  T c[C];
+};
+// MU: component i is stored less r0 (i = 0) or r1, the reference chemical
+// potentials.
+template <class R, class T, bool MU, int C>
+__global__ void __launch_bounds__(256) k_unpack(Rows g, const R* __restrict__ in, T* __restrict__ out, T r0, T r1) {
+  using V = CellOf<R, C>;
+  copy_block<V, copy_cells(C)>(
+      g,
+      [&](int64_t P, int64_t, V& v) {
+#pragma unroll
+        for (int k = 0; k < C; ++k) v.c[k] = in[k * g.cells + P];
+      },
+      [&](int64_t, int64_t i, const V& v) {
+#pragma unroll
+        for (int k = 0; k < C; ++k) out[k * g.live + i] = MU ? (T)v.c[k] + (k == 0 ? r0 : r1) : (T)v.c[k];
+      });
+}
+template <class R, class T, bool MU, int C>
+__global__ void __launch_bounds__(256) k_pack(Rows g, const T* __restrict__ in, R* __restrict__ out, T r0, T r1) {
+  using V = CellOf<T, C>;
+  copy_block<V, copy_cells(C)>(
+      g,
+      [&](int64_t, int64_t i, V& v) {
+#pragma unroll
+        for (int k = 0; k < C; ++k) v.c[k] = in[k * g.live + i];
+      },
+      [&](int64_t P, int64_t, const V& v) {
+#pragma unroll
+        for (int k = 0; k < C; ++k) out[k * g.cells + P] = (R)(MU ? v.c[k] - (k == 0 ? r0 : r1) : v.c[k]);
+      });
 }
 // derived per-cell fields in FP64: 0 rho (out may be fgathered: a cell's sum goes
 // over its own first population), 1 mixture composition C (nc comps), 2
@@ -1438,14 +1480,20 @@ __global__ void k_final_sum(const double* __restrict__ partial, int nblocks, int
 }
 
 // dL/dphi of the loss 1/2 sum (phi - target)^2: phi - target in FP64, dense
-template <class R>
-__global__ void k_loss_seed(KP<R> p, const R* __restrict__ phi, const double* __restrict__ target,
-                            double* __restrict__ out, int ncomp) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t P;
-  int x, y, z;
-  if (!dense_cell(p, i, x, y, z, P)) return;
-  for (int k = 0; k < ncomp; ++k) out[k * p.live + i] = (double)phi[k * p.cells + P] - target[k * p.live + i];
+template <class R, int C>
+__global__ void __launch_bounds__(256) k_loss_seed(Rows g, const R* __restrict__ phi, const double* __restrict__ target,
+                                                   double* __restrict__ out) {
+  using V = CellOf<double, C>;
+  copy_block<V, copy_cells(C)>(
+      g,
+      [&](int64_t P, int64_t i, V& v) {
+#pragma unroll
+        for (int k = 0; k < C; ++k) v.c[k] = (double)phi[k * g.cells + P] - target[k * g.live + i];
+      },
+      [&](int64_t, int64_t i, const V& v) {
+#pragma unroll
+        for (int k = 0; k < C; ++k) out[k * g.live + i] = v.c[k];
+      });
 }
 
 // ---------------------------------------------------------------------------

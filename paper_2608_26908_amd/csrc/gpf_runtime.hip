@@ -224,6 +224,9 @@ double lattice_w(int Q, int k) {
   return Q == 9 ? gpf::Lat<9>::w(k) : (Q == 19 ? gpf::Lat<19>::w(k) : gpf::Lat<27>::w(k));
 }
 
+// what stored chemical potentials are less by
+double mu_ref(const gpf_ctx* c, int i) { return (c->prm.precision == GPF_FP32 && i < c->nc) ? c->prm.mu_inf[i] : 0.0; }
+
 template <class R>
 gpf::KP<R> make_kp(const gpf_ctx* c) {
   const gpf_params& p = c->prm;
@@ -269,7 +272,7 @@ gpf::KP<R> make_kp(const gpf_ctx* c) {
     k.dS[a] = (R)p.dS[a];
   }
   for (int i = 0; i < 2; ++i) {
-    k.mu_ref_d[i] = (p.precision == GPF_FP32 && i < c->nc) ? p.mu_inf[i] : 0.0;
+    k.mu_ref_d[i] = mu_ref(c, i);
     k.mu_ref[i] = (R)k.mu_ref_d[i];
   }
   for (int a = 0; a < 4; ++a)
@@ -783,29 +786,47 @@ struct Impl {
                        c->stream, k, P(c->f[c->cur]), out, tx, ty);
   }
 
+  // the copies between stored and dense form
+  static gpf::Rows rows(const gpf_ctx* c) {
+    return {(int)c->n[0], (int)(c->pitch - c->n[0]), c->pcells, c->cells};
+  }
+  template <int C> static dim3 copy_blocks(const gpf_ctx* c) {
+    return dim3(lin_blocks(c->cells, gpf::copy_cells(C) * 256));
+  }
+  template <int C, class T, bool MU = false>
+  static void unpack(gpf_ctx* c, const R* in, T* out, const gpf::Rows& r) {
+    hipLaunchKernelGGL((gpf::k_unpack<R, T, MU, C>), copy_blocks<C>(c), dim3(256), 0, c->stream, r, in, out,
+                       (T)mu_ref(c, 0), (T)mu_ref(c, 1));
+  }
+  template <int C, class T, bool MU = false> static void unpack(gpf_ctx* c, const R* in, T* out) {
+    unpack<C, T, MU>(c, in, out, rows(c));
+  }
+  template <int C, bool MU = false> static void pack(gpf_ctx* c, const double* in, R* out) {
+    hipLaunchKernelGGL((gpf::k_pack<R, double, MU, C>), copy_blocks<C>(c), dim3(256), 0, c->stream, rows(c), in, out,
+                       mu_ref(c, 0), mu_ref(c, 1));
+  }
+
   // field -> scratch (FP64 on the device); returns the component count
   static int read(gpf_ctx* c, int field, double* comps) {
-    gpf::KP<R> k = make_kp<R>(c);
     const int s = c->cur;
     double* out = static_cast<double*>(c->scratch.ptr);
     const unsigned nb = lin_blocks(c->cells, 256);
     int ncomp = 0;
-    switch (field) {
-      case GPF_PHI: ncomp = N; break;
-      case GPF_MU: ncomp = NC; break;
-      case GPF_U: ncomp = D; break;
-      default: break;
-    }
-    if (field == GPF_FPOST) ncomp = Q;
-    if (field == GPF_MU) {
-      hipLaunchKernelGGL((gpf::k_unpack<R, double, true>), dim3(nb), dim3(256), 0, c->stream, k, P(c->mu[s]), out, ncomp,
-                         k.mu_ref_d[0], k.mu_ref_d[1]);
-    } else if (ncomp) {
-      const R* src = field == GPF_PHI ? P(c->phi[s]) : (field == GPF_U ? P(c->u[s]) : P(c->f[s]));
-      hipLaunchKernelGGL((gpf::k_unpack<R, double, false>), dim3(nb), dim3(256), 0, c->stream, k, src, out, ncomp, 0.0,
-                         0.0);
+    if (field == GPF_PHI) {
+      ncomp = N;
+      unpack<N, double>(c, P(c->phi[s]), out);
+    } else if (field == GPF_MU) {
+      ncomp = NC;
+      unpack<NC, double, true>(c, P(c->mu[s]), out);
+    } else if (field == GPF_U) {
+      ncomp = D;
+      unpack<D, double>(c, P(c->u[s]), out);
+    } else if (field == GPF_FPOST) {
+      ncomp = Q;
+      unpack<Q, double>(c, P(c->f[s]), out);
     } else if (field == GPF_F || field == GPF_RHO) {
       ncomp = (field == GPF_F) ? Q : 1;
+      const gpf::KP<R> k = make_kp<R>(c);
       gather_f(c, k, out);
       if (field == GPF_RHO)  // over the cell's first population
         hipLaunchKernelGGL((gpf::k_derived<D, Q, N, NC, R>), dim3(nb), dim3(256), 0, c->stream, k, 0,
@@ -813,7 +834,7 @@ struct Impl {
     } else if (field == GPF_C || field == GPF_T || field == GPF_FLAGS) {
       const int which = field == GPF_C ? 1 : field == GPF_T ? 2 : 3;
       ncomp = field == GPF_C ? NC : 1;
-      hipLaunchKernelGGL((gpf::k_derived<D, Q, N, NC, R>), dim3(nb), dim3(256), 0, c->stream, k, which,
+      hipLaunchKernelGGL((gpf::k_derived<D, Q, N, NC, R>), dim3(nb), dim3(256), 0, c->stream, make_kp<R>(c), which,
                          P(c->phi[s]), P(c->mu[s]), out, tshift(c, c->step), out);
     } else {
       return fail(c, GPF_ERR_ARG, "unknown field %d", field);
@@ -824,27 +845,22 @@ struct Impl {
   }
 
   static int read_native(gpf_ctx* c, int field, void* dst) {
-    gpf::KP<R> k = make_kp<R>(c);
     const int s = c->cur;
     R* out = static_cast<R*>(dst);
-    const dim3 g(lin_blocks(c->cells, 256)), b(256);
-    switch (field) {
-      case GPF_PHI:
-      case GPF_U: {
-        const R* src = field == GPF_PHI ? P(c->phi[s]) : P(c->u[s]);
-        const int ncomp = field == GPF_PHI ? N : D;
-        if (c->pcells == c->cells)
-          HIP_OR_FAIL(c, hipMemcpyAsync(dst, src, ncomp * c->cells * sizeof(R), hipMemcpyDeviceToDevice, c->stream));
-        else
-          hipLaunchKernelGGL((gpf::k_unpack<R, R, false>), g, b, 0, c->stream, k, src, out, ncomp, R(0), R(0));
-        break;
-      }
-      case GPF_MU:
-        hipLaunchKernelGGL((gpf::k_unpack<R, R, true>), g, b, 0, c->stream, k, P(c->mu[s]), out, NC, k.mu_ref[0],
-                           k.mu_ref[1]);
-        break;
-      case GPF_F: gather_f(c, k, out); break;
-      default: return fail(c, GPF_ERR_ARG, "field %d has no native device copy", field);
+    const bool dense = c->pcells == c->cells;
+    if (field == GPF_MU) {
+      unpack<NC, R, true>(c, P(c->mu[s]), out);
+    } else if (field == GPF_F) {
+      gather_f(c, make_kp<R>(c), out);
+    } else if (field == GPF_PHI && !dense) {
+      unpack<N, R>(c, P(c->phi[s]), out);
+    } else if (field == GPF_U && !dense) {
+      unpack<D, R>(c, P(c->u[s]), out);
+    } else if (field == GPF_PHI || field == GPF_U) {
+      const DevBuf& b = field == GPF_PHI ? c->phi[s] : c->u[s];
+      HIP_OR_FAIL(c, hipMemcpyAsync(dst, b.ptr, b.bytes, hipMemcpyDeviceToDevice, c->stream));
+    } else {
+      return fail(c, GPF_ERR_ARG, "field %d has no native device copy", field);
     }
     HIP_OR_FAIL(c, hipGetLastError());
     return GPF_OK;
@@ -852,20 +868,19 @@ struct Impl {
 
   // scratch (FP64) -> field of the current buffers
   static int write(gpf_ctx* c, int field) {
-    gpf::KP<R> k = make_kp<R>(c);
     const int s = c->cur;
     const double* in = static_cast<const double*>(c->scratch.ptr);
-    const dim3 g(lin_blocks(c->cells, 256)), b(256);
-    if (field == GPF_F) {
-      hipLaunchKernelGGL((gpf::k_scatter_f<D, Q, R>), g, b, 0, c->stream, k, in, P(c->f[s]), 0, 0);
-    } else if (field == GPF_MU) {
-      hipLaunchKernelGGL((gpf::k_pack<R, double, true>), g, b, 0, c->stream, k, in, P(c->mu[s]), NC, k.mu_ref_d[0],
-                         k.mu_ref_d[1]);
-    } else {
-      const int ncomp = field == GPF_PHI ? N : (field == GPF_U ? D : Q);
-      R* dst = field == GPF_PHI ? P(c->phi[s]) : (field == GPF_U ? P(c->u[s]) : P(c->f[s]));
-      hipLaunchKernelGGL((gpf::k_pack<R, double, false>), g, b, 0, c->stream, k, in, dst, ncomp, 0.0, 0.0);
-    }
+    if (field == GPF_F)
+      hipLaunchKernelGGL((gpf::k_scatter_f<D, Q, R>), dim3(lin_blocks(c->cells, 256)), dim3(256), 0, c->stream,
+                         make_kp<R>(c), in, P(c->f[s]), 0, 0);
+    else if (field == GPF_MU)
+      pack<NC, true>(c, in, P(c->mu[s]));
+    else if (field == GPF_PHI)
+      pack<N>(c, in, P(c->phi[s]));
+    else if (field == GPF_U)
+      pack<D>(c, in, P(c->u[s]));
+    else
+      pack<Q>(c, in, P(c->f[s]));
     HIP_OR_FAIL(c, hipGetLastError());
     return GPF_OK;
   }
@@ -896,9 +911,8 @@ struct Impl {
   }
 
   static int loss_seed(gpf_ctx* c, double* dev_seed) {
-    gpf::KP<R> k = make_kp<R>(c);
-    hipLaunchKernelGGL((gpf::k_loss_seed<R>), dim3(lin_blocks(c->cells, 256)), dim3(256), 0, c->stream, k,
-                       P(c->phi[c->cur]), c->target, dev_seed, N);
+    hipLaunchKernelGGL((gpf::k_loss_seed<R, N>), copy_blocks<N>(c), dim3(256), 0, c->stream, rows(c), P(c->phi[c->cur]),
+                       c->target, dev_seed);
     HIP_OR_FAIL(c, hipGetLastError());
     return GPF_OK;
   }
@@ -1166,8 +1180,7 @@ struct Impl {
     if (!seed_on_device)
       HIP_OR_FAIL(c, hipMemcpyAsync(c->scratch.ptr, seed, (size_t)N * c->cells * sizeof(double),
                                     hipMemcpyHostToDevice, c->stream));
-    hipLaunchKernelGGL((gpf::k_pack<R, double, false>), dim3(lin_blocks(c->cells, 256)), dim3(256), 0, c->stream, k,
-                       seed_on_device ? seed : static_cast<const double*>(c->scratch.ptr), P(li->phi), N, 0.0, 0.0);
+    pack<N>(c, seed_on_device ? seed : static_cast<const double*>(c->scratch.ptr), P(li->phi));
     fill(c, li->mu, NC * c->pcells);
     fill(c, li->u, D * c->pcells);
     fill(c, li->f, Q * c->pcells);
@@ -1294,7 +1307,7 @@ struct Impl {
   // call makes anew is given back (the other buffer set is void: the bulk history
   // goes with it).
   static int to_dense(gpf_ctx* c) {
-    const gpf::KP<R> k = make_kp<R>(c);
+    const gpf::Rows padded = rows(c);
     HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));
     if (c->side) HIP_OR_FAIL(c, hipStreamSynchronize(c->side));
     drop_graphs(c);
@@ -1307,28 +1320,28 @@ struct Impl {
     c->lost = true;  // until all of it is there again
     set_pitch(c, c->n[0]);
     const size_t cs = (size_t)c->pcells * sizeof(R);
-    auto pack = [&](DevBuf& b, int ncomp) -> int {
+    auto move = [&](DevBuf& b, auto ncomp) -> int {
+      constexpr int C = decltype(ncomp)::value;
       if (!b.ptr) return GPF_OK;
-      hipLaunchKernelGGL((gpf::k_unpack<R, R, false>), dim3(lin_blocks(c->cells, 256)), dim3(256), 0, c->stream, k, P(b),
-                         P(c->scratch), ncomp, R(0), R(0));
+      unpack<C, R>(c, P(b), P(c->scratch), padded);
       HIP_OR_FAIL(c, hipGetLastError());
       HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));
       dev_release(c, b);
-      if (int rc = dev_alloc(c, b, ncomp * cs)) return rc;
-      HIP_OR_FAIL(c, hipMemcpyAsync(b.ptr, c->scratch.ptr, ncomp * cs, hipMemcpyDeviceToDevice, c->stream));
+      if (int rc = dev_alloc(c, b, C * cs)) return rc;
+      HIP_OR_FAIL(c, hipMemcpyAsync(b.ptr, c->scratch.ptr, C * cs, hipMemcpyDeviceToDevice, c->stream));
       return GPF_OK;
     };
-    auto pack_state = [&](DevBuf& phi, DevBuf& mu, DevBuf& u, DevBuf& f) -> int {
-      int rc = pack(phi, N);
-      if (!rc) rc = pack(mu, NC);
-      if (!rc) rc = pack(u, D);
-      return rc ? rc : pack(f, Q);
+    auto move_state = [&](DevBuf& phi, DevBuf& mu, DevBuf& u, DevBuf& f) -> int {
+      int rc = move(phi, std::integral_constant<int, N>());
+      if (!rc) rc = move(mu, std::integral_constant<int, NC>());
+      if (!rc) rc = move(u, std::integral_constant<int, D>());
+      return rc ? rc : move(f, std::integral_constant<int, Q>());
     };
-    int rc = pack_state(c->phi[c->cur], c->mu[c->cur], c->u[c->cur], c->f[c->cur]);
+    int rc = move_state(c->phi[c->cur], c->mu[c->cur], c->u[c->cur], c->f[c->cur]);
     for (StateBuf& s : c->ckpt)
-      if (!rc) rc = pack_state(s.phi, s.mu, s.u, s.f);
+      if (!rc) rc = move_state(s.phi, s.mu, s.u, s.f);
     for (StateBuf& l : c->lam)
-      if (!rc) rc = pack_state(l.phi, l.mu, l.u, l.f);
+      if (!rc) rc = move_state(l.phi, l.mu, l.u, l.f);
     if (!rc) rc = dev_alloc(c, c->phi[t], N * cs);
     if (!rc) rc = dev_alloc(c, c->mu[t], NC * cs);
     if (!rc) rc = dev_alloc(c, c->u[t], D * cs);
@@ -1342,18 +1355,17 @@ struct Impl {
   // adjoint of the recorded initial state, field by field, as FP64
   static int lam_read(gpf_ctx* c, int field, double* host) {
     StateBuf& l = c->lam[c->lam_cur];
-    const R* src = nullptr;
+    double* out = static_cast<double*>(c->scratch.ptr);
     int ncomp = 0;
     switch (field) {
-      case GPF_PHI: src = P(l.phi); ncomp = N; break;
-      case GPF_MU: src = P(l.mu); ncomp = NC; break;
-      case GPF_U: src = P(l.u); ncomp = D; break;
-      case GPF_F: src = P(l.f); ncomp = Q; break;
+      case GPF_PHI: ncomp = N; unpack<N, double>(c, P(l.phi), out); break;
+      case GPF_MU: ncomp = NC; unpack<NC, double>(c, P(l.mu), out); break;
+      case GPF_U: ncomp = D; unpack<D, double>(c, P(l.u), out); break;
+      case GPF_F: ncomp = Q; unpack<Q, double>(c, P(l.f), out); break;
       default: return fail(c, GPF_ERR_ARG, "field %d has no adjoint", field);
     }
+    HIP_OR_FAIL(c, hipGetLastError());
     const int64_t cnt = ncomp * c->cells;
-    hipLaunchKernelGGL((gpf::k_unpack<R, double, false>), dim3(lin_blocks(c->cells, 256)), dim3(256), 0, c->stream,
-                       make_kp<R>(c), src, static_cast<double*>(c->scratch.ptr), ncomp, 0.0, 0.0);
     HIP_OR_FAIL(c, hipMemcpyAsync(host, c->scratch.ptr, cnt * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIP_OR_FAIL(c, hipStreamSynchronize(c->stream));
     return GPF_OK;
