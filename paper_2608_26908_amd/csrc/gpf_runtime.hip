@@ -435,9 +435,10 @@ inline unsigned adj_blocks(const int64_t (&n)[3]) {
 }
 
 // tiles of k_phi in 3D (64 x 4 cells in 2D) and of k_mulbm (one plane in 2D),
-// and of k_step2 on grids of more and of at most small_grid's cells; one cell
-// per thread (measured, see the kernels; 32 x 4, 16 x 8 and 16 x 4 cells are
-// alike on small grids)
+// and of k_step2 on grids of more and of at most small_grid's cells (the small
+// one also where the other would leave half of its lanes without a cell, see
+// launch_step); one cell per thread (measured, see the kernels; 32 x 4, 16 x 8
+// and 16 x 4 cells are alike on small grids)
 #define GPF_PHI_TX 32
 #define GPF_PHI_TY 4
 #define GPF_PHI_TZ 2
@@ -504,7 +505,9 @@ struct Impl {
     if constexpr (D == 2) {
       if (fused_2d(c)) {
         if (ev) (void)hipEventRecord(ev[1], st);
-        if (small_grid(c))
+        // (of at most 32 columns or 4 rows: 16.5 us per step with the small tile, 24.9
+        // with the other, 100 000 x 4, three phases, FP32; 10.6 and 14.7 on 32 x 9000)
+        if (small_grid(c) || 2 * c->n[0] <= GPF_2D_TX || 2 * c->n[1] <= GPF_2D_TY)
           launch_2d<GPF_2DS_TX, GPF_2DS_TY>(c, k, in, out, ts, st, act_out);
         else
           launch_2d<GPF_2D_TX, GPF_2D_TY>(c, k, in, out, ts, st, act_out);
@@ -586,9 +589,13 @@ struct Impl {
   // between the 2 MiB (1024 x 512 in FP32) where it is the faster form and the
   // 4 MiB (the same in FP64) where it is not
   // (by the layout that row_pitch gives, so the choice stays when the padding is
-  // given up)
+  // given up).  Of a single row the tile's halo is most of the work: all phases
+  // together up to 768 KiB (us per step, one launch and two: 50 000 x 1, two phases,
+  // FP32 6.1, three phases, FP64 14.8 and 12.9; 300 000 x 1, three phases, FP32 30.8
+  // and 29.2, FP64 59.5 and 37.4).
   static bool fused_2d(const gpf_ctx* c) {
-    return D == 2 && row_pitch(c) * c->n[1] * (int64_t)sizeof(R) <= ((int64_t)3 << 20);
+    const int64_t phi = row_pitch(c) * c->n[1] * (int64_t)sizeof(R);
+    return D == 2 && (c->n[1] == 1 ? N * phi <= ((int64_t)768 << 10) : phi <= ((int64_t)3 << 20));
   }
 
   // one step of a 2D grid: a single launch
