@@ -972,17 +972,21 @@ struct Impl {
     return {dim3(nb), dim3(gpf::ADJ_BLOCK), static_cast<double*>(c->t_part.ptr), (int64_t)nb * gpf::NG,
             static_cast<uint8_t*>(c->t_rflag.ptr), static_cast<uint8_t*>(c->t_fflag.ptr)};
   }
-  // One launch per reverse step (k_adj_step2, adj_step_2d) of two and three
-  // phases up to 768 KiB per component, but not of three without anisotropy.  us per
-  // step of a sweep with checkpoints every 20 steps, three launches and one:
-  // two phases 21.1 and 14.9 (100^2, FP32), 24.4 and 22.1 (300^2), 27.6 and 25.0
-  // (362^2), 34.7 and 37.6 (512^2); FP64 21.8 and 16.6 (100^2), 30.1 and 27.6
-  // (300^2), 35.6 and 37.2 (362^2); three phases 45.3 and 29.7 (256^2, FP32), and
-  // without anisotropy, where k_adj_phi_iso runs, 23.6 and 23.9; four phases 54.7
-  // and 38.5 (144 x 256, FP32), but 63.7 and 69.1 in FP64 (registers).  The limit
-  // lies where the work on the tiles' halo (70 % of the cells) outweighs the launches.
+  // One launch per reverse step (k_adj_step2, adj_step_2d) of two phases up to
+  // 768 KiB per component and of three up to 200 KiB, but not of three without
+  // anisotropy.  us per step of a sweep with checkpoints every 20 steps, three
+  // launches and one: two phases 21.1 and 14.9 (100^2, FP32), 24.4 and 22.1 (300^2),
+  // 27.6 and 25.0 (362^2), 34.7 and 37.6 (512^2); FP64 21.8 and 16.6 (100^2), 30.1
+  // and 27.6 (300^2), 35.6 and 37.2 (362^2); three phases without anisotropy, where
+  // k_adj_phi_iso runs, 23.6 and 23.9 (256^2, FP32); four phases 54.7 and 38.5 (144
+  // x 256, FP32), but 63.7 and 69.1 in FP64 (registers).  us of 20 recorded steps and
+  // their sweep, three phases with one solute and with two: FP32 704 and 679, 759
+  // and 730 (160^2), 738 and 729, 795 and 810 (224^2), 817 and 845, 920 and 983
+  // (300^2); FP64 799 and 779, 865 and 858 (160^2), 874 and 911, 957 and 1223 (200^2),
+  // 1061 and 1233, 1242 and 1694 (300^2).  The limits lie where the work on the
+  // tiles' halo (70 % of the cells) outweighs the launches.
   static bool adj_one_fits(const gpf_ctx* c) {
-    return D == 2 && N <= 3 && c->n[0] * c->n[1] * (int64_t)sizeof(R) <= 768 << 10;
+    return D == 2 && N <= 3 && c->n[0] * c->n[1] * (int64_t)sizeof(R) <= (N == 2 ? 768 : 200) << 10;
   }
   static bool adj_one_launch(const gpf_ctx* c, const gpf::KP<R>& k) { return adj_one_fits(c) && (N == 2 || k.aniso); }
   // rows of running sums, one per block: the LBM reverse, then the mu / phi-local

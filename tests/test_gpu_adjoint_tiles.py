@@ -34,6 +34,12 @@ def test_dot_product_two_phases_without_anisotropy(oracle):
     _dot_product(oracle, busy_config("binary2d", [33, 17], delta=[[0, 0], [0, 0]]), 5, 3)
 
 
+@pytest.mark.parametrize("kind,n", [("ternary2d", [160, 160]), ("ternary2d_nc2", [161, 160])])
+def test_dot_product_at_the_limit_of_three_phases(oracle, kind, n):
+    """the last size with one launch in FP64 and the first with three"""
+    _dot_product(oracle, busy_config(kind, n, delta=[[0, 0, 0.04], [0, 0, 0.03], [0.04, 0.03, 0]]), 5, 3)
+
+
 def test_one_tape_bitwise():
     """a second tape that does not fit: the segments' ends are reversed by the
     same launches, so gradients and adjoint state keep their bits"""
