@@ -128,7 +128,10 @@ __device__ __forceinline__ PullAt<ROW> pull_at(const KP<R>& p, int x, int y, int
 
 // The populations f^n of the cell (x, y, z) (what pull_f does cell by cell)
 // for a wave whose lanes share the plane z and, with ROW, the row y: each
-// access is a scalar base plus the lane's 32-bit offset.  Every source is
+// access is a scalar base plus the lane's 32-bit offset.  (The bases come from
+// PullAt's own values, so they are formed per lane where lanes share neither, as
+// in k_partial: slower, and the same cells with ROW, whose lane part is x alone.)
+// Every source is
 // loaded first (clamped at walls); then the cells at a wall, in tiles at the
 // grid's faces only, take the reflected population f*_{opp k}(P) instead
 // (half-way bounce-back).
@@ -784,12 +787,14 @@ k_phi(KP<R> p, const R* __restrict__ phi, const R* __restrict__ mu, R* __restric
 // their lines within a CU: 629 -> 603 us on 256^3, 265 -> 246 on 250 x 200 x
 // 128, though 95 -> 109 on 128^3, where half of their lanes idle; in FP64 (1224
 // and 1228) and with more phases (176 and 178) they gain nothing.
-// Tiles of 32 x 4 x 2 where those of 64 columns leave at least a quarter of their
-// lanes without a cell (rows of up to 32 and of 65 to 96 cells); us per step with
-// 64 and with 32 columns: 49.1 and 45.8 (96^3, two phases, FP32), 83.8 and 78.8
-// (FP64), 48.8 and 44.7 (three phases), 23.9 and 18.1 (24 x 80 x 80), 47.1 and
-// 40.1 (66 x 70 x 60, FP64); but 107.6 and 110.4 on 150 x 131 x 117, where 64
-// leave 22 %.
+// Tiles of 32 x 4 x 2 on rows of up to 32 and of 65 to 96 cells, of whose lanes 64
+// columns leave a quarter and more without a cell; us per step with 64 and with 32
+// columns: 49.1 and 45.8 (96^3, two phases, FP32), 83.8 and 78.8 (FP64), 48.8 and
+// 44.7 (three phases), 23.9 and 18.1 (24 x 80 x 80), 47.1 and 40.1 (66 x 70 x 60,
+// FP64).  Rows of 129 to 160 cells, of whose lanes 64 columns leave 17 to 33 %, keep
+// 64: 129 x 128 x 96 83 and 85, three phases 101 and 105, 27 velocities on 129 x 160 x
+// 96 136 and 141, 150 x 128 x 96 84 and 86; in FP64 144 and 140, but three phases 216
+// and 171.
 // LDS-shared slots of a tile: its T cells (slot = thread), then the halo of
 // each face: z-, z+ (TX x TY cells each), y-, y+ (TX x TZ), x-, x+ (TY x TZ).
 template <int D, int TX, int TY, int TZ> struct MuTile {
@@ -887,7 +892,11 @@ k_mulbm(KP<R> p, const R* __restrict__ phi0, const R* __restrict__ phi1, const R
         R* __restrict__ fout, R* __restrict__ dr_out, const uint8_t* __restrict__ phi_bulk, int phi_lx, int phi_ly,
         int phi_lz, R tshift, int tiles_x, int tiles_y, int strip, Todo todo) {
   using M = MuTile<D, TX, TY, TZ>;
-  constexpr Access AC = N == 2 ? STREAM : EITHER;  // (two phases: nothing gained)
+  // Two phases stream whatever p.cached says.  With both forms in the code, which
+  // also changes how the compiler orders the loads, us per step were 46 -> 37 on 96^3
+  // (FP32, in the cache) and 95 -> 92 on 128^3, but 20.5 -> 21.6 on 64^3 and, FP64 and 27
+  // velocities, 343 -> 373 on 200 x 160 x 96.
+  constexpr Access AC = N == 2 ? STREAM : EITHER;
   constexpr bool ROW = TX % 64 == 0;
   static_assert(TX * TY >= 64 && (ROW || 64 % TX == 0), "a wave's lanes share a plane, and with ROW a row");
   static_assert(D == 3 || TZ == 1, "one plane in 2D");
@@ -1216,8 +1225,8 @@ __global__ void k_shift(KP<R> p, const R* __restrict__ in, R* __restrict__ out, 
 
 // f^n_k(P) = stored f*_k(P - c_k) (+ bounce-back), plus w_k rho0 in FP64: the
 // full f in dense order, as T.  A block owns 4 rows of 64 cells.  HBM bound
-// (one read and one write of the populations; going through an FP64 copy and a
-// conversion cost 261 us on FP64 150 x 131 x 117 against GATHERUS).
+// (one read and one write of the populations: 166 us a call on FP64 150 x 131 x
+// 117, through an FP64 copy and a conversion 277).
 template <int D, int Q, class R, class T>
 __global__ void __launch_bounds__(256) k_gather_f(KP<R> p, const R* __restrict__ fin, T* __restrict__ out, int tiles_x,
                                                   int tiles_y) {
@@ -1434,6 +1443,7 @@ k_partial(KP<R> p, int which, const R* __restrict__ phi, const R* __restrict__ m
       }
     } else if (which == 1) {
       R g[Q];
+      // (a wave's cells lie in rows of their own here: bases per lane, see pull_cell)
       pull_cell<D, Q, true, STREAM, R>(p, f, pull_at<D, true, R>(p, x, y, z), g);
       double r = 0.0;
 #pragma unroll

@@ -542,9 +542,9 @@ struct Impl {
       GPF_PHI(true);
 #undef GPF_PHI
     if (ev) (void)hipEventRecord(ev[1], st);
-    // tiles of whole 1 KiB rows where they fit, and tiles of 32 columns where
-    // 64 leave a quarter of the lanes and more without a cell (see k_mulbm; a
-    // plane's offsets are 32-bit there)
+    // tiles of whole 1 KiB rows where they fit, and tiles of 32 columns on rows of
+    // up to 32 and of 65 to 96 cells (see k_mulbm; a plane's offsets are 32-bit
+    // there)
     bool done = false;
     if constexpr (D == 3 && N == 2 && sizeof(R) == 4)
       if (c->n[0] % 256 == 0 || c->n[0] % 256 > 224) {
@@ -587,8 +587,7 @@ struct Impl {
 
   // 2D grids whose step is one launch (k_step2): up to 3 MiB per component,
   // between the 2 MiB (1024 x 512 in FP32) where it is the faster form and the
-  // 4 MiB (the same in FP64) where it is not
-  // (by the layout that row_pitch gives, so the choice stays when the padding is
+  // 4 MiB (the same in FP64) where it is not (by the layout that row_pitch gives, so the choice stays when the padding is
   // given up).  Of a single row the tile's halo is most of the work: all phases
   // together up to 768 KiB (us per step, one launch and two: 50 000 x 1, two phases,
   // FP32 6.1, three phases, FP64 14.8 and 12.9; 300 000 x 1, three phases, FP32 30.8

@@ -69,3 +69,30 @@ def test_rows_without_padding(oracle, kind, n):
     """widths whose rows are stored as they come, none a multiple of a line: up to 64 cells, in 2D above 2^17 cells,
     and three phases whose state fits the last-level cache"""
     _check(busy_config(kind, n), 2)
+
+
+@pytest.mark.parametrize("kind,n,precision", [
+    ("binary2d", [1, 1], "fp64"), ("binary2d", [31, 33], "fp32"), ("ternary2d_nc2", [41, 25], "fp64"),
+    ("binary3d", [65, 5, 3], "fp32"), ("quaternary3d", [33, 31, 2], "fp64")])
+def test_copies_between_stored_and_dense_form(kind, n, precision):
+    """reads, device reads, writes and the loss seed: blocks of 1024 cells (1, 1023, 1025 and more), rows padded and
+    as they come; copies, so exact"""
+    from paper_2608_26908_amd.gpf import Sim
+    cfg = busy_config(kind, n)
+    st = random_state(cfg, 3)
+    s = Sim(cfg, precision=precision)
+    real = np.float64 if precision == "fp64" else np.float32
+    for k in ("phi", "u"):
+        s.write(k, st[k])
+        assert np.array_equal(s.read(k), st[k].astype(real)), k
+        assert np.array_equal(s.read_device(k).cpu().numpy(), st[k].astype(real)), k
+    s.write("mu", st["mu"])
+    # stored less a reference in FP32: one rounding of values of order one
+    assert np.abs(s.read("mu") - st["mu"]).max() <= (0.0 if precision == "fp64" else 2.0 ** -23)
+    fpost = 0.01 * np.random.default_rng(4).standard_normal(st["f"].shape)
+    s.write("fpost", fpost)
+    assert np.array_equal(s.read("fpost"), fpost.astype(real))
+    target = np.random.default_rng(5).uniform(size=st["phi"].shape)
+    s.set_target(target)
+    assert np.array_equal(s.loss_seed().cpu().numpy(), st["phi"].astype(real).astype(np.float64) - target)
+    s.close()
