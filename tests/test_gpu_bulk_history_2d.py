@@ -40,3 +40,18 @@ def test_bulk_history_skip_2d_is_bitwise(name, n, precision, over):
         assert np.array_equal(a.read(k), b.read(k)), k
     a.close()
     b.close()
+
+
+def test_bulk_history_of_a_single_row_is_bitwise():
+    """long single rows step in two launches below that limit too"""
+    from paper_2608_26908_amd.gpf import Sim
+    cfg = scaled("dendrite2d", [200001, 1], init_center=[100000.0, 0.0])
+    a, b = Sim(cfg, precision="fp32"), Sim(cfg, precision="fp32")
+    a.step(40)
+    for _ in range(40):
+        b.step(1)
+        b.write("phi", b.read("phi"))  # voids the history
+    for k in STATE:
+        assert np.array_equal(a.read(k), b.read(k)), k
+    a.close()
+    b.close()

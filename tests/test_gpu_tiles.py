@@ -96,3 +96,12 @@ def test_copies_between_stored_and_dense_form(kind, n, precision):
     s.set_target(target)
     assert np.array_equal(s.loss_seed().cpu().numpy(), st["phi"].astype(real).astype(np.float64) - target)
     s.close()
+
+
+@pytest.mark.parametrize("kind,n", [
+    # above 2^18 cells on at most 32 columns or 4 rows: the small tile of the one-launch step, and one past the limit
+    ("binary2d", [32, 8193]), ("binary2d", [65537, 4]), ("binary2d", [53000, 5]),
+    # single rows in two launches (all phases above 768 KiB) and in one
+    ("ternary2d", [66001, 1]), ("quaternary2d", [30001, 1]), ("binary2d", [6001, 1])])
+def test_thin_2d_grids(oracle, kind, n):
+    _check(busy_config(kind, n), 2)
